@@ -581,7 +581,7 @@ static fg_status bwd_weight(const fg_conv_desc *d, const uint16_t *x,
   a.mchunk = pl.mchunk;
   a.nsplit = pl.nsplit;
   a.flag = found_nonfinite;
-  return launch_status(launch_wgrad(a, pl.big, stream));
+  return launch_status(launch_wgrad(a, pl.tile, stream));
 }
 
 fg_status conv2d_bwd_weight(const fg_conv_desc *d, const uint16_t *x,

@@ -1,11 +1,11 @@
-// Implicit-GEMM convolutions fed by LDS DMA (gfx950 buffer_load ... lds).
+// Implicit-GEMM convolutions fed by LDS DMA (gfx950 buffer_load ... lds): the
+// data convolutions, then the kernel gradients.
 //
 // Same GEMM formulation as the register-staged kernels in conv_igemm.hip
-// (data convolutions: rows = output channels, columns = output positions of
-// one phase; kernel gradient: rows = (tap, input channel), columns = output
-// channels), for 256 x 256 tiles. Operands go from global memory straight
+// (rows = output channels, columns = output positions of one phase), for
+// 256 x 256 and 128 x 128 tiles. Operands go from global memory straight
 // into LDS: no register staging and no LDS store instructions. A ring of NS
-// reduction stages, each BK deep, holds 128 KiB, so a stage's loads are
+// reduction stages, each BK deep, is kept in LDS, so a stage's loads are
 // issued NS - 1 stages before they are consumed. Padding and ragged tails
 // cost nothing: an out-of-range buffer offset returns zeros. The tile is
 // split among WGM x WGN waves; stage depth, ring length and wave grid are
@@ -29,48 +29,19 @@
 // memory (input-gradient and transposed-conv weights, both kernel-gradient
 // operands) be copied row by row as they lie in memory.
 #include <algorithm>
-#include <type_traits>
 
-#include "common.h"
-#include "internal.h"
+#include "dma_pipe.h"
 
 namespace fg {
 namespace dma {
 
 constexpr int TM = 256, TN = 256;       // output tile of the large kernels
-constexpr unsigned kOOB = 0x80000000u;   // beyond any tensor: loads zero
-
-// Pipeline configuration: T x T output tile, BK-deep reduction stages, NS of
-// them in the LDS ring, WGM x WGN waves each owning (T/WGM) x (T/WGN).
-template <int BK_, int NS_, int WGM_, int WGN_, int T_ = 256>
-struct K {
-  static constexpr int BK = BK_, NS = NS_, WGM = WGM_, WGN = WGN_, T = T_;
-  static constexpr int NW = WGM * WGN, NT = 64 * NW;
-  static constexpr int WM = T / WGM, WN = T / WGN;
-  static constexpr int FM = WM / 32, FN = WN / 32;
-  static constexpr int KS = BK / 16;                 // MFMA steps per stage
-  static constexpr int TILE_BYTES = T * BK * 2;      // per operand per stage
-  static constexpr int NI = TILE_BYTES / 1024;       // DMA instrs per operand
-  static constexpr int PW = NI / NW;                 // ... per wave
-  static constexpr int CPR = BK / 8;                 // 16-byte chunks per row
-  static constexpr int RB = 2 * T;                   // mn-major row bytes
-  static constexpr int RPI = 1024 / RB;              // mn-major rows per DMA
-  // waves per SIMD the kernel must fit (small tiles run two per CU)
-  static constexpr int WPE = T == 128 ? 2 * NW / 4 : (NW + 3) / 4;
-  static_assert(NI % NW == 0, "DMA instructions must divide among waves");
-};
-// The configurations the library runs, chosen by timing the network's layers:
-// data convolutions take 32-deep stages in a 5-stage ring (160 KiB) with 8
-// waves of 128 x 64; the kernel gradient 32-deep stages in a 4-stage ring
-// (128 KiB) with 8 waves of 128 x 64.
+// The configuration the library runs, chosen by timing the network's layers:
+// 32-deep stages in a 5-stage ring (160 KiB) with 8 waves of 128 x 64.
 #ifndef FG_DMA_DATA_CFG
 #define FG_DMA_DATA_CFG 32, 5, 2, 4
 #endif
-#ifndef FG_DMA_WGRAD_CFG
-#define FG_DMA_WGRAD_CFG 32, 4, 2, 4
-#endif
 using DataRun = K<FG_DMA_DATA_CFG>;
-using WgradRun = K<FG_DMA_WGRAD_CFG>;
 #ifndef FG_DMA_HALO_NS
 #define FG_DMA_HALO_NS 3
 #endif
@@ -78,399 +49,6 @@ using HaloRun = K<32, FG_DMA_HALO_NS, 2, 4>;  // weights ring; the rest is patch
 // 128 x 128 tiles for layers with few output positions: 4 waves of 64 x 64,
 // 80 KiB of ring, two workgroups per CU
 using SmallRun = K<32, 5, 2, 2, 128>;
-constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format
-
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) v4s lds_v4s;
-typedef __attribute__((address_space(3))) void lds_void;
-
-// k-major: 16-byte chunk c of tile row `row` (bytes). 64-byte rows (BK 32)
-// permute the 4 chunks by g(row); 128-byte rows (BK 64) the 8 chunks.
-// mn-major: byte xor of reduction row k, below 256 so that rows of 256 bytes
-// take it too. MX = 1: 64-byte blocks permuted by k & 3 (conflict-free
-// transposing reads); MX = 0: 32-byte blocks permuted by (k & 3) | bit 3 of k
-// (two-way conflicts), kept for the halo kernel's weights, whose register
-// allocation spills into its main loop with the other permutation.
-template <int BK>
-__device__ __forceinline__ int kmaj_swz(int row) {
-  return BK == 32 ? ((row >> 2) & 3) : ((row ^ (row >> 3)) & 7);
-}
-template <int BK>
-__device__ __forceinline__ int kmaj_off(int row, int c) {
-  return row * (2 * BK) + ((c ^ kmaj_swz<BK>(row)) << 4);
-}
-template <int MX>
-__device__ __forceinline__ int mn_xor(int k) {
-  return MX ? (k & 3) << 6 : ((k & 3) | (((k >> 3) & 1) << 2)) << 5;
-}
-template <int RB, int MX = 1>
-__device__ __forceinline__ int mnmaj_off(int k, int n) {  // bytes, n % 4 == 0
-  return k * RB + ((2 * n) ^ mn_xor<MX>(k));
-}
-
-// Workgroup barrier without a memory fence. __syncthreads() would add a
-// release fence, which waits for every outstanding LDS-DMA load (vmcnt(0))
-// and so drains the ring; ordering is established instead by each wave's
-// explicit vmcnt wait on its own loads before it arrives here. The empty asm
-// statements keep the compiler from moving LDS accesses across the barrier.
-__device__ __forceinline__ void barrier_nofence() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// s_waitcnt with only vmcnt constrained (gfx9 encoding).
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | (((N >> 4) & 3) << 14));
-}
-
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rs, uint8_t *lds,
-                                      unsigned voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)lds, 16, voff, 0, 0, 0);
-}
-
-// Tile order across the chip. Workgroups are handed to the 8 XCDs (each with
-// its own L2) round-robin by launch index L; tile v = (L % 8) * per + L / 8
-// gives each XCD a contiguous run of the tile sequence, in which neighbours
-// share operands (the output channels of one column tile, the halo rows of
-// adjacent column tiles, one reduction chunk), so they are fetched into that
-// XCD's L2 once. The grid is 8 * per one-dimensional; indices past the tile
-// count exit.
-// With `linear`, tile v = L instead: launch order is tile order, for launches
-// whose tiles differ in cost and are listed costliest first.
-struct TileMap {
-  int32_t n0, n1, n2;  // tile counts, fastest first
-  int32_t per;         // ceil(n0 * n1 * n2 / 8)
-  int32_t linear;
-  __device__ __forceinline__ bool decode(int L, int &i0, int &i1, int &i2) const {
-    const int v = linear ? L : (L & 7) * per + (L >> 3);
-    if (v >= n0 * n1 * n2) return false;
-    i0 = v % n0;
-    const int r = v / n0;
-    i1 = r % n1;
-    i2 = r / n1;
-    return true;
-  }
-};
-
-// Unsigned division by a divisor fixed per launch, as a multiply-high and two
-// shifts (Granlund and Montgomery, "Division by invariant integers using
-// multiplication", 1994): exact for every 32-bit dividend.
-struct FastDiv {
-  uint32_t magic;
-  int32_t s1, s2;
-  __device__ __forceinline__ unsigned div(unsigned n) const {
-    const unsigned t = __umulhi(magic, n);
-    return (t + ((n - t) >> s1)) >> s2;
-  }
-};
-struct WgradDiv {
-  FastDiv pq, q;  // by p * q and by q
-};
-
-// MFMA operand of a 32-row block starting at `base` for reduction step ks.
-template <int BK, bool KMAJOR, int RB = 512, int MX = 1>
-__device__ __forceinline__ u32x4 frag(const uint8_t *tile, int base, int ks,
-                                      int lane) {
-  if (KMAJOR) {
-    return *reinterpret_cast<const u32x4 *>(
-        tile + kmaj_off<BK>(base + (lane & 31), 2 * ks + (lane >> 5)));
-  } else {
-    const int g = lane >> 4, m = lane & 15;
-    const int k = 8 * (g >> 1) + (m >> 2) + 16 * ks;
-    const int n = base + 16 * (g & 1) + 4 * (m & 3);
-    v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_v4s *)(tile + mnmaj_off<RB, MX>(k, n)));
-    v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_v4s *)(tile + mnmaj_off<RB, MX>(k + 4, n)));
-    u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
-    return u32x4{a[0], a[1], b[0], b[1]};
-  }
-}
-
-// Fragments of one 16-deep reduction step for this wave.
-template <class C>
-struct Frags {
-  u32x4 a[C::FM], b[C::FN];
-};
-
-template <class C, bool AK, bool BKM>
-__device__ __forceinline__ void load_frags(Frags<C> &f, const uint8_t *ta,
-                                           const uint8_t *tb, int ks, int wm0,
-                                           int wn0, int lane) {
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-    f.a[i] = frag<C::BK, AK, C::RB>(ta, wm0 + 32 * i, ks, lane);
-#pragma unroll
-  for (int j = 0; j < C::FN; ++j)
-    f.b[j] = frag<C::BK, BKM, C::RB>(tb, wn0 + 32 * j, ks, lane);
-}
-
-template <class C>
-__device__ __forceinline__ void mma(f32x16 (&acc)[C::FM][C::FN],
-                                    const Frags<C> &f) {
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) acc[i][j] = mfma32(f.a[i], f.b[j], acc[i][j]);
-}
-
-// s_waitcnt with only lgkmcnt (LDS) constrained to 0.
-__device__ __forceinline__ void wait_lds() {
-  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-}
-
-// Position of this lane's DMA slots (one per wave instruction jj) in a
-// k-major tile (row, reduction offset of the chunk) and in an mn-major tile
-// (reduction row within the stage, tile column). Each instruction fills 1 KiB
-// of LDS: 512/BK k-major rows or 1024/RB mn-major rows.
-template <class C>
-struct KmSlot {
-  int row[C::PW], coff[C::PW];
-};
-template <class C>
-struct MnSlot {
-  int krow[C::PW], ncol[C::PW];
-};
-
-template <class C>
-__device__ __forceinline__ KmSlot<C> km_slots(int wave, int lane) {
-  KmSlot<C> s;
-#pragma unroll
-  for (int jj = 0; jj < C::PW; ++jj) {
-    int row = (512 / C::BK) * (C::PW * wave + jj) + lane / C::CPR;
-    int pc = lane % C::CPR;
-    s.row[jj] = row;
-    s.coff[jj] = 8 * (pc ^ kmaj_swz<C::BK>(row));
-  }
-  return s;
-}
-
-template <class C, int MX = 1>
-__device__ __forceinline__ MnSlot<C> mn_slots(int wave, int lane) {
-  MnSlot<C> s;
-#pragma unroll
-  for (int jj = 0; jj < C::PW; ++jj) {
-    constexpr int CPM = C::RB / 16;  // 16-byte chunks per mn-major row
-    int k = C::RPI * (C::PW * wave + jj) + lane / CPM;
-    int p = lane % CPM;
-    s.krow[jj] = k;
-    s.ncol[jj] = ((16 * p) ^ mn_xor<MX>(k)) / 2;
-  }
-  return s;
-}
-
-// LDS destination (bytes, wave-uniform) of wave instruction jj of a stage.
-template <class C>
-__device__ __forceinline__ int dma_dst(int wave, int jj) {
-  return 1024 * (C::PW * wave + jj);
-}
-
-__device__ __forceinline__ u32x2 to_h4(float a, float b, float c, float d) {
-  u32x2 o;
-  o[0] = (uint32_t)f32_to_h(a) | ((uint32_t)f32_to_h(b) << 16);
-  o[1] = (uint32_t)f32_to_h(c) | ((uint32_t)f32_to_h(d) << 16);
-  return o;
-}
-
-// Apply the epilogue to 4 consecutive channels; gate and out point at them
-// (out is read for FG_EPI_ACC only).
-__device__ __forceinline__ void epilogue4(float v[4], int epi, const uint16_t *gate,
-                                          const uint16_t *out) {
-  if (epi == FG_EPI_RELU) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
-  } else if (epi == FG_EPI_GATE) {
-    u32x2 gw = *reinterpret_cast<const u32x2 *>(gate);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint16_t gb = (uint16_t)(gw[e >> 1] >> (16 * (e & 1)));
-      v[e] = h_to_f32(gb) > 0.f ? v[e] : 0.f;
-    }
-  } else if (epi == FG_EPI_ACC) {
-    u32x2 ow = *reinterpret_cast<const u32x2 *>(out);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      v[e] += h_to_f32((uint16_t)(ow[e >> 1] >> (16 * (e & 1))));
-  }
-}
-
-// fp16(a + b) for 8 packed pairs (fp32 sum of two fp16 values, one rounding
-// to fp16; the sum of two fp16 values is exact in fp32 unless it is far
-// below the larger's last bit, where the rounding is the same)
-__device__ __forceinline__ u32x4 add_h8(const u32x4 &a, const u32x4 &b) {
-  u32x4 o;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float lo = h_to_f32((uint16_t)(a[w] & 0xFFFFu)) + h_to_f32((uint16_t)(b[w] & 0xFFFFu));
-    const float hi = h_to_f32((uint16_t)(a[w] >> 16)) + h_to_f32((uint16_t)(b[w] >> 16));
-    o[w] = (uint32_t)f32_to_h(lo) | ((uint32_t)f32_to_h(hi) << 16);
-  }
-  return o;
-}
-
-// The ring: stage s of operand X lives in its own LDS array so that the
-// compiler can tell the stages apart when it places waits. Unused slots of a
-// ring shorter than five stages are token-sized.
-struct Ring {
-  uint8_t *a[5];
-  uint8_t *b[5];
-};
-#define FG_DMA_RING(C, R)                                                     \
-  constexpr int T0_ = C::TILE_BYTES, T2_ = C::NS > 2 ? T0_ : 16,              \
-                T3_ = C::NS > 3 ? T0_ : 16, T4_ = C::NS > 4 ? T0_ : 16;       \
-  __shared__ __attribute__((aligned(1024))) uint8_t sA0[T0_], sA1[T0_],       \
-      sA2[T2_], sA3[T3_], sA4[T4_];                                           \
-  __shared__ __attribute__((aligned(1024))) uint8_t sB0[T0_], sB1[T0_],       \
-      sB2[T2_], sB3[T3_], sB4[T4_];                                           \
-  Ring R;                                                                     \
-  R.a[0] = sA0, R.a[1] = sA1, R.a[2] = sA2, R.a[3] = sA3, R.a[4] = sA4;        \
-  R.b[0] = sB0, R.b[1] = sB1, R.b[2] = sB2, R.b[3] = sB3, R.b[4] = sB4
-
-// Wait until at most n stages of this wave's DMA loads remain outstanding
-// (n <= 3; each stage is 2 * PW load instructions).
-template <class C>
-__device__ __forceinline__ void wait_stages(int n) {
-  constexpr int PS = 2 * C::PW;
-  static_assert(3 * PS < 64, "vmcnt range");
-  if (n >= 3) wait_vm<3 * PS>();
-  else if (n == 2) wait_vm<2 * PS>();
-  else if (n == 1) wait_vm<PS>();
-  else wait_vm<0>();
-}
-
-// Instruction-scheduling hints (LLVM AMDGPU IGroupLP): within the current
-// scheduling region, place the MFMAs one by one and put `per` LDS reads
-// after each of the first ones, so the reads of the next step issue among
-// the MFMAs of this one instead of in a block.
-template <int NMF, int NRD>
-__device__ __forceinline__ void sched_mfma_reads() {
-  constexpr int per = (NRD + NMF - 1) / NMF;
-#pragma unroll
-  for (int i = 0; i < NMF; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-    if (i * per < NRD) __builtin_amdgcn_sched_group_barrier(0x100, per, 0);  // DS read
-  }
-}
-// After the barrier: reads first (they gate the next step), then the DMA
-// loads of the refilled slot with their address arithmetic.
-template <int NMF, int NRD, int NVM>
-__device__ __forceinline__ void sched_mfma_reads_dma() {
-  constexpr int per = (NRD + NMF / 2 - 1) / (NMF / 2);
-#pragma unroll
-  for (int i = 0; i < NMF / 2; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (i * per < NRD) __builtin_amdgcn_sched_group_barrier(0x100, per, 0);
-  }
-  constexpr int pv = (NVM + NMF / 2 - 1) / (NMF / 2);
-#pragma unroll
-  for (int i = 0; i < NMF / 2; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (i * pv < NVM) {
-      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
-      __builtin_amdgcn_sched_group_barrier(0x020, pv, 0);  // VMEM read
-    }
-  }
-}
-
-// One stage (ring slot U) of the main loop. With `next`, the stage has a
-// successor: the barrier that publishes it is crossed before the last step
-// and the successor's first fragments are read into f[0]. `full` asserts
-// that NS - 2 stages after the successor have been issued and that stage
-// it + NS exists.
-template <class C, bool AK, bool BKM, int U, class Issue>
-__device__ __forceinline__ void stage(f32x16 (&acc)[C::FM][C::FN],
-                                      Frags<C> (&f)[2], const Ring &R, int it,
-                                      int nst, bool next, bool full, int wm0,
-                                      int wn0, int lane, Issue &issue) {
-  constexpr int NS = C::NS, KS = C::KS;
-  constexpr int NMF = C::FM * C::FN;
-  constexpr int NRD = C::FM * (AK ? 1 : 2) + C::FN * (BKM ? 1 : 2);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    if (ks + 1 < KS)
-      load_frags<C, AK, BKM>(f[(ks + 1) & 1], R.a[U], R.b[U], ks + 1, wm0, wn0,
-                             lane);
-    mma<C>(acc, f[ks & 1]);
-    if (ks + 1 < KS) sched_mfma_reads<NMF, NRD>();
-    __builtin_amdgcn_s_setprio(0);
-    if (ks == KS - 2 && next) {
-      // own DMA of stage it+1 done: later stages may remain in flight
-      wait_stages<C>(full ? NS - 2 : min(NS - 2, nst - 2 - it));
-      wait_lds();  // this wave's reads of slot U are complete
-      barrier_nofence();
-      // Past the barrier a wave has memory work to start (the refill DMA,
-      // the next stage's first fragments) before its next MFMAs: raise its
-      // issue priority over the other wave on its SIMD until those MFMAs
-      // are issued, so the loads go out early. The priority drops back to 0
-      // after every MFMA block. (Measured: 1-4% per layer.)
-      __builtin_amdgcn_s_setprio(2);
-      if (full || it + NS < nst) issue(it + NS, U);
-      load_frags<C, AK, BKM>(f[0], R.a[(U + 1) % NS], R.b[(U + 1) % NS], 0, wm0,
-                             wn0, lane);
-    }
-  }
-  if (next) sched_mfma_reads_dma<NMF, NRD, 2 * C::PW>();
-}
-
-template <class C, bool AK, bool BKM, int U, class Issue>
-__device__ __forceinline__ void group(f32x16 (&acc)[C::FM][C::FN],
-                                      Frags<C> (&f)[2], const Ring &R, int it0,
-                                      int nst, bool tail, int wm0, int wn0,
-                                      int lane, Issue &issue) {
-  if constexpr (U < C::NS) {
-    const int it = it0 + U;
-    if (!tail) {
-      stage<C, AK, BKM, U>(acc, f, R, it, nst, true, true, wm0, wn0, lane, issue);
-    } else if (it < nst) {
-      stage<C, AK, BKM, U>(acc, f, R, it, nst, it + 1 < nst, false, wm0, wn0,
-                           lane, issue);
-    }
-    group<C, AK, BKM, U + 1>(acc, f, R, it0, nst, tail, wm0, wn0, lane, issue);
-  }
-}
-
-// Runs the pipelined main loop over stages [0, nst): issue(st, slot) issues
-// this wave's DMA loads of stage st into ring slot `slot`; stages are issued
-// strictly in order. Full groups of NS stages run in a loop whose body has no
-// data-dependent control flow around the MFMAs (so the compiler's own LDS
-// waits stay exact and its scheduling regions span whole steps); the last
-// groups run with per-stage checks.
-template <class C, bool AK, bool BKM, class Issue>
-__device__ __forceinline__ void pipeline(f32x16 (&acc)[C::FM][C::FN],
-                                         const Ring &R, int nst, int wm0,
-                                         int wn0, int lane, Issue &&issue) {
-  constexpr int NS = C::NS, KS = C::KS;
-  static_assert(NS >= 2 && NS <= 5 && KS >= 2 && KS % 2 == 0, "pipeline shape");
-  if (nst <= 0) return;
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (s < nst) issue(s, s);
-  wait_stages<C>(min(NS - 2, nst - 1));  // publish stage 0
-  barrier_nofence();
-  if (NS - 1 < nst) issue(NS - 1, NS - 1);
-  Frags<C> f[2];
-  load_frags<C, AK, BKM>(f[0], R.a[0], R.b[0], 0, wm0, wn0, lane);
-  // In a full group every stage has a successor, NS - 2 stages issued after
-  // it, and a stage NS ahead to issue, so its waits and issues need no
-  // checks: it0 + 2 NS - 1 < nst.
-  int it0 = 0;
-  for (; it0 + 2 * NS - 1 < nst; it0 += NS)
-    group<C, AK, BKM, 0>(acc, f, R, it0, nst, false, wm0, wn0, lane, issue);
-  for (; it0 < nst; it0 += NS)
-    group<C, AK, BKM, 0>(acc, f, R, it0, nst, true, wm0, wn0, lane, issue);
-}
-
-template <class C>
-__device__ __forceinline__ void zero(f32x16 (&acc)[C::FM][C::FN]) {
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-}
 
 // ---------------------------------------------------------------------------
 // Output tile store of the data convolutions. The accumulator layout gives
@@ -672,7 +250,7 @@ __global__ __launch_bounds__(C::NT, C::WPE) void data_conv_dma_kernel(DataConvAr
 
   // B: this lane's output positions (image row/column of tap (0, 0) of the
   // phase) and element offsets
-  const KmSlot<C> bs = km_slots<C>(wave, lane);
+  const KmSlot<PW> bs = km_slots<C::BK, PW>(wave, lane);
   int bh[PW], bw[PW], bbase[PW];
 #pragma unroll
   for (int jj = 0; jj < PW; ++jj) {
@@ -696,12 +274,12 @@ __global__ __launch_bounds__(C::NT, C::WPE) void data_conv_dma_kernel(DataConvAr
 #pragma unroll
   for (int jj = 0; jj < PW; ++jj) {
     if (WK) {
-      const KmSlot<C> as = km_slots<C>(wave, lane);
+      const KmSlot<PW> as = km_slots<C::BK, PW>(wave, lane);
       const int co = m0 + as.row[jj];
       wok[jj] = co < a.co;
       wbase[jj] = co * a.ldw + as.coff[jj];
     } else {
-      const MnSlot<C> as = mn_slots<C>(wave, lane);
+      const MnSlot<PW> as = mn_slots<C::RB, PW>(wave, lane);
       const int co = m0 + as.ncol[jj];
       wok[jj] = co < a.co;
       wbase[jj] = as.krow[jj] * a.w_red + co;
@@ -729,12 +307,12 @@ __global__ __launch_bounds__(C::NT, C::WPE) void data_conv_dma_kernel(DataConvAr
       const bool v = (unsigned)(bh[jj] + dh) < (unsigned)a.hi &&
                      (unsigned)(bw[jj] + dw) < (unsigned)a.wi;
       const unsigned o = (unsigned)(bbase[jj] + delta) * 2u;
-      dma16(rs_act, tb + dma_dst<C>(wave, jj), v ? o : kOOB);
+      dma16(rs_act, tb + dma_dst<PW>(wave, jj), v ? o : kOOB);
     }
 #pragma unroll
     for (int jj = 0; jj < PW; ++jj) {
       const unsigned o = (unsigned)(wbase[jj] + wst) * 2u;
-      dma16(rs_w, ta + dma_dst<C>(wave, jj), wok[jj] ? o : kOOB);
+      dma16(rs_w, ta + dma_dst<PW>(wave, jj), wok[jj] ? o : kOOB);
     }
     // next stage, without branches (keeps the scheduling region whole)
     cr0 += C::BK;
@@ -886,12 +464,12 @@ __global__ __launch_bounds__(C::NT) void data_conv_halo_kernel(DataConvArgs a,
 #pragma unroll
   for (int jj = 0; jj < PW; ++jj) {
     if (WK) {
-      const KmSlot<C> as = km_slots<C>(wave, lane);
+      const KmSlot<PW> as = km_slots<C::BK, PW>(wave, lane);
       const int co = m0 + as.row[jj];
       wok[jj] = co < a.co;
       wbase[jj] = co * a.ldw + as.coff[jj];
     } else {
-      const MnSlot<C> as = mn_slots<C, 0>(wave, lane);
+      const MnSlot<PW> as = mn_slots<C::RB, PW, 0>(wave, lane);
       const int co = m0 + as.ncol[jj];
       wok[jj] = co < a.co;
       wbase[jj] = as.krow[jj] * a.w_red + co;
@@ -908,7 +486,7 @@ __global__ __launch_bounds__(C::NT) void data_conv_halo_kernel(DataConvArgs a,
 #pragma unroll
     for (int jj = 0; jj < PW; ++jj) {
       const unsigned o = (unsigned)(wbase[jj] + wst) * 2u;
-      dma16(rs_w, ringA[slot] + dma_dst<C>(wave, jj), live && wok[jj] ? o : kOOB);
+      dma16(rs_w, ringA[slot] + dma_dst<PW>(wave, jj), live && wok[jj] ? o : kOOB);
     }
     const bool wrap = ++it_ == kHaloTaps;
     it_ = wrap ? 0 : it_;
@@ -1000,213 +578,284 @@ __global__ __launch_bounds__(C::NT) void data_conv_halo_kernel(DataConvArgs a,
 }
 
 // ---------------------------------------------------------------------------
-// Output tile store of the kernel gradient: rows rho (contiguous in memory
-// for a fixed output channel k), columns k. As for the data convolutions, a
-// wave's block is staged in LDS k-major, 64 rows of rho at a time (128-byte
-// rows: 64 fp16 or, per pass, 32 fp32 values; 16-byte chunks permuted by the
-// row), and read back so that 8 lanes write one row's contiguous 128 bytes.
-// Waves 64 rows high stage 8 KiB (two per 16 KiB ring array), waves 128 rows
-// high two halves of 8 KiB in a ring array of their own.
-template <class C, bool SPLIT>
-__device__ __forceinline__ void store_tile_w(f32x16 (&acc)[C::FM][C::FN],
-                                             const Ring &R, const WgradArgs &a,
-                                             int rsc, int rho0, int k0, int lane,
-                                             int wave, int split) {
-  static_assert((C::WM == 64 || C::WM == 128) && C::WN == 64,
-                "store_tile_w expects waves 64 wide and 64 or 128 high");
-  constexpr int HM = C::WM / 64;   // 64-row halves of the wave's block
-  constexpr int WPA = 2 / HM;      // waves per 16 KiB ring array
-  // the ring arrays 0..NW/WPA-1 (a[0..NS-1], then b[0..]) must exist and be
-  // 16 KiB each
-  static_assert(C::TILE_BYTES == 16384 && C::NW / WPA <= 2 * C::NS,
-                "store_tile_w stages in 16 KiB ring arrays");
-  __syncthreads();  // every wave is done reading the ring
-  uint8_t *buf = R.a[0];
+// Kernel gradients fed by LDS DMA, for any channel counts (multiples of 8).
+//
+// Rows rho = (tap, input channel), columns = output channels, reduction over
+// output positions; both operands are copied row by row from memory into
+// mn-major LDS tiles and read with transposing LDS reads. A tile may straddle
+// taps and run past the last row or column: each lane copies 8 channels, which
+// lie in one tap, so the tap is a property of the lane, decoded once; chunks
+// past the end get an out-of-range offset and read zeros.
+//
+// Three square tiles. 256 has the fewest LDS and L2 bytes per multiply and runs
+// the layers with enough tiles and positions to fill the CUs; the others are
+// bound by the chain of one workgroup's stages (about 0.3 us per 64 rows) and
+// by how few workgroups there are, so they take smaller tiles: 256 x 9 x 256
+// over 1800 positions 41 us on one 256 tile row of workgroups, 27.9 at its best
+// split, 13.4 unsplit on 64 tiles. Against the register-staged kernels that
+// these shapes ran before: 128 x 1152 x 32768 39 -> 27 us with its reduction,
+// 160 x 864 x 20925 33 -> 24, 320 x 320 x 21756 65 -> 21.
+
+// Tiles. 64-deep stages (whole 128-byte lines of both operands per barrier) for
+// the small ones, whose time is the chain of stages.
+using Tile256 = Pipe<32, 4, 2, 4, 256, 256>;  // 8 waves of 128 x 64
+using Tile128 = Pipe<64, 2, 2, 2, 128, 128>;  // 4 waves of 64 x 64
+using Tile64 = Pipe<64, 3, 2, 2, 64, 64>;     // 4 waves of 32 x 32
+
+// Store of a wave's WM x WN block: rows rho (contiguous in memory for a fixed
+// output channel k) within rsc, columns k within a.k. Staged in this wave's
+// part of the ring k-major, 64 rows of rho at a time (128-byte rows: 64 fp16
+// or, per pass, 32 fp32 values; 16-byte chunks permuted by the row), and read
+// back so that 8 lanes write one row's contiguous 128 bytes.
+template <class P, bool SPLIT>
+__device__ __forceinline__ void store_rho(f32x16 (&acc)[P::FM][P::FN], uint8_t *buf,
+                                          const WgradArgs &a, int rsc, int rho0, int k0,
+                                          int lane, int split) {
+  static_assert(P::WM % 64 == 0 && P::WN == 64, "staged blocks are 64 wide");
+  constexpr int HM = P::WM / 64, PASSES = SPLIT ? 2 : 1;
+  bool bad = false;
 #pragma unroll
-  for (int k = 1; k < C::NW / WPA; ++k)
-    if (wave / WPA == k) buf = k < C::NS ? R.a[k] : R.b[k - C::NS];
-  if (HM == 1) buf += (wave & 1) * 8192;
-  constexpr int PASSES = SPLIT ? 2 : 1;
-  bool bad = false;  // an fp16 result is +-inf or NaN
-#pragma unroll
-  for (int h = 0; h < HM; ++h) {
-    uint8_t *hb = buf + h * 8192;
+  for (int h = 0; h < HM; ++h)
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
 #pragma unroll
-      for (int j = 0; j < C::FN; ++j) {
-        const int kr = j * 32 + (lane & 31);  // row within the block
-        uint8_t *row = hb + kr * 128;
+      for (int j = 0; j < P::FN; ++j) {
+        const int kr = j * 32 + (lane & 31);
+        uint8_t *row = buf + kr * 128;
         const int sw = (kr >> 1) & 7;
 #pragma unroll
         for (int ii = 0; ii < 2 / PASSES; ++ii) {
-          const int il = pass * (2 / PASSES) + ii;  // fragment within the half
+          const int il = pass * (2 / PASSES) + ii;
           const f32x16 &c = acc[2 * h + il][j];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            if (SPLIT) {
-              const int chunk = 2 * g + (lane >> 5);
-              *reinterpret_cast<f32x4 *>(row + ((chunk ^ sw) << 4)) =
+            if (SPLIT)
+              *reinterpret_cast<f32x4 *>(row + (((2 * g + (lane >> 5)) ^ sw) << 4)) =
                   f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
-            } else {
-              const int chunk = 4 * il + g;
-              *reinterpret_cast<u32x2 *>(row + ((chunk ^ sw) << 4) + 8 * (lane >> 5)) =
+            else
+              *reinterpret_cast<u32x2 *>(row + (((4 * il + g) ^ sw) << 4) +
+                                         8 * (lane >> 5)) =
                   to_h4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
-            }
           }
         }
       }
       wait_lds();
       __builtin_amdgcn_wave_barrier();
-      // 8 lanes per row, 16-byte chunk q
-      const int q = lane & 7;
-      u32x4 d[8];
+      const int q = lane & 7;  // 16-byte chunk of the row
+      const int rho = rho0 + 64 * h + (SPLIT ? pass * 32 + 4 * q : 8 * q);
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int kr = 8 * t + (lane >> 3);
-        d[t] = *reinterpret_cast<const u32x4 *>(hb + kr * 128 +
-                                                ((q ^ ((kr >> 1) & 7)) << 4));
-      }
-      const int rho = rho0 + 64 * h;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int k = k0 + 8 * t + (lane >> 3);
+      for (int t = 0; t < P::WN / 8; ++t) {
+        const int kr = 8 * t + (lane >> 3), k = k0 + kr;
+        const u32x4 d =
+            *reinterpret_cast<const u32x4 *>(buf + kr * 128 + ((q ^ ((kr >> 1) & 7)) << 4));
+        if (k >= a.k || rho >= rsc) continue;
         if (SPLIT) {
-          *reinterpret_cast<u32x4 *>(a.part + ((size_t)split * a.k + k) * rsc + rho +
-                                     pass * 32 + 4 * q) = d[t];
+          *reinterpret_cast<u32x4 *>(a.part + ((size_t)split * a.k + k) * rsc + rho) = d;
         } else {
 #pragma unroll
-          for (int w = 0; w < 4; ++w) bad |= nonfinite_h2(d[t][w]);
-          *reinterpret_cast<u32x4 *>(a.dw + (size_t)k * rsc + rho + 8 * q) = d[t];
+          for (int w = 0; w < 4; ++w) bad |= nonfinite_h2(d[w]);
+          *reinterpret_cast<u32x4 *>(a.dw + (size_t)k * rsc + rho) = d;
         }
       }
-      if (pass + 1 < PASSES || h + 1 < HM) {
-        wait_lds();
-        __builtin_amdgcn_wave_barrier();
-      }
+      wait_lds();
+      __builtin_amdgcn_wave_barrier();
     }
+  if (!SPLIT && a.flag) flag_nonfinite(a.flag, bad);
+}
+
+// The same without staging (blocks less than 64 wide): each lane writes 4
+// consecutive rho of one output channel.
+template <class P, bool SPLIT>
+__device__ __forceinline__ void store_rho_direct(f32x16 (&acc)[P::FM][P::FN],
+                                                 const WgradArgs &a, int rsc, int rho0,
+                                                 int k0, int lane, int split) {
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < P::FN; ++j) {
+    const int k = k0 + j * 32 + (lane & 31);
+    if (k >= a.k) continue;
+#pragma unroll
+    for (int i = 0; i < P::FM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int rho = rho0 + i * 32 + 8 * g + 4 * (lane >> 5);
+        if (rho >= rsc) continue;
+        const f32x16 &c = acc[i][j];
+        if (SPLIT) {
+          *reinterpret_cast<f32x4 *>(a.part + ((size_t)split * a.k + k) * rsc + rho) =
+              f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+        } else {
+          const u32x2 hv = to_h4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+          bad |= nonfinite_h2(hv[0]) || nonfinite_h2(hv[1]);
+          *reinterpret_cast<u32x2 *>(a.dw + (size_t)k * rsc + rho) = hv;
+        }
+      }
   }
   if (!SPLIT && a.flag) flag_nonfinite(a.flag, bad);
 }
 
-// ---------------------------------------------------------------------------
-// Kernel gradient: rows rho = (tap, c) of one tap (c % 256 == 0 tiles),
-// columns k (K % 256 == 0), reduction over output positions m.
-template <class C, bool SPLIT>
-__global__ __launch_bounds__(C::NT) void wgrad_dma_kernel(WgradArgs a, WgradDiv fd,
-                                                          TileMap tm) {
-  FG_DMA_RING(C, R);
-  constexpr int PW = C::PW;
+// Arguments by value: by reference the 256 tile's register allocation loses
+// its unrolled addresses (236 registers instead of 251, 3-6% slower).
+template <class P, bool SPLIT>
+__device__ __forceinline__ void wgrad_tile(const WgradArgs a, const WgradDiv fd,
+                                           const TileMap tm) {
+  FG_DMA_RING(P, R);
+  constexpr int PA = P::PA, PB = P::PB, BK = P::BK;
 
   const int rsc = a.r * a.s * a.c;
   int tx, ty, split;  // rho tile, k tile, reduction split
   if (!tm.decode(blockIdx.x, tx, ty, split)) return;
-  const int m0 = tx * C::T;  // rho
-  const int n0 = ty * C::T;  // k
+  const int m0 = tx * P::TM, n0 = ty * P::TN;
   const int mbeg = split * a.mchunk;
   const int mend = min(a.mtot, mbeg + a.mchunk);
-  const int nst = mend > mbeg ? (mend - mbeg + C::BK - 1) / C::BK : 0;
+  const int nst = mend > mbeg ? (mend - mbeg + BK - 1) / BK : 0;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave / C::WGN) * C::WM, wn0 = (wave % C::WGN) * C::WN;
-
-  const int tap = m0 / a.c, c0 = m0 - tap * a.c;
-  const int tr = tap / a.s, ts = tap - tr * a.s;
+  const int wm0 = (wave / P::WGN) * P::WM, wn0 = (wave % P::WGN) * P::WN;
 
   const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
       (void *)a.x, 0, (int)x_span_bytes(a), kRsrcFlags);
   const __amdgpu_buffer_rsrc_t rs_dy = __builtin_amdgcn_make_buffer_rsrc(
       (void *)a.dy, 0, (int)((size_t)a.mtot * a.k * 2), kRsrcFlags);
 
-  // This lane's reduction row m = mbeg + BK * st + krow is decoded into
-  // (n, p, q) once, with multiply-shift division; each stage then advances
-  // it by BK rows with adds and at most one carry into p and one into n
-  // (BK = dq + Q * (dp + P * dn) with dq < Q, dp < P), tracking the input
-  // position (hh, ww) and the byte offsets of both operands directly.
-  // Integer multiplies run at a quarter of the VALU rate: a division per
-  // stage cost more VALU time than the stage's MFMAs leave free.
-  const MnSlot<C> sl = mn_slots<C>(wave, lane);
-  const int h0 = tr - a.ph, w0 = ts - a.pw;
+  // A lane's reduction row m = mbeg + BK * st + krow is decoded into (n, p, q)
+  // once, with multiply-shift division; each stage then advances it by BK rows
+  // with adds and at most one carry into p and one into n (BK = dq + Q * (dp +
+  // P * dn) with dq < Q, dp < P). Integer multiplies run at a quarter of the
+  // VALU rate: a division per stage costs more VALU time than the MFMAs leave
+  // free. The input position (hq, wq) is that of tap (0, 0); the lane's tap
+  // offset (h0, w0) enters the bounds check and the byte offset. Slots whose
+  // column is the same in every instruction share one tap.
+  const MnSlot<PA> sa = mn_slots<P::RBA, PA>(wave, lane);
+  const MnSlot<PB> sb = mn_slots<P::RBB, PB>(wave, lane);
+  constexpr int NTAP = P::RBA > 256 ? PA : 1;
   const int pixb = a.ldx * 2, rowb = a.w * pixb, imgb = a.h * rowb;
-  int hh[PW], ww[PW], ox[PW], od[PW];
+  int h0[NTAP], w0[NTAP], hq[PA], wq[PA], ox[PA], od[PB];
 #pragma unroll
-  for (int jj = 0; jj < PW; ++jj) {
-    const int m = mbeg + sl.krow[jj];
+  for (int jj = 0; jj < PA; ++jj) {
+    const int rho = m0 + sa.ncol[jj];
+    const int tap = rho / a.c, tr = tap / a.s;
+    const int th = tr - a.ph, tw = tap - tr * a.s - a.pw;
+    if (jj < NTAP) {
+      h0[jj] = rho < rsc ? th : -(1 << 29);  // never inside the image
+      w0[jj] = tw;
+    }
+    const int m = mbeg + sa.krow[jj];
     const unsigned nn = fd.pq.div((unsigned)m);
     const unsigned rem = (unsigned)m - nn * (unsigned)(a.p * a.q);
     const unsigned pp = fd.q.div(rem);
-    const int qq = (int)(rem - pp * (unsigned)a.q);
-    hh[jj] = (int)pp * a.sh + h0;
-    ww[jj] = qq * a.sw + w0;
-    ox[jj] = (int)nn * imgb + hh[jj] * rowb + ww[jj] * pixb + (c0 + sl.ncol[jj]) * 2;
-    od[jj] = (m * a.k + n0 + sl.ncol[jj]) * 2;
+    hq[jj] = (int)pp * a.sh;
+    wq[jj] = (int)(rem - pp * (unsigned)a.q) * a.sw;
+    ox[jj] = (int)nn * imgb + (hq[jj] + th) * rowb + (wq[jj] + tw) * pixb +
+             (rho - tap * a.c) * 2;
   }
-  const int dq = C::BK % a.q, dpt = C::BK / a.q, dp = dpt % a.p, dn = dpt / a.p;
+#pragma unroll
+  for (int jj = 0; jj < PB; ++jj)
+    od[jj] = n0 + sb.ncol[jj] < a.k
+                 ? ((mbeg + sb.krow[jj]) * a.k + n0 + sb.ncol[jj]) * 2
+                 : -1;
+  const int dq = BK % a.q, dpt = BK / a.q, dp = dpt % a.p, dn = dpt / a.p;
   const int inc_w = dq * a.sw, inc_h = dp * a.sh;
   const int inc_o = inc_w * pixb + inc_h * rowb + dn * imgb;
-  const int wlim = a.q * a.sw + w0, hlim = a.p * a.sh + h0;
-  const int wrap_o = a.sh * rowb - a.q * a.sw * pixb;  // q wraps into p
-  const int hwrap_o = imgb - a.p * a.sh * rowb;         // p wraps into n
-  const int inc_d = C::BK * a.k * 2;
+  const int wlim = a.q * a.sw, hlim = a.p * a.sh;
+  const int wrap_o = a.sh * rowb - wlim * pixb;  // q wraps into p
+  const int hwrap_o = imgb - hlim * rowb;        // p wraps into n
+  const int inc_d = BK * a.k * 2;
   const int mleft = mend - mbeg;
 
   auto issue = [&](int st, int slot) __attribute__((always_inline)) {
     uint8_t *ta = R.a[slot], *tb = R.b[slot];
 #pragma unroll
-    for (int jj = 0; jj < PW; ++jj) {
-      // row krow = RPI (PW wave + jj) + lane / (RB / 16) of stage st exists
-      const bool mv = (int)(lane / (C::RB / 16)) <
-                      mleft - C::BK * st - C::RPI * (C::PW * wave + jj);
-      const bool v = mv && (unsigned)hh[jj] < (unsigned)a.h &&
-                     (unsigned)ww[jj] < (unsigned)a.w;
-      dma16(rs_x, ta + dma_dst<C>(wave, jj), v ? (unsigned)ox[jj] : kOOB);
-      dma16(rs_dy, tb + dma_dst<C>(wave, jj), mv ? (unsigned)od[jj] : kOOB);
-      od[jj] += inc_d;
-      ww[jj] += inc_w;
-      hh[jj] += inc_h;
+    for (int jj = 0; jj < PA; ++jj) {
+      const int jt = NTAP == 1 ? 0 : jj;
+      const bool v = sa.krow[jj] < mleft - BK * st &&
+                     (unsigned)(hq[jj] + h0[jt]) < (unsigned)a.h &&
+                     (unsigned)(wq[jj] + w0[jt]) < (unsigned)a.w;
+      dma16(rs_x, ta + dma_dst<PA>(wave, jj), v ? (unsigned)ox[jj] : kOOB);
+      wq[jj] += inc_w;
+      hq[jj] += inc_h;
       ox[jj] += inc_o;
-      if (ww[jj] >= wlim) {
-        ww[jj] -= a.q * a.sw;
-        hh[jj] += a.sh;
+      if (wq[jj] >= wlim) {
+        wq[jj] -= wlim;
+        hq[jj] += a.sh;
         ox[jj] += wrap_o;
       }
-      if (hh[jj] >= hlim) {
-        hh[jj] -= a.p * a.sh;
+      if (hq[jj] >= hlim) {
+        hq[jj] -= hlim;
         ox[jj] += hwrap_o;
       }
     }
+#pragma unroll
+    for (int jj = 0; jj < PB; ++jj) {
+      const bool v = sb.krow[jj] < mleft - BK * st && od[jj] >= 0;
+      dma16(rs_dy, tb + dma_dst<PB>(wave, jj), v ? (unsigned)od[jj] : kOOB);
+      od[jj] += od[jj] >= 0 ? inc_d : 0;
+    }
   };
 
-  f32x16 acc[C::FM][C::FN];
-  zero<C>(acc);
-  pipeline<C, false, false>(acc, R, nst, wm0, wn0, lane, issue);
-  if constexpr ((C::WM == 64 || C::WM == 128) && C::WN == 64) {
-    store_tile_w<C, SPLIT>(acc, R, a, rsc, m0 + wm0, n0 + wn0, lane, wave, split);
+  f32x16 acc[P::FM][P::FN];
+  zero<P>(acc);
+  pipeline<P, false, false>(acc, R, nst, wm0, wn0, lane, issue);
+  if constexpr (P::WM % 64 == 0 && P::WN == 64) {
+    // 8 KiB of the ring per wave, a-side arrays first (constant indices only)
+    constexpr int WPA = P::A_BYTES / 8192;  // waves per array
+    static_assert(P::A_BYTES % 8192 == 0 && P::A_BYTES == P::B_BYTES &&
+                      (P::NW + WPA - 1) / WPA <= 2 * P::NS,
+                  "the store stages 8 KiB per wave in the ring");
+    __syncthreads();  // every wave is done reading the ring
+    uint8_t *buf = R.a[0];
+#pragma unroll
+    for (int k = 1; k < (P::NW + WPA - 1) / WPA; ++k)
+      if (wave / WPA == k) buf = k < P::NS ? R.a[k] : R.b[k - P::NS];
+    buf += (wave % WPA) * 8192;
+    store_rho<P, SPLIT>(acc, buf, a, rsc, m0 + wm0, n0 + wn0, lane, split);
   } else {
-    // direct: each lane writes 4 consecutive rho of one output channel k
-    bool bad = false;
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-      const int k = n0 + wn0 + j * 32 + (lane & 31);
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int rho = m0 + wm0 + i * 32 + 8 * g + 4 * (lane >> 5);
-          const f32x16 &c = acc[i][j];
-          if (!SPLIT) {
-            const u32x2 hv = to_h4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
-            bad |= nonfinite_h2(hv[0]) | nonfinite_h2(hv[1]);
-            *reinterpret_cast<u32x2 *>(a.dw + (size_t)k * rsc + rho) = hv;
-          } else {
-            *reinterpret_cast<f32x4 *>(a.part + ((size_t)split * a.k + k) * rsc +
-                                       rho) =
-                f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
-          }
-        }
-    }
-    if (!SPLIT && a.flag) flag_nonfinite(a.flag, bad);
+    store_rho_direct<P, SPLIT>(acc, a, rsc, m0 + wm0, n0 + wn0, lane, split);
   }
+}
+
+// The kernels, one overload per tile (the last argument's type). Two names:
+// wgrad_dma_kernel for channel counts that are multiples of 256, wgrad_kernel
+// for the others, with the largest tile their row and column counts fill.
+// WPE: waves per SIMD (workgroups per CU that the ring leaves room for).
+#define FG_WGRAD_KERNELS(P, WPE)                                                  \
+  template <bool SPLIT>                                                           \
+  __global__ __launch_bounds__(P::NT, WPE) void wgrad_dma_kernel(                 \
+      WgradArgs a, WgradDiv fd, TileMap tm, P) {                                  \
+    wgrad_tile<P, SPLIT>(a, fd, tm);                                              \
+  }                                                                               \
+  template <class C, bool SPLIT>                                                  \
+  __global__ __launch_bounds__(P::NT, WPE) void wgrad_kernel(                     \
+      WgradArgs a, WgradDiv fd, TileMap tm, P) {                                  \
+    wgrad_tile<P, SPLIT>(a, fd, tm);                                              \
+  }
+FG_WGRAD_KERNELS(Tile256, 2)
+FG_WGRAD_KERNELS(Tile128, 2)
+FG_WGRAD_KERNELS(Tile64, 3)
+#undef FG_WGRAD_KERNELS
+
+template <class P>
+static hipError_t launch_tile(const WgradArgs &a, WgName name, hipStream_t st) {
+  using Kernel = void (*)(WgradArgs, WgradDiv, TileMap, P);
+  using Big = Cfg<256, 256, 2, 4>;
+  using Small = Cfg<128, 128, 2, 2>;
+  const bool s = a.nsplit > 1;
+  const Kernel k =
+      name == WgName::kDma
+          ? (s ? (Kernel)wgrad_dma_kernel<true> : (Kernel)wgrad_dma_kernel<false>)
+      : name == WgName::kBig
+          ? (s ? (Kernel)wgrad_kernel<Big, true> : (Kernel)wgrad_kernel<Big, false>)
+      : P::TM == 256
+          ? nullptr  // not planned for fewer than 256 rows or columns
+          : (s ? (Kernel)wgrad_kernel<std::conditional_t<P::TM == 256, Big, Small>, true>
+               : (Kernel)wgrad_kernel<std::conditional_t<P::TM == 256, Big, Small>, false>);
+  if (!k) return hipErrorInvalidValue;
+  const WgradDiv fd{make_fastdiv((uint32_t)(a.p * a.q)), make_fastdiv((uint32_t)a.q)};
+  TileMap tm{(a.r * a.s * a.c + P::TM - 1) / P::TM, (a.k + P::TN - 1) / P::TN, a.nsplit, 0,
+             0};
+  tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
+  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, fd, tm, P{});
+  return hipGetLastError();
 }
 
 }  // namespace dma
@@ -1216,12 +865,6 @@ bool data_dma_ok(const DataConvArgs &a) {
   return a.cr % dma::DataRun::BK == 0 &&
          act_span_bytes(a) < 0x7FFFFFFFull &&
          (size_t)a.wbytes < 0x7FFFFFFFull;
-}
-
-bool wgrad_dma_ok(const WgradArgs &a) {
-  return a.c % dma::TM == 0 && a.k % dma::TN == 0 &&
-         x_span_bytes(a) < 0x7FFFFFFFull &&
-         (size_t)a.mtot * a.k * 2 < 0x7FFFFFFFull;
 }
 
 bool data_halo_ok(const DataConvArgs &a) {
@@ -1317,26 +960,15 @@ hipError_t launch_data_conv_dma_small(const DataConvArgs &a, bool w_kmajor,
   return launch_dma_cfg<dma::SmallRun>(a, w_kmajor, st);
 }
 
-static dma::FastDiv make_fastdiv(uint32_t d) {
-  int l = 0;
-  while ((1ull << l) < d) ++l;
-  const uint64_t m = ((1ull << 32) * ((1ull << l) - d)) / d + 1;
-  return {(uint32_t)m, l ? 1 : 0, l ? l - 1 : 0};
+bool wgrad_tile_ok(const WgradArgs &a) {
+  return x_span_bytes(a) < 0x7FFFFFFFull && (size_t)a.mtot * a.k * 2 < 0x7FFFFFFFull;
 }
 
-hipError_t launch_wgrad_dma(const WgradArgs &a, hipStream_t st) {
-  const int rsc = a.r * a.s * a.c;
-  const dma::WgradDiv fd{make_fastdiv((uint32_t)(a.p * a.q)), make_fastdiv((uint32_t)a.q)};
-  dma::TileMap tm{rsc / dma::TM, a.k / dma::TN, a.nsplit, 0, 0};
-  tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
-  dim3 grid(8 * tm.per);
-  if (a.nsplit > 1)
-    hipLaunchKernelGGL((dma::wgrad_dma_kernel<dma::WgradRun, true>), grid, dim3(dma::WgradRun::NT), 0, st,
-                       a, fd, tm);
-  else
-    hipLaunchKernelGGL((dma::wgrad_dma_kernel<dma::WgradRun, false>), grid, dim3(dma::WgradRun::NT), 0, st,
-                       a, fd, tm);
-  return hipGetLastError();
+hipError_t launch_wgrad_tile(const WgradArgs &a, WgTile tile, hipStream_t st) {
+  const WgName name = wgrad_name(a.r * a.s * a.c, a.c, a.k);
+  return tile == WgTile::k256   ? dma::launch_tile<dma::Tile256>(a, name, st)
+         : tile == WgTile::k128 ? dma::launch_tile<dma::Tile128>(a, name, st)
+                                : dma::launch_tile<dma::Tile64>(a, name, st);
 }
 
 }  // namespace fg

@@ -12,7 +12,9 @@
 //
 // The kernel gradient is a second kernel: rows are (tap, input channel),
 // columns output channels, reduction over all output positions, split across
-// workgroups with fp32 partials summed afterwards in a fixed order.
+// workgroups with fp32 partials summed afterwards in a fixed order. This one
+// runs the tensors that a buffer resource cannot address; the others take the
+// LDS-DMA kernels (conv_dma.hip).
 //
 // Both kernels stage 64-deep reduction slices of each operand in LDS (double
 // buffered, one barrier per slice). LDS rows are 128 bytes with the eight
@@ -28,15 +30,6 @@ namespace fg {
 
 constexpr int BK = 64;        // reduction slice per LDS stage (halves)
 
-// Tile configuration: BM x BN output tile, WGM x WGN waves, each owning a
-// (BM/WGM) x (BN/WGN) block of 32x32 MFMA fragments.
-template <int BM_, int BN_, int WGM_, int WGN_>
-struct Cfg {
-  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
-  static constexpr int NT = 64 * WGM * WGN;
-  static constexpr int WM = BM / WGM, WN = BN / WGN;
-  static constexpr int FM = WM / 32, FN = WN / 32;
-};
 // 256x256 tile, 8 waves (two per SIMD) of 128x64: one wave's MFMAs overlap
 // the other's address, load and LDS instructions.
 using BigCfg = Cfg<256, 256, 2, 4>;
@@ -366,7 +359,7 @@ __global__ __launch_bounds__(256) void split_epilogue_kernel(
 // ---------------------------------------------------------------------------
 // Kernel-gradient kernel: rows rho = (tap, c) of the x patch, columns k.
 template <class C, bool SPLIT>
-__global__ __launch_bounds__(C::NT) void wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(C::NT) void wgrad_staged_kernel(WgradArgs a) {
   constexpr int BM = C::BM, BN = C::BN, NT = C::NT;
   __shared__ __attribute__((aligned(16))) uint16_t sA[2][BM * BK];
   __shared__ __attribute__((aligned(16))) uint16_t sB[2][BN * BK];
@@ -781,17 +774,8 @@ static TileCost data_cost(bool dma_small) {
                               kRateSmallDmaAlone}
                    : TileCost{3.0e12, kRateSmallRegs, 6.0e12, 4e-6, 0.0, kRateSmallRegs};
 }
-// Kernel gradient: a least-squares fit of this model to the DMA kernel's
-// times on the network's twelve kernel-gradient shapes at 1-8 splits
-// (per 256x256x32 stage 0.66 us, 4.2 us per wave, partials at 4.05 TB/s,
-// 6.3 us per split launch; mean error 9%). The 128x128 rate is the
-// register-staged kernel's, which only shapes too small for 256x256 tiles
-// take.
-constexpr TileCost kWgradCost{6.35e12, 1.3e12, 4.05e12, 6.3e-6, 4.2e-6, 1.3e12};
-
 TileChoice choose_tiles(int64_t tiles_big, int64_t tiles_small, int64_t nk,
-                        int64_t out_elems, bool allow_big, const TileCost &cost,
-                        int max_split = 16) {
+                        int64_t out_elems, bool allow_big, const TileCost &cost) {
   TileChoice best{false, 1};
   double best_t = 1e30;
   for (int big = 0; big < 2; ++big) {
@@ -799,7 +783,7 @@ TileChoice choose_tiles(int64_t tiles_big, int64_t tiles_small, int64_t nk,
     const int64_t tiles = big ? tiles_big : tiles_small;
     const int64_t slots = big ? kCUs : 2 * kCUs;
     const int t = big ? 256 : 128;
-    for (int ns = 1; ns <= max_split; ++ns) {
+    for (int ns = 1; ns <= 16; ++ns) {
       if (ns > 1 && (nk + ns - 1) / ns < 4) break;  // >= 4 slices per split
       const double rate = big                 ? cost.rate_big
                           : tiles * ns <= kCUs ? cost.rate_small_alone
@@ -919,93 +903,127 @@ const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor) {
   return names[pl.big][w_kmajor][(a.cr % BK) == 0][pl.nsplit > 1];
 }
 
-// max_ws_bytes bounds the fp32 partials of a split (and so the split count).
-// A kernel gradient whose R*S*C or K is below 256 (so no 256 x 256 tile)
-// with a long reduction needs many splits to fill the GPU: a 1x1 layer of
-// 128 x 64 has a single 128 x 128 tile. Such shapes may split up to
-// kMaxWgradSplit ways (at least 4 stages each); the others keep the cap of
-// 16, under which the network's layers were fitted and timed.
-constexpr int kMaxWgradSplit = 256;
-
-static TileChoice wgrad_choice(const fg_conv_desc &d, int32_t p, int32_t q,
-                               size_t max_ws_bytes) {
-  const int64_t rsc = (int64_t)d.r * d.s * d.c;
-  const int64_t mtot = (int64_t)d.n * p * q;
-  const int64_t tb = ((rsc + 255) / 256) * ((d.k + 255) / 256);
-  const int64_t ts = ((rsc + 127) / 128) * ((d.k + 127) / 128);
-  const size_t per_split = (size_t)d.k * rsc * sizeof(float);
-  const size_t cap = max_ws_bytes / per_split;
-  const bool allow_big = rsc >= 256 && d.k >= 256;
-  const int limit = allow_big ? 16 : kMaxWgradSplit;
-  const int max_split = cap >= (size_t)limit ? limit : (cap < 2 ? 1 : (int)cap);
-  return choose_tiles(tb, ts, (mtot + BK - 1) / BK, (int64_t)d.k * rsc, allow_big,
-                      kWgradCost, max_split);
-}
-
 const char *wgrad_kernel_name(const fg_conv_desc &d) {
   int32_t p = (d.h + 2 * d.pad_h - d.r) / d.stride_h + 1;
   int32_t q = (d.w + 2 * d.pad_w - d.s) / d.stride_w + 1;
   const WgradPlan pl = plan_wgrad(d, p, q);
-  WgradArgs wa;
-  wa.n = d.n; wa.h = d.h; wa.w = d.w; wa.c = d.c; wa.k = d.k;
-  wa.ldx = d.x_ld ? d.x_ld : d.c;
-  wa.mtot = d.n * p * q;
-  if (pl.big && wgrad_dma_ok(wa))
-    return pl.nsplit > 1 ? "wgrad_dma_kernel<true>" : "wgrad_dma_kernel<false>";
-  static const char *names[2][2] = {
-      {"wgrad_kernel<Cfg<128, 128, 2, 2>, false>",
-       "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"},
-      {"wgrad_kernel<Cfg<256, 256, 2, 4>, false>",
-       "wgrad_kernel<Cfg<256, 256, 2, 4>, true>"}};
-  return names[pl.big][pl.nsplit > 1];
+  const int split = pl.nsplit > 1;
+  static const char *staged[2][2] = {
+      {"wgrad_staged_kernel<Cfg<128, 128, 2, 2>, false>",
+       "wgrad_staged_kernel<Cfg<128, 128, 2, 2>, true>"},
+      {"wgrad_staged_kernel<Cfg<256, 256, 2, 4>, false>",
+       "wgrad_staged_kernel<Cfg<256, 256, 2, 4>, true>"}};
+  if (pl.tile == WgTile::kStaged256 || pl.tile == WgTile::kStaged128)
+    return staged[pl.tile == WgTile::kStaged256][split];
+  static const char *names[3][2] = {  // by WgName
+      {"wgrad_dma_kernel<false>", "wgrad_dma_kernel<true>"},
+      {"wgrad_kernel<Cfg<256, 256, 2, 4>, false>", "wgrad_kernel<Cfg<256, 256, 2, 4>, true>"},
+      {"wgrad_kernel<Cfg<128, 128, 2, 2>, false>", "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"}};
+  return names[(int)wgrad_name((int64_t)d.r * d.s * d.c, d.c, d.k)][split];
 }
 
-WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
-                     size_t max_ws_bytes) {
+// Tile and split count of a kernel gradient, by an estimate of its time:
+//   kWgradFixed + stages * max(alone, L * shared) (+ a split's reduction),
+// stages of 64 rows in the longest split, L the workgroups per CU (rounded up).
+// `alone` is the chain of one workgroup's stages (loads, barrier, transposing
+// reads, MFMAs), `shared` what the CU needs per workgroup stage when several
+// interleave. Fitted to 900 timings of the three tiles at 1 to 256 splits over
+// 25 shapes (0.01 to 310 GFLOP, 16 to 1024 channels, 1x1 to 4x4 kernels); mean
+// error 7.5%, the choice within 4% of the best timing in the mean. The tiles
+// trade LDS traffic for workgroups: 512 x 4608 x 65536 (K x RSC x positions)
+// takes 340 us on 256 x 256 tiles, 427 on 128 and 577 on 64; 512 x 2376 x 1024
+// 29, 15 and 11 us.
+struct WgradTileCost {
+  WgTile tile;
+  int32_t t;
+  double alone, shared;  // us per 64-row stage
+};
+constexpr WgradTileCost kWgradTiles[] = {{WgTile::k256, 256, 1.08, 1.39},
+                                         {WgTile::k128, 128, 0.65, 0.52},
+                                         {WgTile::k64, 64, 0.33, 0.22}};
+constexpr double kWgradFixed = 4.4;       // us: launch, first loads, tile store
+constexpr double kWgradReduce = 2.8;      // us: the reduction's launch
+constexpr double kWgradPartialBw = 5.6e6; // bytes/us, 8 per partial element
+constexpr int kMaxWgradSplit = 256;
+
+// The register-staged kernels (tensors beyond a buffer resource): their
+// 128 x 128 tiles everywhere but where both counts fill a 256 x 256 one.
+static WgradPlan plan_staged(int64_t rsc, int64_t k, int64_t mtot, int max_split) {
+  const bool big = rsc >= 256 && k >= 256;
+  const int64_t t = big ? 256 : 128;
+  const int64_t tiles = ((rsc + t - 1) / t) * ((k + t - 1) / t);
+  const int64_t want = (kCUs + tiles - 1) / tiles;
   WgradPlan pl;
-  const TileChoice c = wgrad_choice(d, p, q, max_ws_bytes);
-  const int64_t rsc = (int64_t)d.r * d.s * d.c;
-  const int64_t mtot = (int64_t)d.n * p * q;
-  int64_t ns = c.nsplit;
-  int64_t chunk = (mtot + ns - 1) / ns;
-  chunk = (chunk + BK - 1) / BK * BK;
-  ns = (mtot + chunk - 1) / chunk;
-  pl.big = c.big;
-  pl.nsplit = (int32_t)ns;
-  pl.mchunk = (int32_t)chunk;
-  pl.ws_bytes = ns > 1 ? (size_t)ns * d.k * rsc * sizeof(float) : 0;
+  pl.tile = big ? WgTile::kStaged256 : WgTile::kStaged128;
+  pl.nsplit = (int32_t)std::max<int64_t>(
+      1, std::min<int64_t>(std::min<int64_t>(want, max_split), mtot / (4 * BK)));
   return pl;
 }
 
-hipError_t launch_wgrad(const WgradArgs &a, bool big, hipStream_t st) {
-  const int rsc = a.r * a.s * a.c;
-  const bool split = a.nsplit > 1;
+// max_ws_bytes bounds the fp32 partials of a split (and so the split count).
+WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
+                     size_t max_ws_bytes) {
+  const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k;
+  const int64_t mtot = (int64_t)d.n * p * q;
+  const size_t cap = max_ws_bytes / ((size_t)k * rsc * sizeof(float));
+  const int max_split = cap >= (size_t)kMaxWgradSplit ? kMaxWgradSplit
+                                                      : (cap < 2 ? 1 : (int)cap);
+  WgradArgs wa;
+  wa.n = d.n; wa.h = d.h; wa.w = d.w; wa.c = d.c; wa.k = d.k;
+  wa.ldx = d.x_ld ? d.x_ld : d.c;
+  wa.mtot = (int32_t)mtot;
+  const int64_t nk = (mtot + BK - 1) / BK;  // 64-row stages
+  WgradPlan pl;
+  if (!wgrad_tile_ok(wa)) {
+    pl = plan_staged(rsc, k, mtot, max_split);
+  } else {
+    double best = 1e30;
+    for (const WgradTileCost &c : kWgradTiles) {
+      if (c.t == 256 && wgrad_name(rsc, d.c, d.k) == WgName::kSmall) continue;
+      const int64_t tiles = ((rsc + c.t - 1) / c.t) * ((k + c.t - 1) / c.t);
+      for (int ns = 1; ns <= max_split && ns <= nk; ++ns) {
+        const int64_t st = (nk + ns - 1) / ns, wgs = tiles * ((nk + st - 1) / st);
+        const int64_t per_cu = (wgs + kCUs - 1) / kCUs;
+        double t = kWgradFixed + st * std::max(c.alone, per_cu * c.shared);
+        if (ns > 1) t += kWgradReduce + ns * (double)(k * rsc) * 8.0 / kWgradPartialBw;
+        if (t < best * 0.98) {  // fewer splits and larger tiles on near ties
+          best = t;
+          pl.tile = c.tile;
+          pl.nsplit = ns;
+        }
+      }
+    }
+  }
+  int64_t chunk = (mtot + pl.nsplit - 1) / pl.nsplit;
+  chunk = (chunk + BK - 1) / BK * BK;
+  const int64_t ns = (mtot + chunk - 1) / chunk;
+  pl.nsplit = (int32_t)ns;
+  pl.mchunk = (int32_t)chunk;
+  pl.ws_bytes = ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
+  return pl;
+}
+
+template <class C>
+static hipError_t launch_staged_wgrad(const WgradArgs &a, hipStream_t st) {
+  dim3 grid((a.r * a.s * a.c + C::BM - 1) / C::BM, (a.k + C::BN - 1) / C::BN, a.nsplit);
+  if (a.nsplit > 1)
+    hipLaunchKernelGGL((wgrad_staged_kernel<C, true>), grid, dim3(C::NT), 0, st, a);
+  else
+    hipLaunchKernelGGL((wgrad_staged_kernel<C, false>), grid, dim3(C::NT), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad(const WgradArgs &a, WgTile tile, hipStream_t st) {
   hipError_t e = prof_begin(st);
   if (e != hipSuccess) return e;
-  if (big && wgrad_dma_ok(a)) {
-    e = launch_wgrad_dma(a, st);
-  } else if (big) {
-    dim3 grid((rsc + 255) / 256, (a.k + 255) / 256, a.nsplit);
-    if (split)
-      hipLaunchKernelGGL((wgrad_kernel<BigCfg, true>), grid, dim3(BigCfg::NT), 0,
-                         st, a);
-    else
-      hipLaunchKernelGGL((wgrad_kernel<BigCfg, false>), grid, dim3(BigCfg::NT), 0,
-                         st, a);
-    e = hipGetLastError();
-  } else {
-    dim3 grid((rsc + 127) / 128, (a.k + 127) / 128, a.nsplit);
-    if (split)
-      hipLaunchKernelGGL((wgrad_kernel<SmallCfg, true>), grid, dim3(SmallCfg::NT),
-                         0, st, a);
-    else
-      hipLaunchKernelGGL((wgrad_kernel<SmallCfg, false>), grid,
-                         dim3(SmallCfg::NT), 0, st, a);
-    e = hipGetLastError();
+  switch (tile) {
+    case WgTile::kStaged256: e = launch_staged_wgrad<BigCfg>(a, st); break;
+    case WgTile::kStaged128: e = launch_staged_wgrad<SmallCfg>(a, st); break;
+    default: e = launch_wgrad_tile(a, tile, st);
   }
   if (e == hipSuccess) e = prof_end(st);
-  if (e != hipSuccess || !split) return e;
-  const int64_t len = (int64_t)a.k * rsc;
+  if (e != hipSuccess || a.nsplit == 1) return e;
+  const int64_t len = (int64_t)a.k * a.r * a.s * a.c;
   if (a.nsplit > kMaxSerialSplit) {
     hipLaunchKernelGGL(split_reduce_multi_kernel, dim3((unsigned)((len + 63) / 64)),
                        dim3(256), 0, st, a.part, a.nsplit, len, a.dw, a.flag);

@@ -11,6 +11,16 @@
 
 namespace fg {
 
+// Tile configuration: BM x BN output tile, WGM x WGN waves, each owning a
+// (BM/WGM) x (BN/WGN) block of 32x32 MFMA fragments.
+template <int BM_, int BN_, int WGM_, int WGN_>
+struct Cfg {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
+  static constexpr int NT = 64 * WGM * WGN;
+  static constexpr int WM = BM / WGM, WN = BN / WGN;
+  static constexpr int FM = WM / 32, FN = WN / 32;
+};
+
 // One output phase of a data convolution (forward, input gradient or
 // transposed forward) written as an implicit GEMM over the taps that reach
 // it. Output positions (a, b) of the phase land at image position
@@ -79,8 +89,19 @@ struct WgradArgs {
 
 // Kernel selection for a shape; pure host logic, shared by the workspace
 // query and the launchers so both always agree.
+enum class WgTile : int32_t {
+  k256, k128, k64,           // fed by LDS DMA, square rho x k tiles (conv_dma.hip)
+  kStaged256, kStaged128     // register-staged: tensors beyond a buffer resource
+};
+// Which name the kernel gradient of a shape runs under.
+enum class WgName : int32_t { kDma, kBig, kSmall };
+inline WgName wgrad_name(int64_t rsc, int32_t c, int32_t k) {
+  return c % 256 == 0 && k % 256 == 0 ? WgName::kDma
+         : rsc >= 256 && k >= 256     ? WgName::kBig
+                                      : WgName::kSmall;
+}
 struct WgradPlan {
-  bool big;              // 256 x 256 tiles (else 128 x 128)
+  WgTile tile;
   int32_t nsplit, mchunk;
   size_t ws_bytes;
 };
@@ -100,7 +121,7 @@ hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor,
                             hipStream_t st);
 const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor);
 const char *wgrad_kernel_name(const fg_conv_desc &d);
-hipError_t launch_wgrad(const WgradArgs &a, bool big, hipStream_t st);
+hipError_t launch_wgrad(const WgradArgs &a, WgTile tile, hipStream_t st);
 
 // LDS-DMA kernels (256 x 256 tiles): applicability and launchers.
 bool data_dma_ok(const DataConvArgs &a);
@@ -109,13 +130,13 @@ bool data_dma_ok(const DataConvArgs &a);
 bool data_halo_ok(const DataConvArgs &a);
 hipError_t launch_data_conv_halo(const DataConvArgs &a, bool w_kmajor,
                                  hipStream_t st);
-bool wgrad_dma_ok(const WgradArgs &a);
+bool wgrad_tile_ok(const WgradArgs &a);
+hipError_t launch_wgrad_tile(const WgradArgs &a, WgTile tile, hipStream_t st);
 // The same with 128 x 128 tiles (two workgroups per CU).
 hipError_t launch_data_conv_dma_small(const DataConvArgs &a, bool w_kmajor,
                                       hipStream_t st);
 hipError_t launch_data_conv_dma(const DataConvArgs &a, bool w_kmajor,
                                 hipStream_t st);
-hipError_t launch_wgrad_dma(const WgradArgs &a, hipStream_t st);
 hipError_t launch_head_fwd(const uint16_t *x, const uint16_t *w, uint16_t *y,
                            int64_t npix, int32_t c, int32_t epi,
                            const uint16_t *gate, hipStream_t st);
