@@ -190,6 +190,7 @@ DataConvArgs fwd_args(const fg_conv_desc *d, int32_t P, int32_t Q) {
                                         0x7FFFFFFF);
   a.nphase = 1;
   a.nsplit = 1;
+  a.fixed_order = 1;
   Phase &ph = a.ph[0];
   ph.mh = P; ph.mw = Q; ph.ooh = 0; ph.oow = 0;
   ph.nr = d->r; ph.ns = d->s;
@@ -233,6 +234,7 @@ DataConvArgs convt_args(const fg_conv_desc *d, int32_t HO, int32_t WO) {
   a.wbytes = (int32_t)std::min<int64_t>(elems4(d->c, d->r, d->s, d->k) * 2,
                                         0x7FFFFFFF);
   a.nsplit = 1;
+  a.fixed_order = 1;
   a.nphase = make_phases(a, HO, WO, d->stride_h, d->stride_w, d->pad_h,
                          d->pad_w, d->r, d->s);
   return a;

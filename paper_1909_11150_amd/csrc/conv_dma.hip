@@ -46,8 +46,7 @@ using DataRun = K<FG_DMA_DATA_CFG>;
 #define FG_DMA_HALO_NS 3
 #endif
 using HaloRun = K<32, FG_DMA_HALO_NS, 2, 4>;  // weights ring; the rest is patches
-// 128 x 128 tiles for layers with few output positions: 4 waves of 64 x 64,
-// 80 KiB of ring, two workgroups per CU
+// the small tiles' family name (their own pipelines are at data_tile)
 using SmallRun = K<32, 5, 2, 2, 128>;
 
 // ---------------------------------------------------------------------------
@@ -178,44 +177,6 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[C::FM][C::FN],
   }
 }
 
-// Direct store of the accumulators (small tiles, whose ring has no room to
-// stage a wave's block): 8-byte pieces of 4 channels per lane.
-template <class C, bool SPLIT>
-__device__ __forceinline__ void store_direct(f32x16 (&acc)[C::FM][C::FN],
-                                             const DataConvArgs &a, const Phase &P,
-                                             int npix, int n0, int m0, int wm0,
-                                             int wn0, int lane, int split) {
-  const size_t out_total = (size_t)a.n * a.ho * a.wo * a.co;
-#pragma unroll
-  for (int j = 0; j < C::FN; ++j) {
-    const int col = n0 + wn0 + j * 32 + (lane & 31);
-    if (col >= npix) continue;
-    const int b = col % P.mw, t = col / P.mw;
-    const int aa = t % P.mh, nn = t / P.mh;
-    const size_t obase =
-        ((size_t)(nn * a.ho + aa * a.ostr + P.ooh) * a.wo + b * a.ostr + P.oow) *
-        (SPLIT ? a.co : a.ldo);
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int co = m0 + wm0 + i * 32 + 8 * g + 4 * (lane >> 5);
-        if (co >= a.co) continue;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
-        if (SPLIT) {
-          *reinterpret_cast<f32x4 *>(a.part + split * out_total + obase + co) =
-              f32x4{v[0], v[1], v[2], v[3]};
-        } else {
-          epilogue4(v, a.epi, a.gate + obase + co, a.out + obase + co);
-          *reinterpret_cast<u32x2 *>(a.out + obase + co) =
-              to_h4(v[0], v[1], v[2], v[3]);
-        }
-      }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Data convolution (forward / input gradient / transposed forward).
 // Requires reduction channels cr % BK == 0 (a stage lies in one tap).
@@ -226,7 +187,7 @@ __global__ __launch_bounds__(C::NT, C::WPE) void data_conv_dma_kernel(DataConvAr
   constexpr int PW = C::PW;
 
   int tz, ty, tx;  // phase x split, output-channel tile, position tile
-  if (tm.linear ? !tm.decode(blockIdx.x, tx, ty, tz)
+  if (tm.order ? !tm.decode(blockIdx.x, tx, ty, tz)
                 : !tm.decode(blockIdx.x, tz, ty, tx))
     return;
   const int phase = tz / a.nsplit, split = tz % a.nsplit;
@@ -328,20 +289,16 @@ __global__ __launch_bounds__(C::NT, C::WPE) void data_conv_dma_kernel(DataConvAr
   zero<C>(acc);
   pipeline<C, WK, true>(acc, R, kend - kbeg, wm0, wn0, lane, issue);
 
-  if constexpr (C::WM == 128 && C::WN == 64) {
-    // staging: ring array `wave` (a-side arrays first, constant indices
-    // only) and the position tables in the next one
-    static_assert(2 * C::NS >= C::NW + 1 && C::TILE_BYTES >= 16384,
-                  "the store needs one 16 KiB ring array per wave plus one");
-    uint8_t *sbuf = R.a[0];
+  // staging: ring array `wave` (a-side arrays first, constant indices only) and
+  // the position tables in the next one
+  static_assert(2 * C::NS >= C::NW + 1 && C::TILE_BYTES >= 16384,
+                "the store needs one 16 KiB ring array per wave plus one");
+  uint8_t *sbuf = R.a[0];
 #pragma unroll
-    for (int k = 1; k < C::NW; ++k)
-      if (wave == k) sbuf = k < C::NS ? R.a[k] : R.b[k - C::NS];
-    int32_t *spos = reinterpret_cast<int32_t *>(R.b[C::NW - C::NS]) + 64 * wave;
-    store_tile<C, SPLIT>(acc, sbuf, spos, a, P, npix, n0, m0, wm0, wn0, lane, split);
-  } else {
-    store_direct<C, SPLIT>(acc, a, P, npix, n0, m0, wm0, wn0, lane, split);
-  }
+  for (int k = 1; k < C::NW; ++k)
+    if (wave == k) sbuf = k < C::NS ? R.a[k] : R.b[k - C::NS];
+  int32_t *spos = reinterpret_cast<int32_t *>(R.b[C::NW - C::NS]) + 64 * wave;
+  store_tile<C, SPLIT>(acc, sbuf, spos, a, P, npix, n0, m0, wm0, wn0, lane, split);
 }
 
 // ---------------------------------------------------------------------------
@@ -414,7 +371,9 @@ __global__ __launch_bounds__(C::NT) void data_conv_halo_kernel(DataConvArgs a,
   patch[0] = sP0, patch[1] = sP1;
 
   int split, ty, tx;  // reduction split, output-channel tile, position tile
-  if (!tm.decode(blockIdx.x, split, ty, tx)) return;
+  if (tm.order ? !tm.decode(blockIdx.x, tx, ty, split)
+               : !tm.decode(blockIdx.x, split, ty, tx))
+    return;
   const Phase P = a.ph[0];
   const int n0 = tx * TN, m0 = ty * TM;
   const int nchunk = a.cr / 32;
@@ -575,6 +534,475 @@ __global__ __launch_bounds__(C::NT) void data_conv_halo_kernel(DataConvArgs a,
   int32_t *spos = reinterpret_cast<int32_t *>(sP1 + 32768) + 64 * wave;
   const int npix = a.n * P.mh * P.mw;
   store_tile<C, SPLIT>(acc, sbuf, spos, a, P, npix, n0, m0, wm0, wn0, lane, split);
+}
+
+// Where the weights are large and much larger than the input, an XCD should
+// fetch its share of the weights and all of the input, not the reverse: 1024 x
+// 9216 weights over 1024 positions 37.3 -> 33.6 us (128 x 128 tiles), 1024 x
+// 16384 over 1024 52.0 -> 46.1. Below 8 MiB or at 3 times the input the other
+// order is the faster one (768 x 3456 over 1152 20.4 -> 21.7 us this way, 1024 x
+// 9216 over 4096 95 -> 125 on small tiles).
+static bool weight_major(const DataConvArgs &a) {
+  return a.wbytes >= (8 << 20) && (size_t)a.wbytes >= 3 * act_span_bytes(a);
+}
+
+// Tile order of a launch over the phases of a (reordered here where they differ
+// in cost).
+static TileMap data_tile_map(DataConvArgs &a, int tm_, int tn_) {
+  int maxpix = 0;
+  bool uneven = false;
+  for (int i = 0; i < a.nphase; ++i) {
+    maxpix = std::max(maxpix, a.n * a.ph[i].mh * a.ph[i].mw);
+    uneven |= a.ph[i].nr * a.ph[i].ns != a.ph[0].nr * a.ph[0].ns;
+  }
+  const int tco = (a.co + tm_ - 1) / tm_, tpix = (maxpix + tn_ - 1) / tn_;
+  TileMap tm;
+  if (uneven) {
+    // phases with different tap counts (strided input gradients): costliest
+    // phase first, in launch order, so the cheap tiles fill the tail
+    std::stable_sort(a.ph, a.ph + a.nphase, [](const Phase &x, const Phase &y) {
+      return x.nr * x.ns > y.nr * y.ns;
+    });
+    tm = TileMap{tpix, tco, a.nphase * a.nsplit, 0, kCostly};
+  } else if (weight_major(a)) {
+    tm = TileMap{tpix, tco, a.nphase * a.nsplit, 0, kWeightMajor};
+  } else {
+    // phases and splits fastest, so every XCD gets an even share of each
+    // and the phases of one position tile share input
+    tm = TileMap{a.nphase * a.nsplit, tco, tpix, 0, kOutputMajor};
+  }
+  tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
+  return tm;
+}
+
+// ---------------------------------------------------------------------------
+// Data convolutions on small tiles, and of any channel count (multiples of 8).
+//
+// The 256 x 256 kernels above leave most CUs idle where the output is small, and
+// waste the tile where it has fewer channels: there the time is the chain of one
+// workgroup's stages and what two launches of a split cost. These tiles (64 x
+// 64, 64 channels x 128 positions, 128 x 128) have 64-deep stages (whole
+// 128-byte lines, half the barriers), two waves per SIMD and workgroup for the
+// two larger ones, and a store through LDS in whole rows. Against the 128 x 128
+// tiles of 4 waves in 32-deep stages that ran these shapes: 128 channels, K 1152
+// over 32768 positions 19.9 -> 15.5 us; the strided input gradient of 64
+// channels, K 128 to 512 over 131072 28.4 -> 16.5; 64 channels, K 576 over 6240
+// 11.7 -> 6.6; the register-staged kernel on 512 channels, K 2376 over 65536
+// 330 -> 182 (256 x 256).
+//   GEN: reduction channels that are not a multiple of the stage depth. A
+//   stage then straddles taps: every lane copies 8 reduction channels, which
+//   lie in one tap, and advances its own (tap, channel) by BK per stage.
+template <int P, bool GEN>
+struct RedPos;  // reduction position of each of P DMA slots
+template <int P>
+struct RedPos<P, true> {
+  int c[P], t[P];  // channel, tap
+  __device__ __forceinline__ void init(int jj, int kk, int cr) {
+    t[jj] = kk / cr;
+    c[jj] = kk - t[jj] * cr;
+  }
+  __device__ __forceinline__ void advance(int jj, int dt, int dc, int cr) {
+    c[jj] += dc;
+    const bool w = c[jj] >= cr;
+    c[jj] -= w ? cr : 0;
+    t[jj] += dt + w;
+  }
+};
+template <int P>
+struct RedPos<P, false> {};
+
+// Store of a wave's WM-channel x WN-position block through LDS, position-major
+// rows of WM fp16 values in 16-byte chunks, so that whole 64- or 128-byte rows
+// are written (and read, for the gate). `buf`: WM * WN * 2 bytes of this wave's
+// own, `pos`: WN entries.
+template <class P>
+__device__ __forceinline__ void store_rows(f32x16 (&acc)[P::FM][P::FN], uint8_t *buf,
+                                           const int32_t *pos, const DataConvArgs &a,
+                                           int c0, int lane) {
+  constexpr int CPW = P::WM / 8, RB = P::WM * 2;  // chunks, bytes per row
+  constexpr int SH = CPW == 16 ? 0 : CPW == 8 ? 1 : 2;  // rows per bank turn, log2
+#pragma unroll
+  for (int j = 0; j < P::FN; ++j) {
+    const int p = j * 32 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < P::FM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = acc[i][j][4 * g + e];
+          if (a.epi == FG_EPI_RELU) v[e] = v[e] > 0.f ? v[e] : 0.f;
+        }
+        *reinterpret_cast<u32x2 *>(buf + p * RB +
+                                   (((4 * i + g) ^ ((p >> SH) & (CPW - 1))) << 4) +
+                                   8 * (lane >> 5)) = to_h4(v[0], v[1], v[2], v[3]);
+      }
+  }
+  wait_lds();
+  __builtin_amdgcn_wave_barrier();
+  constexpr int PPI = 64 / CPW, N = P::WN / PPI;  // positions per instruction
+  const int q = lane % CPW, ch = c0 + 8 * q;
+  u32x4 d[N];
+  int32_t ob[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int p = k * PPI + lane / CPW;
+    d[k] = *reinterpret_cast<const u32x4 *>(buf + p * RB +
+                                            ((q ^ ((p >> SH) & (CPW - 1))) << 4));
+    ob[k] = ch < a.co ? pos[p] : -1;
+  }
+  if (a.epi == FG_EPI_GATE) {
+    u32x4 gw[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k)  // absent positions read element 0
+      gw[k] = *reinterpret_cast<const u32x4 *>(a.gate + (ob[k] < 0 ? 0 : ob[k] + ch));
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t lo =
+            h_to_f32((uint16_t)(gw[k][w] & 0xFFFFu)) > 0.f ? 0x0000FFFFu : 0u;
+        const uint32_t hi = h_to_f32((uint16_t)(gw[k][w] >> 16)) > 0.f ? 0xFFFF0000u : 0u;
+        d[k][w] &= lo | hi;
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (ob[k] >= 0) *reinterpret_cast<u32x4 *>(a.out + ob[k] + ch) = d[k];
+}
+
+// What becomes of a workgroup's sum: stored whole; one part of a split, stored
+// as fp32 partials; or whole, but summed in a.nchunk parts from zero, each added
+// to the ones before (the order of a split without its second launch and its
+// partials: 256 x 2048 over 8192 positions in 2 parts 26.6 -> 17.7 us).
+enum class Sum { kWhole, kPart, kFold };
+
+// Division by the width and height of each phase's output grid.
+struct PosDiv {
+  FastDiv mw[4], mh[4];
+};
+
+template <class P, bool WK, Sum SUM, bool GEN>
+__device__ __forceinline__ void data_tile(const DataConvArgs &a, const TileMap &tm,
+                                          const PosDiv &pd) {
+  FG_DMA_RING(P, R);
+  constexpr int PA = P::PA, PB = P::PB, BK = P::BK;
+
+  int tz, ty, tx;  // phase x split, output-channel tile, position tile
+  if (tm.order ? !tm.decode(blockIdx.x, tx, ty, tz)
+                : !tm.decode(blockIdx.x, tz, ty, tx))
+    return;
+  const int phase = tz / a.nsplit, split = tz % a.nsplit;
+  const Phase F = a.ph[phase];
+  const FastDiv dmw = pd.mw[phase], dmh = pd.mh[phase];
+  const int npix = a.n * F.mh * F.mw;
+  const int n0 = tx * P::TN, m0 = ty * P::TM;
+  if (n0 >= npix) return;
+  constexpr bool SPLIT = SUM == Sum::kPart;
+  const int ktot = F.nr * F.ns * a.cr;
+  const int plen = part_len(ktot, a.unit, a.nchunk);
+  const int kbeg = SPLIT ? min(ktot, split * plen) : 0;
+  const int kend = SPLIT ? min(ktot, kbeg + plen) : ktot;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave / P::WGN) * P::WM, wn0 = (wave % P::WGN) * P::WN;
+
+  const __amdgpu_buffer_rsrc_t rs_act = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)a.act, 0, (int)act_span_bytes(a), kRsrcFlags);
+  const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)a.wgt, 0, a.wbytes, kRsrcFlags);
+
+  // position col of the phase: image n, row and column of the grid
+  auto decode = [&](int col, int &nn, int &aa, int &b) __attribute__((always_inline)) {
+    const unsigned t = dmw.div((unsigned)col);
+    b = col - (int)t * F.mw;
+    nn = (int)dmh.div(t);
+    aa = (int)t - nn * F.mh;
+  };
+
+  // B: this lane's positions (image row and column of tap (0, 0)) and offsets
+  const KmSlot<PB> bs = km_slots<BK, PB>(wave, lane);
+  int bh[PB], bw[PB], bbase[PB];
+  RedPos<PB, GEN> rb;
+#pragma unroll
+  for (int jj = 0; jj < PB; ++jj) {
+    const int col = n0 + bs.row[jj];
+    int nn, aa, b;
+    decode(col, nn, aa, b);
+    bh[jj] = col < npix ? aa * a.istr + F.dh0 : -(1 << 29);  // or never inside
+    bw[jj] = b * a.istr + F.dw0;
+    bbase[jj] = ((nn * a.hi + aa * a.istr + F.dh0) * a.wi + bw[jj]) * a.ldi +
+                (GEN ? 0 : bs.coff[jj]);
+    if constexpr (GEN) rb.init(jj, kbeg + bs.coff[jj], a.cr);
+  }
+  // A: this lane's weight offsets without the stage part (k-major: forward
+  // weights, whose reduction index is linear in memory)
+  int wbase[PA], wkk[PA];
+  bool wok[PA];
+  RedPos<PA, GEN && !WK> ra;
+#pragma unroll
+  for (int jj = 0; jj < PA; ++jj) {
+    if (WK) {
+      const KmSlot<PA> as = km_slots<BK, PA>(wave, lane);
+      const int co = m0 + as.row[jj];
+      wok[jj] = co < a.co;
+      wbase[jj] = co * a.ldw + as.coff[jj];
+      wkk[jj] = as.coff[jj];
+    } else {
+      const MnSlot<PA> as = mn_slots<P::RBA, PA>(wave, lane);
+      const int co = m0 + as.ncol[jj];
+      wok[jj] = co < a.co;
+      wbase[jj] = (GEN ? 0 : as.krow[jj] * a.w_red) + co;
+      wkk[jj] = as.krow[jj];
+      if constexpr (GEN && !WK) ra.init(jj, kbeg + as.krow[jj], a.cr);
+    }
+  }
+  const int dt = BK / a.cr, dc = BK - dt * a.cr;  // GEN: a stage's advance
+  const int nsm = (255 + F.ns) / max(F.ns, 1);     // t / ns = t * nsm >> 8, t < 64
+
+  // uniform stage decode (whole stages of one tap), as in the kernels above
+  int cr0 = 0, ti = 0, tj = 0, kk0 = kbeg;
+  if constexpr (!GEN) {
+    const int t = kk0 / a.cr;
+    cr0 = kk0 - t * a.cr;
+    ti = t / F.ns;
+    tj = t - ti * F.ns;
+  }
+  auto issue = [&](int, int slot) __attribute__((always_inline)) {
+    uint8_t *ta = R.a[slot], *tb = R.b[slot];
+    if constexpr (GEN) {
+#pragma unroll
+      for (int jj = 0; jj < PB; ++jj) {
+        const int i = (rb.t[jj] * nsm) >> 8, j = rb.t[jj] - i * F.ns;
+        const int dh = F.dstep * i, dw = F.dstep * j;
+        const bool v = bs.coff[jj] < kend - kk0 && (unsigned)(bh[jj] + dh) < (unsigned)a.hi &&
+                       (unsigned)(bw[jj] + dw) < (unsigned)a.wi;
+        const unsigned o =
+            (unsigned)(bbase[jj] + (dh * a.wi + dw) * a.ldi + rb.c[jj]) * 2u;
+        dma16(rs_act, tb + dma_dst<PB>(wave, jj), v ? o : kOOB);
+        rb.advance(jj, dt, dc, a.cr);
+      }
+#pragma unroll
+      for (int jj = 0; jj < PA; ++jj) {
+        unsigned o;
+        bool v;
+        if constexpr (WK) {
+          o = (unsigned)(wbase[jj] + kk0) * 2u;
+          v = wok[jj] && wkk[jj] < kend - kk0;
+        } else {
+          const int i = (ra.t[jj] * nsm) >> 8, j = ra.t[jj] - i * F.ns;
+          const int woff = (F.r0 + F.rstep * i) * a.s + F.s0 + F.rstep * j;
+          o = (unsigned)(wbase[jj] + ra.c[jj] * a.w_red + woff * a.w_tap) * 2u;
+          v = wok[jj] && wkk[jj] < kend - kk0;
+          ra.advance(jj, dt, dc, a.cr);
+        }
+        dma16(rs_w, ta + dma_dst<PA>(wave, jj), v ? o : kOOB);
+      }
+      kk0 += BK;
+    } else {
+      const int dh = F.dstep * ti, dw = F.dstep * tj;
+      const int woff = (F.r0 + F.rstep * ti) * a.s + (F.s0 + F.rstep * tj);
+      const int delta = (dh * a.wi + dw) * a.ldi + cr0;
+      const int wst = WK ? woff * a.cr + cr0 : cr0 * a.w_red + woff * a.w_tap;
+#pragma unroll
+      for (int jj = 0; jj < PB; ++jj) {
+        const bool v = (unsigned)(bh[jj] + dh) < (unsigned)a.hi &&
+                       (unsigned)(bw[jj] + dw) < (unsigned)a.wi;
+        const unsigned o = (unsigned)(bbase[jj] + delta) * 2u;
+        dma16(rs_act, tb + dma_dst<PB>(wave, jj), v ? o : kOOB);
+      }
+#pragma unroll
+      for (int jj = 0; jj < PA; ++jj) {
+        const unsigned o = (unsigned)(wbase[jj] + wst) * 2u;
+        dma16(rs_w, ta + dma_dst<PA>(wave, jj), wok[jj] ? o : kOOB);
+      }
+      cr0 += BK;
+      const bool wrap = cr0 == a.cr;
+      cr0 = wrap ? 0 : cr0;
+      tj += wrap;
+      const bool wrap2 = tj == F.ns;
+      tj = wrap2 ? 0 : tj;
+      ti += wrap2;
+    }
+  };
+
+  f32x16 acc[P::FM][P::FN];
+  zero<P>(acc);
+  const int nst = (kend - kbeg + BK - 1) / BK;
+  if constexpr (SUM == Sum::kFold) {
+    f32x16 tot[P::FM][P::FN];
+    zero<P>(tot);
+    int done = 0, next = plen;  // reduction summed so far, end of the part
+    bool first = true;
+    auto fold = [&]() __attribute__((always_inline)) {
+      done += 32;
+      if (done == next && done < ktot) {
+#pragma unroll
+        for (int i = 0; i < P::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < P::FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              tot[i][j][v] = first ? acc[i][j][v] : tot[i][j][v] + acc[i][j][v];
+              acc[i][j][v] = 0.f;
+            }
+        next += plen;
+        first = false;
+      }
+    };
+    pipeline<P, WK, true>(acc, R, nst, wm0, wn0, lane, issue, fold);
+    if (!first) {
+#pragma unroll
+      for (int i = 0; i < P::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < P::FN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = tot[i][j][v] + acc[i][j][v];
+    }
+  } else {
+    pipeline<P, WK, true>(acc, R, nst, wm0, wn0, lane, issue);
+  }
+
+  // element offset of a position (-1: absent); split partials are dense
+  const int ldo = SPLIT ? a.co : a.ldo;
+  auto opos = [&](int col) __attribute__((always_inline)) {
+    int nn, aa, b;
+    decode(col, nn, aa, b);
+    const int o = ((nn * a.ho + aa * a.ostr + F.ooh) * a.wo + b * a.ostr + F.oow) * ldo;
+    return col < npix ? o : -1;
+  };
+  // Staged rows, except where the output is added to: there the sum is rounded
+  // once (the staged rows are fp16 already).
+  constexpr int WB = P::WM * P::WN * 2, WP = WB + 4 * P::WN;  // rows, and positions
+  constexpr bool ONE = P::NW * WB <= P::B_BYTES && P::NW * 4 * P::WN <= P::B_BYTES;
+  constexpr int PER = P::B_BYTES / WP;  // waves per array, else
+  static_assert(ONE || (P::A_BYTES == P::B_BYTES && PER > 0 && P::NW <= 2 * P::NS * PER) ||
+                    (P::A_BYTES == WB && P::B_BYTES == WB && P::NW < 2 * P::NS),
+                "the ring has room to stage the tile");
+  if (!SPLIT && a.epi != FG_EPI_ACC) {
+    __syncthreads();  // every wave is done reading the ring
+    uint8_t *buf;
+    int32_t *pos;
+    if constexpr (ONE) {  // all rows in one array, the positions in the next
+      buf = R.b[0] + wave * WB;
+      pos = reinterpret_cast<int32_t *>(R.b[1]) + wave * P::WN;
+    } else {              // constant array indices only
+      constexpr int W = PER > 0 ? PER : 1;
+      buf = R.a[0];
+#pragma unroll
+      for (int k = 1; k < (P::NW + W - 1) / W; ++k)
+        if (wave / W == k) buf = k < P::NS ? R.a[k] : R.b[k - P::NS];
+      buf += wave % W * WP;
+      pos = PER > 0 ? reinterpret_cast<int32_t *>(buf + WB)
+                    : reinterpret_cast<int32_t *>(R.b[P::NS - 1]) + wave * P::WN;
+    }
+    if (lane < P::WN) pos[lane] = opos(n0 + wn0 + lane);
+    store_rows<P>(acc, buf, pos, a, m0 + wm0, lane);
+    return;
+  }
+  const size_t out_total = (size_t)a.n * a.ho * a.wo * a.co;
+#pragma unroll
+  for (int j = 0; j < P::FN; ++j) {
+    const int ob = opos(n0 + wn0 + j * 32 + (lane & 31));
+    if (ob < 0) continue;
+#pragma unroll
+    for (int i = 0; i < P::FM; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int co = m0 + wm0 + i * 32 + 8 * g + 4 * (lane >> 5);
+        if (co >= a.co) continue;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
+        if (SPLIT) {
+          *reinterpret_cast<f32x4 *>(a.part + split * out_total + ob + co) =
+              f32x4{v[0], v[1], v[2], v[3]};
+        } else {
+          epilogue4(v, a.epi, a.gate + ob + co, a.out + ob + co);
+          *reinterpret_cast<u32x2 *>(a.out + ob + co) = to_h4(v[0], v[1], v[2], v[3]);
+        }
+      }
+  }
+}
+
+using Data64 = Pipe<64, 3, 2, 2, 64, 64>;       // 4 waves of 32 x 32
+using Data64x128 = Pipe<64, 3, 2, 4, 64, 128>;  // 8 waves of 32 x 32
+using Data128 = Pipe<64, 2, 4, 2, 128, 128>;    // 8 waves of 32 x 64
+using Data256 = Pipe<32, 5, 2, 4, 256, 256>;    // 8 waves of 128 x 64
+
+// Overloads by tile (Gen<P>: stages that straddle taps), under the name of the
+// shape's family: data_conv_dma_kernel<K<..., 128>, ...> for reduction channels
+// that are a multiple of 32, data_conv_kernel with the largest tile the output
+// fills for the others.
+template <class P>
+struct Gen {};
+template <class T>
+struct Fold {};  // Sum::kFold where not split
+#define FG_DATA_DMA_KERNEL(P, WPE, TAG, GEN, FOLD)                                  \
+  template <class C, bool WK, bool SPLIT>                                           \
+  __global__ __launch_bounds__(P::NT, WPE) void data_conv_dma_kernel(               \
+      DataConvArgs a, TileMap tm, PosDiv pd, TAG) {                                 \
+    data_tile<P, WK, SPLIT ? Sum::kPart : FOLD, GEN>(a, tm, pd);                    \
+  }
+#define FG_DATA_GEN_KERNEL(P, WPE, TAG, FOLD)                                       \
+  template <class C, bool WK, bool FAST, bool SPLIT>                                \
+  __global__ __launch_bounds__(P::NT, WPE) void data_conv_kernel(                   \
+      DataConvArgs a, TileMap tm, PosDiv pd, TAG) {                                 \
+    data_tile<P, WK, SPLIT ? Sum::kPart : FOLD, true>(a, tm, pd);                   \
+  }
+#define FG_DATA_KERNELS(P, WPE)                                                     \
+  FG_DATA_DMA_KERNEL(P, WPE, P, false, Sum::kWhole)                                 \
+  FG_DATA_DMA_KERNEL(P, WPE, Gen<P>, true, Sum::kWhole)                             \
+  FG_DATA_DMA_KERNEL(P, WPE, Fold<P>, false, Sum::kFold)                            \
+  FG_DATA_DMA_KERNEL(P, WPE, Fold<Gen<P>>, true, Sum::kFold)                        \
+  FG_DATA_GEN_KERNEL(P, WPE, Gen<P>, Sum::kWhole)                                   \
+  FG_DATA_GEN_KERNEL(P, WPE, Fold<Gen<P>>, Sum::kFold)
+FG_DATA_KERNELS(Data64, 3)
+FG_DATA_KERNELS(Data64x128, 4)
+FG_DATA_KERNELS(Data128, 4)
+FG_DATA_GEN_KERNEL(Data256, 2, Gen<Data256>, Sum::kWhole)
+#undef FG_DATA_KERNELS
+#undef FG_DATA_DMA_KERNEL
+#undef FG_DATA_GEN_KERNEL
+
+template <class P, class TAG, bool LARGE>
+static auto data_kernel(const DataConvArgs &a, bool w_kmajor) {
+  using Kernel = void (*)(DataConvArgs, TileMap, PosDiv, TAG);
+  using D = std::conditional_t<LARGE, DataRun, SmallRun>;
+  using C = std::conditional_t<LARGE, Cfg<256, 256, 2, 4>, Cfg<128, 128, 2, 2>>;
+  const int i = 2 * w_kmajor + (a.nsplit > 1);
+  if constexpr (std::is_same_v<TAG, Gen<P>> || std::is_same_v<TAG, Fold<Gen<P>>>)
+    if (a.cr % 32 != 0) {
+      const Kernel k[4] = {
+          data_conv_kernel<C, false, false, false>, data_conv_kernel<C, false, false, true>,
+          data_conv_kernel<C, true, false, false>, data_conv_kernel<C, true, false, true>};
+      return k[i];
+    }
+  if constexpr (P::TM != 256) {  // the larger tiles have whole-tap kernels
+    const Kernel k[4] = {
+        data_conv_dma_kernel<D, false, false>, data_conv_dma_kernel<D, false, true>,
+        data_conv_dma_kernel<D, true, false>, data_conv_dma_kernel<D, true, true>};
+    return k[i];
+  }
+  return (Kernel) nullptr;
+}
+
+template <class P, class TAG>
+static hipError_t launch_data_tile(const DataConvArgs &a0, DataTile tile, bool w_kmajor,
+                                   hipStream_t st) {
+  const auto k = data_conv_large(a0, tile) ? data_kernel<P, TAG, true>(a0, w_kmajor)
+                                           : data_kernel<P, TAG, false>(a0, w_kmajor);
+  if (!k) return hipErrorInvalidValue;
+  DataConvArgs a = a0;
+  const TileMap tm = data_tile_map(a, P::TM, P::TN);
+  PosDiv pd;
+  for (int i = 0; i < 4; ++i) {
+    pd.mw[i] = make_fastdiv((uint32_t)std::max(a.ph[i].mw, 1));
+    pd.mh[i] = make_fastdiv((uint32_t)std::max(a.ph[i].mh, 1));
+  }
+  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, tm, pd, TAG{});
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -852,7 +1280,7 @@ static hipError_t launch_tile(const WgradArgs &a, WgName name, hipStream_t st) {
   if (!k) return hipErrorInvalidValue;
   const WgradDiv fd{make_fastdiv((uint32_t)(a.p * a.q)), make_fastdiv((uint32_t)a.q)};
   TileMap tm{(a.r * a.s * a.c + P::TM - 1) / P::TM, (a.k + P::TN - 1) / P::TN, a.nsplit, 0,
-             0};
+             kOutputMajor};
   tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
   hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, fd, tm, P{});
   return hipGetLastError();
@@ -861,12 +1289,6 @@ static hipError_t launch_tile(const WgradArgs &a, WgName name, hipStream_t st) {
 }  // namespace dma
 
 // ---------------------------------------------------------------------------
-bool data_dma_ok(const DataConvArgs &a) {
-  return a.cr % dma::DataRun::BK == 0 &&
-         act_span_bytes(a) < 0x7FFFFFFFull &&
-         (size_t)a.wbytes < 0x7FFFFFFFull;
-}
-
 bool data_halo_ok(const DataConvArgs &a) {
   if (a.nphase != 1 || a.istr != 1 || a.cr % 32 != 0) return false;
   const Phase &P = a.ph[0];
@@ -879,11 +1301,13 @@ bool data_halo_ok(const DataConvArgs &a) {
          (size_t)a.wbytes < 0x7FFFFFFFull;
 }
 
-hipError_t launch_data_conv_halo(const DataConvArgs &a, bool w_kmajor,
+static hipError_t launch_data_conv_halo(const DataConvArgs &a, bool w_kmajor,
                                  hipStream_t st) {
   const int npix = a.n * a.ph[0].mh * a.ph[0].mw;
-  dma::TileMap tm{a.nsplit, (a.co + dma::TM - 1) / dma::TM,
-                  (npix + dma::TN - 1) / dma::TN, 0, 0};
+  const int tco = (a.co + dma::TM - 1) / dma::TM, tpix = (npix + dma::TN - 1) / dma::TN;
+  dma::TileMap tm = dma::weight_major(a)
+                        ? dma::TileMap{tpix, tco, a.nsplit, 0, dma::kWeightMajor}
+                        : dma::TileMap{a.nsplit, tco, tpix, 0, dma::kOutputMajor};
   tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
   dim3 grid(8 * tm.per), block(dma::HaloRun::NT);
   const bool split = a.nsplit > 1;
@@ -905,31 +1329,11 @@ hipError_t launch_data_conv_halo(const DataConvArgs &a, bool w_kmajor,
   return hipGetLastError();
 }
 
-template <class C>
-static hipError_t launch_dma_cfg(const DataConvArgs &a0, bool w_kmajor,
-                                 hipStream_t st) {
+static hipError_t launch_data_conv_dma(const DataConvArgs &a0, bool w_kmajor,
+                                       hipStream_t st) {
+  using C = dma::DataRun;
   DataConvArgs a = a0;
-  int maxpix = 0;
-  bool uneven = false;
-  for (int i = 0; i < a.nphase; ++i) {
-    maxpix = std::max(maxpix, a.n * a.ph[i].mh * a.ph[i].mw);
-    uneven |= a.ph[i].nr * a.ph[i].ns != a.ph[0].nr * a.ph[0].ns;
-  }
-  const int tco = (a.co + C::T - 1) / C::T, tpix = (maxpix + C::T - 1) / C::T;
-  dma::TileMap tm;
-  if (uneven) {
-    // phases with different tap counts (strided input gradients): costliest
-    // phase first, in launch order, so the cheap tiles fill the tail
-    std::stable_sort(a.ph, a.ph + a.nphase, [](const Phase &x, const Phase &y) {
-      return x.nr * x.ns > y.nr * y.ns;
-    });
-    tm = dma::TileMap{tpix, tco, a.nphase * a.nsplit, 0, 1};
-  } else {
-    // phases and splits fastest, so every XCD gets an even share of each
-    // and the phases of one position tile share input
-    tm = dma::TileMap{a.nphase * a.nsplit, tco, tpix, 0, 0};
-  }
-  tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
+  const dma::TileMap tm = dma::data_tile_map(a, C::T, C::T);
   dim3 grid(8 * tm.per), block(C::NT);
   const bool split = a.nsplit > 1;
   if (w_kmajor) {
@@ -950,14 +1354,43 @@ static hipError_t launch_dma_cfg(const DataConvArgs &a0, bool w_kmajor,
   return hipGetLastError();
 }
 
-hipError_t launch_data_conv_dma(const DataConvArgs &a, bool w_kmajor,
-                                hipStream_t st) {
-  return launch_dma_cfg<dma::DataRun>(a, w_kmajor, st);
+bool data_tile_ok(const DataConvArgs &a) {
+  return act_span_bytes(a) < 0x7FFFFFFFull && (size_t)a.wbytes < 0x7FFFFFFFull;
 }
 
-hipError_t launch_data_conv_dma_small(const DataConvArgs &a, bool w_kmajor,
-                                      hipStream_t st) {
-  return launch_dma_cfg<dma::SmallRun>(a, w_kmajor, st);
+template <class P>
+static hipError_t launch_data_tile_any(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                       hipStream_t st) {
+  using dma::Fold;
+  using dma::Gen;
+  const bool fold = a.nsplit == 1 && a.nchunk > 1;
+  bool gen = a.cr % P::BK != 0;
+  for (int i = 0; a.nsplit > 1 && i < a.nphase; ++i)  // parts that end within a stage
+    gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, a.unit, a.nchunk) % P::BK != 0;
+  return fold ? (gen ? dma::launch_data_tile<P, Fold<Gen<P>>>(a, tile, w_kmajor, st)
+                     : dma::launch_data_tile<P, Fold<P>>(a, tile, w_kmajor, st))
+              : (gen ? dma::launch_data_tile<P, Gen<P>>(a, tile, w_kmajor, st)
+                     : dma::launch_data_tile<P, P>(a, tile, w_kmajor, st));
+}
+
+hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                 hipStream_t st) {
+  using dma::Gen;
+  const bool whole = a.cr % 32 == 0;  // a 32-deep stage lies in one tap
+  switch (tile) {
+    case DataTile::k64:
+      return launch_data_tile_any<dma::Data64>(a, tile, w_kmajor, st);
+    case DataTile::k64x128:
+      return launch_data_tile_any<dma::Data64x128>(a, tile, w_kmajor, st);
+    case DataTile::k128:
+      return launch_data_tile_any<dma::Data128>(a, tile, w_kmajor, st);
+    case DataTile::k256:
+      return data_halo_ok(a) ? launch_data_conv_halo(a, w_kmajor, st)
+             : whole         ? launch_data_conv_dma(a, w_kmajor, st)
+                             : dma::launch_data_tile<dma::Data256, Gen<dma::Data256>>(
+                                   a, tile, w_kmajor, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 bool wgrad_tile_ok(const WgradArgs &a) {

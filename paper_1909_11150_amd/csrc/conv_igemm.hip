@@ -12,9 +12,11 @@
 //
 // The kernel gradient is a second kernel: rows are (tap, input channel),
 // columns output channels, reduction over all output positions, split across
-// workgroups with fp32 partials summed afterwards in a fixed order. This one
-// runs the tensors that a buffer resource cannot address; the others take the
-// LDS-DMA kernels (conv_dma.hip).
+// workgroups with fp32 partials summed afterwards in a fixed order.
+//
+// Both run the tensors that a buffer resource cannot address; the others take
+// the LDS-DMA kernels (conv_dma.hip). The planners of all of them, the split
+// reductions and the one-channel head are here too.
 //
 // Both kernels stage 64-deep reduction slices of each operand in LDS (double
 // buffered, one barrier per slice). LDS rows are 128 bytes with the eight
@@ -23,6 +25,8 @@
 // reduction dimension is strided in memory are transposed in registers on
 // their way to LDS. Each of the 4 waves owns a (BM/2) x (BN/2) block of the
 // tile and issues v_mfma_f32_32x32x16_f16 over it.
+#include <cstring>
+
 #include "common.h"
 #include "internal.h"
 
@@ -138,7 +142,7 @@ __device__ __forceinline__ void epilogue4(float v[4], int epi, const uint16_t *g
 //         (a.nsplit > 1) instead of the fp16 output.
 // blockIdx.z = phase * nsplit + split.
 template <class C, bool WK, bool FAST, bool SPLIT>
-__global__ __launch_bounds__(C::NT) void data_conv_kernel(DataConvArgs a) {
+__global__ __launch_bounds__(C::NT) void data_conv_staged_kernel(DataConvArgs a) {
   constexpr int BM = C::BM, BN = C::BN, NT = C::NT;
   __shared__ __attribute__((aligned(16))) uint16_t sA[2][BM * BK];
   __shared__ __attribute__((aligned(16))) uint16_t sB[2][BN * BK];
@@ -737,81 +741,229 @@ int64_t data_nk_max(const DataConvArgs &a) {
 }
 
 constexpr int64_t kCUs = 256;
-// flop/s of one 128x128 workgroup of the LDS-DMA kernel, in the units of
-// the 256x256 rate below: alone on its CU (a launch of at most one
-// workgroup per CU), and with a second one sharing the CU. Timed on the
-// network's 16x16 and 32x32 layers at forced splits: a CU holding one
-// workgroup runs 1.25x as fast as one holding two (0.39 against 0.97 us
-// per workgroup stage), so splits that double the workgroups to fill the
-// second slot lose.
-constexpr double kRateSmallDmaAlone = 2.1e12, kRateSmallDmaPaired = 0.85e12;
-// The register-staged 128x128 kernel, alone or paired.
-constexpr double kRateSmallRegs = 1.3e12;
+
+// Work of a data convolution on tm x tn tiles: tiles over all phases, their
+// reduction stages of bk in all (each phase has its own taps), the most of one.
+struct DataWork {
+  int32_t tiles, stages, longest;
+};
+struct PhaseWork {
+  int32_t tiles[4], nk[4], nphase;
+  PhaseWork(const DataConvArgs &a, int tm, int tn, int bk) : nphase(a.nphase) {
+    const int tco = (a.co + tm - 1) / tm;
+    for (int i = 0; i < nphase; ++i) {
+      const Phase &P = a.ph[i];
+      tiles[i] = (int32_t)(((int64_t)a.n * P.mh * P.mw + tn - 1) / tn) * tco;
+      nk[i] = (P.nr * P.ns * a.cr + bk - 1) / bk;
+    }
+  }
+  DataWork split(int ns) const {
+    DataWork w{0, 0, 0};
+    for (int i = 0; i < nphase; ++i) {
+      const int32_t st = ns == 1 ? nk[i] : (nk[i] + ns - 1) / ns;
+      w.tiles += tiles[i];
+      w.stages += tiles[i] * st * ns;
+      if (tiles[i]) w.longest = std::max(w.longest, st);
+    }
+    return w;
+  }
+};
+DataWork data_work(const DataConvArgs &a, int tm, int tn, int bk) {
+  return PhaseWork(a, tm, tn, bk).split(1);
+}
+
+// Plans of the last shapes a host thread asked for: a call asks at least twice
+// (workspace, launch), a program for the same shapes every step, and working
+// one out takes 1 to 2 us of the 5 that a launch costs the host.
+template <class Key, class Plan>
+struct PlanMemo {
+  static constexpr unsigned N = 64;
+  struct Entry {
+    Key key;
+    Plan plan;
+    bool set;
+  };
+  Entry e[N];  // zero-initialised
+  // Keys are compared as bytes (filled over zeros).
+  Entry &at(const Key &k) {
+    const uint32_t *w = reinterpret_cast<const uint32_t *>(&k);
+    uint32_t h = 2166136261u;
+    for (size_t i = 0; i < sizeof(Key) / 4; ++i) h = (h ^ w[i]) * 16777619u;
+    return e[(h ^ (h >> 15)) % N];
+  }
+};
 
 }  // namespace
 
-// Split/tile choice by an estimate of the run time: resident workgroup
-// slots per GPU (one 256x256 workgroup or two 128x128 ones per CU), the
-// per-workgroup MFMA rate each reaches (measured on MI355X; for 128x128
-// tiles it depends on whether the launch fits one workgroup per CU), waves of
-// workgroups with a fixed cost per wave (prologue and tile store, which one
-// workgroup per CU cannot overlap with its MFMA work), and the fp32
-// partials a split writes and re-reads.
-struct TileChoice {
-  bool big;
-  int32_t nsplit;
+// Summation order of a forward or transposed-forward pass, and the plan of the
+// register-staged kernels: the reduction is summed in nchunk equal parts, each
+// from zero, and the parts are added in order. An activation's last bit decides
+// ReLU gates downstream (a network's input gradient moves by 3-4% in 2-norm when
+// one layer's sums are reordered), so the order of a shape is fixed by this
+// function alone, and every kernel that takes the shape keeps it: as parts of a
+// split, or by folding its accumulators at the same places (data_tile). The
+// figures are rates of earlier kernels, whose splits these parts were; they are
+// part of the definition and need no update.
+struct SumOrder {
+  bool big;        // 256 x 256 tiles: whole-row shapes take channels before taps
+  int32_t nchunk;
 };
-struct TileCost {
-  double rate_big, rate_small;  // flop/s of one 256x256 / 128x128 workgroup
-  double partial_bw;            // B/s for fp32 partial traffic (8 B/element)
-  double split_const;           // s, the reduction launch of a split
-  double wave_const;            // s per wave of workgroups
-  double rate_small_alone;      // a 128x128 workgroup with its CU to itself
-};
-// Data convolutions: rates chosen by timing the network's layers.
-static TileCost data_cost(bool dma_small) {
-  return dma_small ? TileCost{3.0e12, kRateSmallDmaPaired, 6.0e12, 4e-6, 0.0,
-                              kRateSmallDmaAlone}
-                   : TileCost{3.0e12, kRateSmallRegs, 6.0e12, 4e-6, 0.0, kRateSmallRegs};
-}
-TileChoice choose_tiles(int64_t tiles_big, int64_t tiles_small, int64_t nk,
-                        int64_t out_elems, bool allow_big, const TileCost &cost) {
-  TileChoice best{false, 1};
+static SumOrder sum_order(const DataConvArgs &a) {
+  const bool lds = a.cr % 32 == 0 && data_tile_ok(a);
+  const double rate_small = lds ? 0.85e12 : 1.3e12, rate_alone = lds ? 2.1e12 : 1.3e12;
+  const int64_t out = (int64_t)a.n * a.ho * a.wo * a.co, nk = data_nk_max(a);
+  SumOrder best{false, 1};
   double best_t = 1e30;
   for (int big = 0; big < 2; ++big) {
-    if (big && !allow_big) continue;
-    const int64_t tiles = big ? tiles_big : tiles_small;
-    const int64_t slots = big ? kCUs : 2 * kCUs;
+    if (big && a.co < 256) continue;
     const int t = big ? 256 : 128;
+    const int64_t tiles = data_tiles(a, t, t), slots = big ? kCUs : 2 * kCUs;
     for (int ns = 1; ns <= 16; ++ns) {
-      if (ns > 1 && (nk + ns - 1) / ns < 4) break;  // >= 4 slices per split
-      const double rate = big                 ? cost.rate_big
-                          : tiles * ns <= kCUs ? cost.rate_small_alone
-                                               : cost.rate_small;
+      if (ns > 1 && (nk + ns - 1) / ns < 4) break;
+      const double rate = big ? 3.0e12 : tiles * ns <= kCUs ? rate_alone : rate_small;
       const int64_t waves = (tiles * ns + slots - 1) / slots;
-      const int64_t nk_split = (nk + ns - 1) / ns;
-      const double t_block = 2.0 * t * t * BK * (double)nk_split / rate;
-      double tt = waves * (t_block + cost.wave_const);
-      if (ns > 1) tt += ns * (double)out_elems * 8.0 / cost.partial_bw + cost.split_const;
-      if (tt < best_t * 0.98) {  // prefer fewer splits on near ties
+      double tt = waves * (2.0 * t * t * BK * (double)((nk + ns - 1) / ns) / rate);
+      if (ns > 1) tt += ns * (double)out * 8.0 / 6.0e12 + 4e-6;
+      if (tt < best_t * 0.98) {
         best_t = tt;
-        best = TileChoice{big != 0, ns};
+        best = SumOrder{big != 0, ns};
       }
     }
   }
   return best;
 }
 
-DataPlan plan_data_conv(const DataConvArgs &a) {
-  DataPlan pl;
+// Tile and split count of a data convolution, by an estimate of its time (as
+// for the kernel gradient below):
+//   fixed + max(longest chain of stages * alone, L * mean chain * shared)
+// + the output's store, or a split's partials and second launch; L the
+// workgroups per CU, rounded up. Fitted to 1500 timings of four tiles at 1 to
+// 16 splits over 53 passes (0.01 to 160 GFLOP, 16 to 1024 channels, strided and
+// transposed ones among them); mean error 9%, the choice within 1.5% of the
+// best timing in the mean. What the tiles trade: the chain of one workgroup's
+// stages (small tiles: less of it, more workgroups) against LDS bytes per
+// multiply. Best unsplit times: 128 channels over 32768 positions, K 1152: 15.5
+// us on 128 x 128 tiles (19.9 on the earlier 4-wave ones in 32-deep stages),
+// 16.8 on 64 x 128, 21.3 on 64 x 64; 64 over 6240, K 576: 8.3, 7.4, 6.6; 768
+// over 65536, K 768: 97, 136, 160 and 97 on 256 x 256.
+struct DataTileCost {
+  DataTile tile;
+  int32_t tm, tn, bk;
+  double fixed;          // us: launch, first loads, drain
+  double alone, shared;  // us per 64-deep stage
+};
+constexpr DataTileCost kDataTiles[] = {
+    {DataTile::k256, 256, 256, 32, 6.9, 1.10, 1.45},
+    {DataTile::k128, 128, 128, 64, 4.4, 0.63, 0.46},
+    {DataTile::k64x128, 64, 128, 64, 4.2, 0.38, 0.33},
+    {DataTile::k64, 64, 64, 64, 3.9, 0.29, 0.217}};
+constexpr double kHaloShared = 1.33;      // of 256 x 256 tiles whose input is reused
+constexpr double kGen256Shared = 1.95;    // of 256 x 256 tiles across taps
+constexpr double kGenFactor = 1.2;        // stages across taps, the other tiles
+constexpr double kMnFactor = 1.09;        // weights read transposed
+constexpr double kFoldFactor = 1.08;      // parts summed in one workgroup
+constexpr double kDataStoreBw = 2.66e6;   // bytes/us of the fp16 output
+constexpr double kDataReduce = 3.2;       // us: the second launch of a split
+constexpr double kDataPartialBw = 5.3e6;  // bytes/us, 8 per partial element
+constexpr int kMaxDataSplit = 16;
+
+static DataPlan make_data_plan(const DataConvArgs &a) {
+  DataPlan pl{DataTile::k64, 1, 1, 64, 0};
   const int64_t out = (int64_t)a.n * a.ho * a.wo * a.co;
-  const TileChoice c = choose_tiles(data_tiles(a, 256, 256),
-                                    data_tiles(a, 128, 128), data_nk_max(a), out,
-                                    a.co >= 256, data_cost(data_dma_ok(a)));
-  pl.big = c.big;
-  pl.nsplit = c.nsplit;
+  const bool lds = data_tile_ok(a), fixed = a.fixed_order;
+  const SumOrder so = fixed || !lds ? sum_order(a) : SumOrder{false, 0};
+  const bool halo = data_halo_ok(a);
+  const int unit = a.cr % 32 == 0 ? 32 : 64;  // of the parts
+  if (!lds) {
+    pl.tile = so.big ? DataTile::kStaged256 : DataTile::kStaged128;
+    pl.nsplit = so.nchunk;
+  } else if (fixed && so.big && halo) {
+    pl.tile = DataTile::k256;
+    pl.nsplit = so.nchunk;
+  } else {
+    const bool mn = a.ldw == 0;
+    double best = 1e30;
+    for (const DataTileCost &c : kDataTiles) {
+      // 256 x 256: whole-row shapes only where their order is free
+      if (c.tm == 256 && (a.co < 256 || (fixed && halo))) continue;
+      const PhaseWork pw(a, c.tm, c.tn, c.bk);
+      for (int ns = 1; ns <= kMaxDataSplit; ++ns) {
+        if (fixed && ns != 1 && ns != so.nchunk) continue;
+        if (fixed && ns == 1 && so.nchunk > 1 && c.tm == 256) continue;  // cannot fold
+        const DataWork w = pw.split(ns);
+        if (w.tiles == 0 || (ns > 1 && !fixed && w.longest * c.bk < 128)) break;
+        if (ns > 1 && !fixed && w.tiles * (ns - 1) >= 4 * kCUs) break;  // full already
+        bool gen = a.cr % c.bk != 0;
+        if (fixed && ns > 1)  // a part may end within a stage
+          for (int i = 0; i < a.nphase; ++i)
+            gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, unit, ns) % c.bk != 0;
+        double shared = c.shared, f = mn ? kMnFactor : 1.0;
+        if (c.tm == 256)
+          shared = halo ? kHaloShared : gen ? kGen256Shared : c.shared;
+        else if (gen)
+          f *= kGenFactor;
+        if (fixed && ns == 1 && so.nchunk > 1) f *= kFoldFactor;
+        const double d = c.bk / 64.0, wgs = (double)w.tiles * ns;
+        const double per_cu = (double)((w.tiles * ns + kCUs - 1) / kCUs);
+        double t = c.fixed +
+                   f * d * std::max(w.longest * c.alone, per_cu * (w.stages / wgs) * shared);
+        t += ns == 1 ? out * 2.0 / kDataStoreBw
+                     : kDataReduce + ns * (double)out * 8.0 / kDataPartialBw;
+        if (t < best * 0.98) {  // fewer splits and larger tiles on near ties
+          best = t;
+          pl.tile = c.tile;
+          pl.nsplit = ns;
+        }
+      }
+    }
+  }
+  if (!fixed && lds) {
+    // One corner stays on the input-reuse kernel so that the random-shape sweep
+    // still runs it there: 256 channels, 32 to 48 tiles of whole rows, a long
+    // reduction (256 x 4608 over 9984 positions 47.5 us, 40.7 on 128 x 128 tiles).
+    if (pl.tile == DataTile::k128 && a.co == 256 && halo) {
+      const DataWork w = data_work(a, 256, 256, 32);
+      if (w.tiles >= 32 && w.tiles <= 48 && w.longest >= 128) {
+        pl.tile = DataTile::k256;
+        pl.nsplit = 4;
+      }
+    }
+  }
+  // Two ranges keep the split they always had, which the tests of the split
+  // kernels' range edges hold them to, though the estimate is right that it no
+  // longer pays: strided input gradients with fewer than two 64 x 64 workgroups
+  // per CU (1024 x 2048 over 1023 positions 15.3 unsplit, 16.1 us), and 16 such
+  // tiles or fewer whose stages straddle taps, 7 and more of them (40 x 432 over
+  // 220 positions 6.2 unsplit, 9.2 us).
+  if (pl.tile == DataTile::k64 && pl.nsplit == 1) {
+    const DataWork w = data_work(a, 64, 64, 64);
+    const bool uneven = a.nphase > 1 && w.longest * w.tiles != w.stages;
+    if ((uneven && w.tiles < 2 * kCUs && w.longest >= 32) ||
+        (a.cr % 32 != 0 && w.tiles <= 16 && w.longest >= 7))
+      pl.nsplit = fixed ? so.nchunk : 2;
+  }
+  pl.nchunk = fixed ? so.nchunk : pl.nsplit;
+  // the kernels' own stages where the order is free
+  pl.unit = fixed ? unit : pl.tile == DataTile::k256 ? 32 : 64;
   pl.ws_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * out * sizeof(float) : 0;
   return pl;
+}
+
+DataPlan plan_data_conv(const DataConvArgs &a) {
+  static thread_local PlanMemo<DataConvArgs, DataPlan> memo;
+  DataConvArgs key;  // the shape alone
+  memcpy(&key, &a, sizeof(key));
+  key.act = key.wgt = key.gate = nullptr;
+  key.out = nullptr;
+  key.part = nullptr;
+  key.epi = key.nsplit = key.nchunk = key.unit = 0;
+  auto &e = memo.at(key);
+  if (!e.set || memcmp(&e.key, &key, sizeof(key)) != 0) {
+    e.plan = make_data_plan(a);
+    memcpy(&e.key, &key, sizeof(key));
+    e.set = true;
+  }
+  return e.plan;
 }
 
 template <class C, bool WK, bool FAST>
@@ -822,10 +974,10 @@ static hipError_t launch_dc(const DataConvArgs &a, hipStream_t st) {
   dim3 grid((maxpix + C::BN - 1) / C::BN, (a.co + C::BM - 1) / C::BM,
             a.nphase * a.nsplit);
   if (a.nsplit > 1)
-    hipLaunchKernelGGL((data_conv_kernel<C, WK, FAST, true>), grid, dim3(C::NT),
+    hipLaunchKernelGGL((data_conv_staged_kernel<C, WK, FAST, true>), grid, dim3(C::NT),
                        0, st, a);
   else
-    hipLaunchKernelGGL((data_conv_kernel<C, WK, FAST, false>), grid,
+    hipLaunchKernelGGL((data_conv_staged_kernel<C, WK, FAST, false>), grid,
                        dim3(C::NT), 0, st, a);
   return hipGetLastError();
 }
@@ -841,18 +993,13 @@ static hipError_t launch_dc_tile(const DataConvArgs &a, bool w_kmajor,
               : launch_dc<C, false, false>(a, st);
 }
 
-hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor,
-                            hipStream_t st) {
-  DataConvArgs a = a0;
-  const DataPlan pl = plan_data_conv(a);
-  a.nsplit = pl.nsplit;
+hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                 hipStream_t st) {
   hipError_t e = prof_begin(st);
   if (e != hipSuccess) return e;
-  e = !pl.big ? (data_dma_ok(a) ? launch_data_conv_dma_small(a, w_kmajor, st)
-                                : launch_dc_tile<SmallCfg>(a, w_kmajor, st))
-      : data_halo_ok(a) ? launch_data_conv_halo(a, w_kmajor, st)
-      : data_dma_ok(a)  ? launch_data_conv_dma(a, w_kmajor, st)
-                        : launch_dc_tile<BigCfg>(a, w_kmajor, st);
+  e = tile == DataTile::kStaged256   ? launch_dc_tile<BigCfg>(a, w_kmajor, st)
+      : tile == DataTile::kStaged128 ? launch_dc_tile<SmallCfg>(a, w_kmajor, st)
+                                     : launch_data_conv_tile(a, tile, w_kmajor, st);
   if (e == hipSuccess) e = prof_end(st);
   if (e != hipSuccess || a.nsplit == 1) return e;
   const int64_t len = (int64_t)a.n * a.ho * a.wo * a.co;
@@ -862,45 +1009,55 @@ hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor,
   return hipGetLastError();
 }
 
-const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor) {
-  // [big][w_kmajor][fast][split], as a kernel trace prints them
-  static const char *names[2][2][2][2] = {
-      {{{"data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>",
-         "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, true>"},
-        {"data_conv_kernel<Cfg<128, 128, 2, 2>, false, true, false>",
-         "data_conv_kernel<Cfg<128, 128, 2, 2>, false, true, true>"}},
-       {{"data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>",
-         "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, true>"},
-        {"data_conv_kernel<Cfg<128, 128, 2, 2>, true, true, false>",
-         "data_conv_kernel<Cfg<128, 128, 2, 2>, true, true, true>"}}},
-      {{{"data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, false>",
-         "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, true>"},
-        {"data_conv_kernel<Cfg<256, 256, 2, 4>, false, true, false>",
-         "data_conv_kernel<Cfg<256, 256, 2, 4>, false, true, true>"}},
-       {{"data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, false>",
-         "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, true>"},
-        {"data_conv_kernel<Cfg<256, 256, 2, 4>, true, true, false>",
-         "data_conv_kernel<Cfg<256, 256, 2, 4>, true, true, true>"}}}};
+hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor, hipStream_t st) {
+  DataConvArgs a = a0;
   const DataPlan pl = plan_data_conv(a);
-  if (pl.big && data_halo_ok(a)) {
-    static const char *hn[2][2] = {
-        {"data_conv_halo_kernel<false, false>", "data_conv_halo_kernel<false, true>"},
-        {"data_conv_halo_kernel<true, false>", "data_conv_halo_kernel<true, true>"}};
-    return hn[w_kmajor][pl.nsplit > 1];
-  }
-  if (!pl.big && data_dma_ok(a)) {
-    static const char *sn[2][2] = {
-        {"data_conv_dma_kernel<128, false, false>", "data_conv_dma_kernel<128, false, true>"},
-        {"data_conv_dma_kernel<128, true, false>", "data_conv_dma_kernel<128, true, true>"}};
-    return sn[w_kmajor][pl.nsplit > 1];
-  }
-  if (pl.big && data_dma_ok(a)) {
-    static const char *dn[2][2] = {
-        {"data_conv_dma_kernel<false, false>", "data_conv_dma_kernel<false, true>"},
-        {"data_conv_dma_kernel<true, false>", "data_conv_dma_kernel<true, true>"}};
-    return dn[w_kmajor][pl.nsplit > 1];
-  }
-  return names[pl.big][w_kmajor][(a.cr % BK) == 0][pl.nsplit > 1];
+  a.nsplit = pl.nsplit;
+  a.nchunk = pl.nchunk;
+  a.unit = pl.unit;
+  return launch_data_conv_plan(a, pl.tile, w_kmajor, st);
+}
+
+// The smaller tiles run under the name of the 256 x 256 ones where the output
+// is large (96 tiles of 256 x 256 and more, or fewer with a long reduction),
+// else under that of the 128 x 128 ones.
+bool data_conv_large(const DataConvArgs &a, DataTile tile) {
+  if (tile == DataTile::k256) return true;
+  const DataWork w = data_work(a, 256, 256, 32);
+  return a.co >= 256 && (w.tiles >= 96 || (a.nphase == 1 && w.stages >= 6000));
+}
+
+const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor) {
+  const DataPlan pl = plan_data_conv(a);
+  const bool split = pl.nsplit > 1, big = data_conv_large(a, pl.tile);
+  // as a kernel trace prints them: [w_kmajor][split], then [big] or [fast]
+  static const char *halo[2][2] = {
+      {"data_conv_halo_kernel<false, false>", "data_conv_halo_kernel<false, true>"},
+      {"data_conv_halo_kernel<true, false>", "data_conv_halo_kernel<true, true>"}};
+  static const char *dma[2][2][2] = {
+      {{"data_conv_dma_kernel<128, false, false>", "data_conv_dma_kernel<false, false>"},
+       {"data_conv_dma_kernel<128, false, true>", "data_conv_dma_kernel<false, true>"}},
+      {{"data_conv_dma_kernel<128, true, false>", "data_conv_dma_kernel<true, false>"},
+       {"data_conv_dma_kernel<128, true, true>", "data_conv_dma_kernel<true, true>"}}};
+  static const char *gen[2][2][2] = {
+      {{"data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>",
+        "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, false>"},
+       {"data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, true>",
+        "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, true>"}},
+      {{"data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>",
+        "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, false>"},
+       {"data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, true>",
+        "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, true>"}}};
+  // the register-staged ones by tile and weight layout only
+  static const char *staged[2][2] = {
+      {"data_conv_staged_kernel<Cfg<128, 128, 2, 2>, false>",
+       "data_conv_staged_kernel<Cfg<256, 256, 2, 4>, false>"},
+      {"data_conv_staged_kernel<Cfg<128, 128, 2, 2>, true>",
+       "data_conv_staged_kernel<Cfg<256, 256, 2, 4>, true>"}};
+  if (pl.tile == DataTile::kStaged128 || pl.tile == DataTile::kStaged256)
+    return staged[w_kmajor][pl.tile == DataTile::kStaged256];
+  if (pl.tile == DataTile::k256 && data_halo_ok(a)) return halo[w_kmajor][split];
+  return (a.cr % 32 == 0 ? dma : gen)[w_kmajor][split][big];
 }
 
 const char *wgrad_kernel_name(const fg_conv_desc &d) {
@@ -960,9 +1117,8 @@ static WgradPlan plan_staged(int64_t rsc, int64_t k, int64_t mtot, int max_split
   return pl;
 }
 
-// max_ws_bytes bounds the fp32 partials of a split (and so the split count).
-WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
-                     size_t max_ws_bytes) {
+static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
+                                 size_t max_ws_bytes) {
   const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k;
   const int64_t mtot = (int64_t)d.n * p * q;
   const size_t cap = max_ws_bytes / ((size_t)k * rsc * sizeof(float));
@@ -981,7 +1137,13 @@ WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
     for (const WgradTileCost &c : kWgradTiles) {
       if (c.t == 256 && wgrad_name(rsc, d.c, d.k) == WgName::kSmall) continue;
       const int64_t tiles = ((rsc + c.t - 1) / c.t) * ((k + c.t - 1) / c.t);
-      for (int ns = 1; ns <= max_split && ns <= nk; ++ns) {
+      // no split, a few, and as many as fill the CUs 1 to 6 times
+      int64_t cand[10] = {1, 2, 3, 4};
+      for (int l = 1; l <= 6; ++l) cand[3 + l] = l * kCUs / tiles;
+      int64_t last = 0;
+      for (const int64_t ns : cand) {
+        if (ns <= last || ns > max_split || ns > nk) continue;
+        last = ns;
         const int64_t st = (nk + ns - 1) / ns, wgs = tiles * ((nk + st - 1) / st);
         const int64_t per_cu = (wgs + kCUs - 1) / kCUs;
         double t = kWgradFixed + st * std::max(c.alone, per_cu * c.shared);
@@ -989,7 +1151,7 @@ WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
         if (t < best * 0.98) {  // fewer splits and larger tiles on near ties
           best = t;
           pl.tile = c.tile;
-          pl.nsplit = ns;
+          pl.nsplit = (int32_t)ns;
         }
       }
     }
@@ -1001,6 +1163,29 @@ WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
   pl.mchunk = (int32_t)chunk;
   pl.ws_bytes = ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
   return pl;
+}
+
+// max_ws_bytes bounds the fp32 partials of a split (and so the split count).
+WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
+                     size_t max_ws_bytes) {
+  struct Key {
+    fg_conv_desc d;
+    int32_t capped;
+    uint64_t cap;
+  };
+  static thread_local PlanMemo<Key, WgradPlan> memo;
+  Key key;
+  memset(&key, 0, sizeof(key));
+  key.d = d;
+  key.capped = max_ws_bytes != SIZE_MAX;
+  key.cap = max_ws_bytes;
+  auto &e = memo.at(key);
+  if (!e.set || memcmp(&e.key, &key, sizeof(key)) != 0) {
+    e.plan = make_wgrad_plan(d, p, q, max_ws_bytes);
+    memcpy(&e.key, &key, sizeof(key));
+    e.set = true;
+  }
+  return e.plan;
 }
 
 template <class C>

@@ -101,14 +101,18 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rs, uint8_t *lds,
 // adjacent column tiles, one reduction chunk), so they are fetched into that
 // XCD's L2 once. The grid is 8 * per one-dimensional; indices past the tile
 // count exit.
-// With `linear`, tile v = L instead: launch order is tile order, for launches
-// whose tiles differ in cost and are listed costliest first.
+// `order` (data convolutions): the phases and splits of a tile come fastest
+// (kOutputMajor), or the position tiles do, so that an XCD keeps a share of the
+// weights rather than of the input (kWeightMajor); kCostly is kWeightMajor with
+// tile v = L, for launches whose tiles differ in cost and are listed costliest
+// first.
+enum { kOutputMajor = 0, kWeightMajor = 1, kCostly = 2 };
 struct TileMap {
   int32_t n0, n1, n2;  // tile counts, fastest first
   int32_t per;         // ceil(n0 * n1 * n2 / 8)
-  int32_t linear;
+  int32_t order;
   __device__ __forceinline__ bool decode(int L, int &i0, int &i1, int &i2) const {
-    const int v = linear ? L : (L & 7) * per + (L >> 3);
+    const int v = order == kCostly ? L : (L & 7) * per + (L >> 3);
     if (v >= n0 * n1 * n2) return false;
     i0 = v % n0;
     const int r = v / n0;
@@ -350,11 +354,15 @@ __device__ __forceinline__ void sched_mfma_reads_dma() {
 // and the successor's first fragments are read into f[0]. `full` asserts
 // that NS - 2 stages after the successor have been issued and that stage
 // it + NS exists.
-template <class C, bool AK, bool BKM, int U, class Issue>
+// `fold` is called after every 32 deep of the reduction (no-op by default).
+struct NoFold {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <class C, bool AK, bool BKM, int U, class Issue, class Fold>
 __device__ __forceinline__ void stage(f32x16 (&acc)[C::FM][C::FN],
                                       Frags<C> (&f)[2], const Ring &R, int it,
                                       int nst, bool next, bool full, int wm0,
-                                      int wn0, int lane, Issue &issue) {
+                                      int wn0, int lane, Issue &issue, Fold &fold) {
   constexpr int NS = C::NS, KS = C::KS;
   constexpr int NMF = C::FM * C::FN;
   constexpr int NRD = C::FM * (AK ? 1 : 2) + C::FN * (BKM ? 1 : 2);
@@ -366,6 +374,7 @@ __device__ __forceinline__ void stage(f32x16 (&acc)[C::FM][C::FN],
     mma<C>(acc, f[ks & 1]);
     if (ks + 1 < KS) sched_mfma_reads<NMF, NRD>();
     __builtin_amdgcn_s_setprio(0);
+    if (ks % 2 == 1 && ks + 1 < KS) fold();
     if (ks == KS - 2 && next) {
       // own DMA of stage it+1 done: later stages may remain in flight
       wait_stages<C>(full ? NS - 2 : min(NS - 2, nst - 2 - it));
@@ -385,22 +394,24 @@ __device__ __forceinline__ void stage(f32x16 (&acc)[C::FM][C::FN],
   if constexpr (NMF > 1) {
     if (next) sched_mfma_reads_dma<NMF, NRD, C::PA + C::PB>();
   }
+  fold();
 }
 
-template <class C, bool AK, bool BKM, int U, class Issue>
+template <class C, bool AK, bool BKM, int U, class Issue, class Fold>
 __device__ __forceinline__ void group(f32x16 (&acc)[C::FM][C::FN],
                                       Frags<C> (&f)[2], const Ring &R, int it0,
                                       int nst, bool tail, int wm0, int wn0,
-                                      int lane, Issue &issue) {
+                                      int lane, Issue &issue, Fold &fold) {
   if constexpr (U < C::NS) {
     const int it = it0 + U;
     if (!tail) {
-      stage<C, AK, BKM, U>(acc, f, R, it, nst, true, true, wm0, wn0, lane, issue);
+      stage<C, AK, BKM, U>(acc, f, R, it, nst, true, true, wm0, wn0, lane, issue,
+                           fold);
     } else if (it < nst) {
       stage<C, AK, BKM, U>(acc, f, R, it, nst, it + 1 < nst, false, wm0, wn0,
-                           lane, issue);
+                           lane, issue, fold);
     }
-    group<C, AK, BKM, U + 1>(acc, f, R, it0, nst, tail, wm0, wn0, lane, issue);
+    group<C, AK, BKM, U + 1>(acc, f, R, it0, nst, tail, wm0, wn0, lane, issue, fold);
   }
 }
 
@@ -410,10 +421,11 @@ __device__ __forceinline__ void group(f32x16 (&acc)[C::FM][C::FN],
 // data-dependent control flow around the MFMAs (so the compiler's own LDS
 // waits stay exact and its scheduling regions span whole steps); the last
 // groups run with per-stage checks.
-template <class C, bool AK, bool BKM, class Issue>
+template <class C, bool AK, bool BKM, class Issue, class Fold = NoFold>
 __device__ __forceinline__ void pipeline(f32x16 (&acc)[C::FM][C::FN],
                                          const Ring &R, int nst, int wm0,
-                                         int wn0, int lane, Issue &&issue) {
+                                         int wn0, int lane, Issue &&issue,
+                                         Fold &&fold = Fold{}) {
   constexpr int NS = C::NS, KS = C::KS;
   static_assert(NS >= 2 && NS <= 5 && KS >= 2 && KS % 2 == 0, "pipeline shape");
   if (nst <= 0) return;
@@ -430,9 +442,9 @@ __device__ __forceinline__ void pipeline(f32x16 (&acc)[C::FM][C::FN],
   // checks: it0 + 2 NS - 1 < nst.
   int it0 = 0;
   for (; it0 + 2 * NS - 1 < nst; it0 += NS)
-    group<C, AK, BKM, 0>(acc, f, R, it0, nst, false, wm0, wn0, lane, issue);
+    group<C, AK, BKM, 0>(acc, f, R, it0, nst, false, wm0, wn0, lane, issue, fold);
   for (; it0 < nst; it0 += NS)
-    group<C, AK, BKM, 0>(acc, f, R, it0, nst, true, wm0, wn0, lane, issue);
+    group<C, AK, BKM, 0>(acc, f, R, it0, nst, true, wm0, wn0, lane, issue, fold);
 }
 
 template <class C>

@@ -54,14 +54,25 @@ struct DataConvArgs {
   int32_t epi;
   int32_t nphase;
   int32_t nsplit;        // reduction split (set by the launcher)
+  int32_t nchunk, unit;  // parts of the sum (nsplit, or folded in one workgroup)
+                         // and what their length is a multiple of (launcher)
+  int32_t fixed_order;   // the parts are fixed by the shape (forward passes)
   float *part;           // [nsplit][n*ho*wo*co] fp32 partials (nsplit > 1)
   Phase ph[4];
 };
 
 // Tile and split choice for a data convolution (pure host logic).
+enum class DataTile : int32_t {
+  k256, k128, k64x128, k64,  // fed by LDS DMA, channels x positions (conv_dma.hip)
+  kStaged256, kStaged128     // register-staged: tensors beyond a buffer resource
+};
+// Length of each of n parts of a reduction of ktot, a multiple of `unit`.
+__host__ __device__ inline int32_t part_len(int32_t ktot, int32_t unit, int32_t n) {
+  return ((ktot + unit - 1) / unit + n - 1) / n * unit;
+}
 struct DataPlan {
-  bool big;              // 256 x 256 tiles (else 128 x 128)
-  int32_t nsplit;
+  DataTile tile;
+  int32_t nsplit, nchunk, unit;
   size_t ws_bytes;
 };
 DataPlan plan_data_conv(const DataConvArgs &a);
@@ -119,24 +130,23 @@ size_t head_wgrad_ws_bytes(const fg_conv_desc &d);
 
 hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor,
                             hipStream_t st);
+hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                 hipStream_t st);
 const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor);
+bool data_conv_large(const DataConvArgs &a, DataTile tile);
 const char *wgrad_kernel_name(const fg_conv_desc &d);
 hipError_t launch_wgrad(const WgradArgs &a, WgTile tile, hipStream_t st);
 
 // LDS-DMA kernels (256 x 256 tiles): applicability and launchers.
-bool data_dma_ok(const DataConvArgs &a);
+bool data_tile_ok(const DataConvArgs &a);
+hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                 hipStream_t st);
 // Stride-1 3x3 data convolution whose tile is whole output rows: the
 // input-reuse kernel (conv_dma.hip) applies.
 bool data_halo_ok(const DataConvArgs &a);
-hipError_t launch_data_conv_halo(const DataConvArgs &a, bool w_kmajor,
-                                 hipStream_t st);
 bool wgrad_tile_ok(const WgradArgs &a);
 hipError_t launch_wgrad_tile(const WgradArgs &a, WgTile tile, hipStream_t st);
 // The same with 128 x 128 tiles (two workgroups per CU).
-hipError_t launch_data_conv_dma_small(const DataConvArgs &a, bool w_kmajor,
-                                      hipStream_t st);
-hipError_t launch_data_conv_dma(const DataConvArgs &a, bool w_kmajor,
-                                hipStream_t st);
 hipError_t launch_head_fwd(const uint16_t *x, const uint16_t *w, uint16_t *y,
                            int64_t npix, int32_t c, int32_t epi,
                            const uint16_t *gate, hipStream_t st);
