@@ -23,25 +23,20 @@ __device__ __forceinline__ float h_to_f32(uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, b);
 }
 
-// fp64 -> fp16 bits, one nearest-even rounding (overflow to infinity).
-// The value is first rounded in fp64 to a multiple of the fp16 spacing at its
-// magnitude (rint rounds half to even); the result is an fp16 number, so the
-// remaining conversions are exact.
+// fp64 -> fp16 bits, one nearest-even rounding (overflow to infinity). The
+// value first goes to fp32 rounded to odd (the last bit is set where anything
+// was cut off): fp32 keeps 13 bits more than fp16, so the second rounding then
+// sees on which side of a tie the fp64 value lies. Eight instructions, four of
+// them in fp64; rounding in fp64 to a multiple of the fp16 spacing took some
+// thirty, and bound the pooling kernel (16384 x 768 outputs 25.9 -> 19.9 us).
 __device__ __forceinline__ uint16_t f64_to_h(double d) {
   if (d != d) return 0x7E00;
-  double ad = fabs(d);
-  double r;
-  if (ad >= 65520.0) {
-    r = __builtin_inf();
-  } else if (ad == 0.0) {
-    r = 0.0;
-  } else {
-    int e = ilogb(ad);                 // ad in [2^e, 2^(e+1))
-    int ue = (e < -14 ? -14 : e) - 10; // spacing 2^ue of fp16 at this size
-    r = ldexp(rint(ldexp(ad, -ue)), ue);
-  }
-  r = copysign(r, d);
-  _Float16 h = (_Float16)(float)r;
+  const float f = (float)d;
+  const double e = (double)f;
+  uint32_t u = __builtin_bit_cast(uint32_t, f);
+  u -= fabs(e) > fabs(d);  // back to the value cut off towards zero
+  u |= e != d;
+  const _Float16 h = (_Float16)__builtin_bit_cast(float, u);
   return __builtin_bit_cast(uint16_t, h);
 }
 
@@ -75,6 +70,19 @@ __device__ __forceinline__ bool nonfinite_h2(uint32_t w) {
 __device__ __forceinline__ void flag_nonfinite(int32_t *flag, bool bad) {
   const unsigned long long b = __ballot(bad);
   if (b != 0 && (threadIdx.x & 63) == (unsigned)__builtin_ctzll(b)) *flag = 1;
+}
+
+// Index of the last of n table entries whose first workgroup, start(i), is at
+// most b (starts rise from 0). Every lane looks at its own entries, so the wave
+// waits for one load where a binary search waits for six or seven in turn.
+template <class Start>
+__device__ __forceinline__ int find_entry(int n, uint32_t b, Start &&start) {
+  int below = 0;
+  for (int k = 0; k < n; k += 64) {
+    const int i = k + (threadIdx.x & 63);
+    below += __popcll(__ballot(i < n && start(i < n ? i : 0) <= b));
+  }
+  return __builtin_amdgcn_readfirstlane(below - 1);
 }
 
 }  // namespace fg
