@@ -48,18 +48,14 @@ struct OptParams {
 };
 
 __device__ __forceinline__ int opt_piece(const OptTable &t, uint32_t b) {
-  int lo = 0, hi = t.n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (t.p[mid].block0 <= b) lo = mid; else hi = mid - 1;
-  }
-  return lo;
+  return find_entry(t.n, b, [&](int i) { return t.p[i].block0; });
 }
 
+// Any of the flags set (a lane each: one load to wait for).
 __device__ __forceinline__ bool opt_skip(const int32_t *flags, int nflags) {
   bool any = false;
-  for (int i = 0; i < nflags; ++i) any |= flags[i] != 0;
-  return any;
+  for (int i = threadIdx.x & 63; i < nflags; i += 64) any |= flags[i] != 0;
+  return __ballot(any) != 0;
 }
 
 // Per-step constants. The bias corrections 1 - b^t are formed in fp64 (in
@@ -79,9 +75,24 @@ struct OptStep {
   }
 };
 
+// b^t by repeated squaring (t >= 1). Every squaring doubles the relative error:
+// t * 2^-53 in all, so that of 1 - b^t stays below 1e-8 of the fp32 rounding of
+// the reciprocal it becomes. pow() is some 300 fp64 instructions that every
+// thread waits for first: with the table search and the flags below, the norms
+// and apply kernels of a small update (38 tensors, 169 k elements) 6.7 and 7.2
+// -> 5.3 and 6.0 us.
+__device__ __forceinline__ double ipow(double b, int t) {
+  double r = 1.0;
+  for (; t > 0; t >>= 1) {
+    if (t & 1) r *= b;
+    b *= b;
+  }
+  return r;
+}
+
 __device__ __forceinline__ OptStep opt_step(const OptParams &p, int t) {
-  const double bc1 = 1.0 - pow((double)p.b1, (double)t);
-  const double bc2 = 1.0 - pow((double)p.b2, (double)t);
+  const double bc1 = 1.0 - ipow((double)p.b1, t);
+  const double bc2 = 1.0 - ipow((double)p.b2, t);
   return OptStep{p.b1, 1.f - p.b1, p.b2, 1.f - p.b2, p.eps, p.wd,
                  (float)(1.0 / bc1), (float)(1.0 / bc2)};
 }
@@ -103,8 +114,8 @@ struct Grad {
   float inv;
   __device__ __forceinline__ f32x4 load4(uint32_t i) const {
     if constexpr (H) {
-      const u32x2 h = *reinterpret_cast<const u32x2 *>(
-          reinterpret_cast<const uint16_t *>(p) + i);
+      const u32x2 h = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(
+          reinterpret_cast<const uint16_t *>(p) + i));
       f32x4 g;
       g[0] = h_to_f32((uint16_t)h[0]) * inv;
       g[1] = h_to_f32((uint16_t)(h[0] >> 16)) * inv;
@@ -114,7 +125,8 @@ struct Grad {
       for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(g[e]));
       return g;
     } else {
-      return *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(p) + i);
+      return __builtin_nontemporal_load(
+          reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(p) + i));
     }
   }
   __device__ __forceinline__ float load1(uint32_t j) const {
@@ -128,6 +140,18 @@ struct Grad {
   }
 };
 
+// The update streams 46 bytes per parameter and finds nothing of an array in a
+// cache when it comes back to it, but what it allocates there pushes out what the
+// step still needs and has to be written back: all its large accesses are
+// non-temporal. Norms and apply over 38.9 M parameters 356 -> 290 us (loads of
+// the norms pass alone 303, of both 298).
+__device__ __forceinline__ f32x4 ld_nt(const float *p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+}
+__device__ __forceinline__ void st_nt(float *p, const f32x4 &v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+}
+
 // One 4-element chunk of a layer's arrays, zero beyond the layer's end
 // (zeros add nothing to either sum).
 template <bool H>
@@ -139,9 +163,9 @@ __device__ __forceinline__ void load_chunk(const OptPiece &pc, const Grad<H> &gr
   const float *vp = reinterpret_cast<const float *>(pc.v);
   if (i + 4 <= end) {
     g = gr.load4(i);
-    w = *reinterpret_cast<const f32x4 *>(wp + i);
-    m = *reinterpret_cast<const f32x4 *>(mp + i);
-    v = *reinterpret_cast<const f32x4 *>(vp + i);
+    w = ld_nt(wp + i);
+    m = ld_nt(mp + i);
+    v = ld_nt(vp + i);
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -278,9 +302,9 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
       w[c][e] = w[c][e] - step * s.u(mm, vv);
     }
     if (i + 4 <= end) {
-      *reinterpret_cast<f32x4 *>(mp + i) = m[c];
-      *reinterpret_cast<f32x4 *>(vp + i) = v[c];
-      *reinterpret_cast<f32x4 *>(wp + i) = w[c];
+      st_nt(mp + i, m[c]);
+      st_nt(vp + i, v[c]);
+      st_nt(wp + i, w[c]);
       u32x2 h;
       h[0] = (uint32_t)stored_f32_to_h(w[c][0]) |
              ((uint32_t)stored_f32_to_h(w[c][1]) << 16);
