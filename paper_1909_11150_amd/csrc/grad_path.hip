@@ -5,26 +5,22 @@
 // Pack and unpack are one launch each over all members of a group: the host
 // turns the members (and, for pack, the gaps between them) into "pieces",
 // gives every piece a contiguous range of workgroups, and each workgroup
-// finds its piece by binary search over the piece table passed by value.
+// finds its piece in the piece table passed by value.
 #include "common.h"
 #include "internal.h"
 
 namespace fg {
 
 // Streaming knobs: 16-byte vectors in flight per thread (fp16; twice as many
-// for the fp32 copy), and non-temporal loads / stores. Measured on MI355X
-// with the caches evicted, the nine 25 MiB groups back to back: 2 vectors
-// gave pack 4.46, unscale 4.18, unpack 4.86 TB/s; 4 gave 4.27 / 4.07 / 3.35;
-// 8 gave 2.74 / 2.91 / 4.61. Non-temporal stores gained nothing, and
-// interleaving the workgroups' chunks changed nothing.
+// for the fp32 copy). Measured on MI355X with the caches evicted, the nine 25 MiB
+// groups back to back: 2 vectors gave pack 4.46, unscale 4.18, unpack 4.86 TB/s;
+// 4 gave 4.27 / 4.07 / 3.35; 8 gave 2.74 / 2.91 / 4.61. Interleaving the
+// workgroups' chunks changed nothing. Loads are non-temporal: nothing reads a
+// source again, so it should not push the written buffers, which the next call
+// reads, out of the caches (four groups of 38.9 M elements through pack, unscale,
+// unpack and the optimizer 444 -> 436 us; non-temporal stores too: 445).
 #ifndef FG_GRAD_VECS
 #define FG_GRAD_VECS 2
-#endif
-#ifndef FG_GRAD_NT_LOAD
-#define FG_GRAD_NT_LOAD 0
-#endif
-#ifndef FG_GRAD_NT_STORE
-#define FG_GRAD_NT_STORE 0
 #endif
 
 constexpr int kGradThreads = 256;
@@ -34,20 +30,7 @@ constexpr int kPieceElems = kGradThreads * 8 * FG_GRAD_VECS;
 
 template <class T>
 __device__ __forceinline__ T ld_stream(const T *p) {
-#if FG_GRAD_NT_LOAD
   return __builtin_nontemporal_load(p);
-#else
-  return *p;
-#endif
-}
-
-template <class T>
-__device__ __forceinline__ void st_stream(T *p, const T &v) {
-#if FG_GRAD_NT_STORE
-  __builtin_nontemporal_store(v, p);
-#else
-  *p = v;
-#endif
 }
 
 struct Piece {
@@ -64,12 +47,7 @@ struct PieceTable {
 };
 
 __device__ __forceinline__ int find_piece(const PieceTable &t, uint32_t b) {
-  int lo = 0, hi = t.npiece - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (t.p[mid].block0 <= b) lo = mid; else hi = mid - 1;
-  }
-  return lo;
+  return find_entry(t.npiece, b, [&](int i) { return t.p[i].block0; });
 }
 
 // Bit copy of ESZ-byte elements (2: fp16 pack, 4: fp32 unpack); a piece with
@@ -102,7 +80,7 @@ __global__ __launch_bounds__(kGradThreads) void copy_pieces_kernel(
     for (int j = 0; j < NV; ++j) {
       const uint64_t i =
           beg + ((uint64_t)j * kGradThreads + threadIdx.x) * EPV;
-      if (i < nvec_end) st_stream(reinterpret_cast<u32x4 *>(pc.dst + i * ESZ), v[j]);
+      if (i < nvec_end) *reinterpret_cast<u32x4 *>(pc.dst + i * ESZ) = v[j];
     }
     // the last (< EPV) elements of the piece
     const uint64_t i = nvec_end + threadIdx.x;
@@ -200,7 +178,8 @@ __device__ __forceinline__ bool nonfinite16(uint32_t h) {
 constexpr int kUnscaleVecs = FG_GRAD_VECS;
 
 __global__ __launch_bounds__(kGradThreads) void unscale_vec_kernel(
-    const uint16_t *in, uint64_t nvec, float inv, float *out, int32_t *flag) {
+    const uint16_t *in, uint64_t nvec, uint32_t tail, float inv, float *out,
+    int32_t *flag) {
   const uint64_t base = (uint64_t)blockIdx.x * (kGradThreads * kUnscaleVecs);
   u32x4 w[kUnscaleVecs];
 #pragma unroll
@@ -229,21 +208,28 @@ __global__ __launch_bounds__(kGradThreads) void unscale_vec_kernel(
       }
     }
     if (v < nvec) {
-      st_stream(reinterpret_cast<f32x4 *>(out + v * 8), o0);
-      st_stream(reinterpret_cast<f32x4 *>(out + v * 8 + 4), o1);
+      *reinterpret_cast<f32x4 *>(out + v * 8) = o0;
+      *reinterpret_cast<f32x4 *>(out + v * 8 + 4) = o1;
     }
+  }
+  // the last workgroup takes the values after the last whole vector too (a
+  // second launch for them cost 4.6 us of a 25 MiB group's 12.3)
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x < tail) {
+    const uint64_t i = nvec * 8 + threadIdx.x;
+    const uint16_t h = in[i];
+    bad |= nonfinite16(h);
+    out[i] = h_to_f32(h) * inv;
   }
   // zero words past the end convert to finite values: bad is exact
   flag_nonfinite(flag, bad);
 }
 
 __global__ __launch_bounds__(kGradThreads) void unscale_scalar_kernel(
-    const uint16_t *in, uint64_t beg, uint64_t end, float inv, float *out,
-    int32_t *flag) {
+    const uint16_t *in, uint64_t end, float inv, float *out, int32_t *flag) {
   bool bad = false;
   const uint64_t stride = (uint64_t)gridDim.x * kGradThreads;
-  for (uint64_t i = beg + (uint64_t)blockIdx.x * kGradThreads + threadIdx.x;
-       i < end; i += stride) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kGradThreads + threadIdx.x; i < end;
+       i += stride) {
     uint16_t h = in[i];
     bad |= nonfinite16(h);
     out[i] = h_to_f32(h) * inv;
@@ -260,23 +246,17 @@ hipError_t launch_unscale(const uint16_t *group, uint64_t numel,
   if (nvec) {
     const uint64_t per = (uint64_t)kGradThreads * kUnscaleVecs;
     const uint64_t blocks = (nvec + per - 1) / per;  // < 2^26 for numel < 2^31
-    hipLaunchKernelGGL(unscale_vec_kernel, dim3((unsigned)blocks),
-                       dim3(kGradThreads), 0, st, group, nvec, inv_scale, out,
-                       flag);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  uint64_t beg = nvec * 8;
-  if (beg < numel) {
-    uint64_t n = numel - beg;
-    uint64_t blocks = (n + kGradThreads - 1) / kGradThreads;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(unscale_scalar_kernel, dim3((unsigned)blocks),
-                       dim3(kGradThreads), 0, st, group, beg, numel, inv_scale,
-                       out, flag);
+    hipLaunchKernelGGL(unscale_vec_kernel, dim3((unsigned)blocks), dim3(kGradThreads), 0,
+                       st, group, nvec, (uint32_t)(numel % 8), inv_scale, out, flag);
     return hipGetLastError();
   }
-  return hipSuccess;
+  // misaligned, or shorter than a vector
+  if (!numel) return hipSuccess;
+  uint64_t blocks = (numel + kGradThreads - 1) / kGradThreads;
+  if (blocks > 8192) blocks = 8192;
+  hipLaunchKernelGGL(unscale_scalar_kernel, dim3((unsigned)blocks), dim3(kGradThreads), 0,
+                     st, group, numel, inv_scale, out, flag);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
