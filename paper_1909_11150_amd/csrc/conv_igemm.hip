@@ -339,6 +339,42 @@ __global__ __launch_bounds__(C::NT) void data_conv_staged_kernel(DataConvArgs a)
   }
 }
 
+// Elements i4..i4+3 of part[first], part[first + step], ... (first < nsplit)
+// summed in that order. A short sum is bound by the latency of its loads, so
+// four are issued before their adds; one load a step, as before, waits for
+// each in turn. 3x3 kernel gradients, 16 channels (2304 outputs): 4.4 -> 3.2
+// us; 128 channels, 5.1 -> 4.3; 1x1 of 768 channels, 12.2 -> 11.1.
+__device__ __forceinline__ f32x4 sum_parts(const float *part, int first, int step, int nsplit,
+                                           int64_t len, int64_t i4) {
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  int k = first;
+  bool any = false;
+  auto add = [&](const f32x4 &v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = any ? s[e] + v[e] : v[e];
+    any = true;
+  };
+  for (; k + 3 * step < nsplit; k += 4 * step) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      v[u] = *reinterpret_cast<const f32x4 *>(part + (size_t)(k + u * step) * len + i4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(v[u]);
+  }
+  if (k >= nsplit) return s;
+  // the last 1 to 3, loaded together too (absent ones repeat the first)
+  f32x4 v[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    v[u] = *reinterpret_cast<const f32x4 *>(
+        part + (size_t)(k + u * step < nsplit ? k + u * step : first) * len + i4);
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (k + u * step < nsplit) add(v[u]);
+  return s;
+}
+
 // Sum nsplit fp32 partial arrays of len elements (dense, co channels per
 // pixel) in split order, apply the epilogue, round to fp16 into out (and
 // read gate) at pixel stride ldo. len and co are multiples of 4.
@@ -347,12 +383,7 @@ __global__ __launch_bounds__(256) void split_epilogue_kernel(
     const uint16_t *gate, uint16_t *out) {
   int64_t i4 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i4 >= len) return;
-  f32x4 s = *reinterpret_cast<const f32x4 *>(part + i4);
-  for (int k = 1; k < nsplit; ++k) {
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part + (size_t)k * len + i4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] += v[e];
-  }
+  const f32x4 s = sum_parts(part, 0, 1, nsplit, len, i4);
   const int64_t pix = i4 / co;
   const int64_t o = pix * ldo + (i4 - pix * co);
   float v[4] = {s[0], s[1], s[2], s[3]};
@@ -509,12 +540,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float *part,
   int64_t i4 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   bool bad = false;
   if (i4 < len) {
-    f32x4 s = *reinterpret_cast<const f32x4 *>(part + i4);
-    for (int k = 1; k < nsplit; ++k) {
-      f32x4 v = *reinterpret_cast<const f32x4 *>(part + (size_t)k * len + i4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] += v[e];
-    }
+    const f32x4 s = sum_parts(part, 0, 1, nsplit, len, i4);
     const u32x2 h = to_h4(s[0], s[1], s[2], s[3]);
     bad = nonfinite_h2(h[0]) | nonfinite_h2(h[1]);
     *reinterpret_cast<u32x2 *>(out + i4) = h;
@@ -530,11 +556,7 @@ __global__ __launch_bounds__(256) void split_reduce_wide_kernel(
   __shared__ f32x4 red[256];
   const int64_t i4 = (int64_t)blockIdx.x * 4;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  for (int k = threadIdx.x; k < nsplit; k += 256) {
-    f32x4 v = *reinterpret_cast<const f32x4 *>(part + (size_t)k * len + i4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] += v[e];
-  }
+  if ((int)threadIdx.x < nsplit) s = sum_parts(part, threadIdx.x, 256, nsplit, len, i4);
   red[threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -557,8 +579,8 @@ __global__ __launch_bounds__(256) void split_reduce_wide_kernel(
 // Same sum for a moderate number of longer partials (more than
 // kMaxSerialSplit splits): each workgroup covers 64 outputs as 16 groups of
 // 4, with 16 lanes per group; lane j adds splits j, j + 16, ... in order,
-// then a fixed-shape tree combines the 16 lane sums. (The serial sum of
-// split_reduce_kernel would wait on its many loads one by one.)
+// then a fixed-shape tree combines the 16 lane sums. (In the serial sum of
+// split_reduce_kernel the loads of a group wait for the group before.)
 constexpr int kMaxSerialSplit = 16;
 __global__ __launch_bounds__(256) void split_reduce_multi_kernel(
     const float *part, int nsplit, int64_t len, uint16_t *out, int32_t *flag) {
@@ -566,12 +588,7 @@ __global__ __launch_bounds__(256) void split_reduce_multi_kernel(
   const int grp = threadIdx.x & 15, lane = threadIdx.x >> 4;
   const int64_t i4 = ((int64_t)blockIdx.x * 16 + grp) * 4;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (i4 < len)
-    for (int k = lane; k < nsplit; k += 16) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(part + (size_t)k * len + i4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] += v[e];
-    }
+  if (i4 < len) s = sum_parts(part, lane, 16, nsplit, len, i4);  // nsplit > 16 > lane
   red[lane][grp] = s;
   __syncthreads();
   for (int w = 8; w > 0; w >>= 1) {
