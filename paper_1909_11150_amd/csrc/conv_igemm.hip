@@ -1182,9 +1182,14 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
   return pl;
 }
 
-// max_ws_bytes bounds the fp32 partials of a split (and so the split count).
+// max_ws_bytes bounds the fp32 partials of a split (and so the split count);
+// a bound that the plan without one keeps does not change the plan.
 WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
                      size_t max_ws_bytes) {
+  if (max_ws_bytes != SIZE_MAX) {
+    const WgradPlan pl = plan_wgrad(d, p, q, SIZE_MAX);
+    if (pl.ws_bytes <= max_ws_bytes) return pl;
+  }
   struct Key {
     fg_conv_desc d;
     int32_t capped;
