@@ -2,8 +2,8 @@
 // data convolutions, then the kernel gradients.
 //
 // Same GEMM formulation as the register-staged kernels in conv_igemm.hip
-// (rows = output channels, columns = output positions of one phase), for
-// 256 x 256 and 128 x 128 tiles. Operands go from global memory straight
+// (rows = output channels, columns = output positions of one phase), on
+// tiles from 64 x 64 to 256 x 256. Operands go from global memory straight
 // into LDS: no register staging and no LDS store instructions. A ring of NS
 // reduction stages, each BK deep, is kept in LDS, so a stage's loads are
 // issued NS - 1 stages before they are consumed. Padding and ragged tails

@@ -137,7 +137,7 @@ bool data_conv_large(const DataConvArgs &a, DataTile tile);
 const char *wgrad_kernel_name(const fg_conv_desc &d);
 hipError_t launch_wgrad(const WgradArgs &a, WgTile tile, hipStream_t st);
 
-// LDS-DMA kernels (256 x 256 tiles): applicability and launchers.
+// Kernels fed by LDS DMA, on every tile: applicability and launchers.
 bool data_tile_ok(const DataConvArgs &a);
 hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_kmajor,
                                  hipStream_t st);
@@ -146,7 +146,6 @@ hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_km
 bool data_halo_ok(const DataConvArgs &a);
 bool wgrad_tile_ok(const WgradArgs &a);
 hipError_t launch_wgrad_tile(const WgradArgs &a, WgTile tile, hipStream_t st);
-// The same with 128 x 128 tiles (two workgroups per CU).
 hipError_t launch_head_fwd(const uint16_t *x, const uint16_t *w, uint16_t *y,
                            int64_t npix, int32_t c, int32_t epi,
                            const uint16_t *gate, hipStream_t st);
