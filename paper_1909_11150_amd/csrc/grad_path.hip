@@ -13,12 +13,14 @@ namespace fg {
 
 // Streaming knobs: 16-byte vectors in flight per thread (fp16; twice as many
 // for the fp32 copy). Measured on MI355X with the caches evicted, the nine 25 MiB
-// groups back to back: 2 vectors gave pack 4.46, unscale 4.18, unpack 4.86 TB/s;
-// 4 gave 4.27 / 4.07 / 3.35; 8 gave 2.74 / 2.91 / 4.61. Interleaving the
-// workgroups' chunks changed nothing. Loads are non-temporal: nothing reads a
-// source again, so it should not push the written buffers, which the next call
-// reads, out of the caches (four groups of 38.9 M elements through pack, unscale,
-// unpack and the optimizer 444 -> 436 us; non-temporal stores too: 445).
+// groups back to back, with plain loads: 2 vectors gave pack 4.46, unscale 4.18,
+// unpack 4.86 TB/s; 4 gave 4.27 / 4.07 / 3.35; 8 gave 2.74 / 2.91 / 4.61.
+// Interleaving the workgroups' chunks changed nothing. Loads are non-temporal:
+// nothing reads a source again, so it should not push the written buffers, which
+// the next call reads, out of the caches. Each kernel gains by itself: pack 4.40
+// -> 4.53, unscale 4.20 -> 4.34, unpack 4.84 -> 5.11, and all three with
+// the optimizer 444 -> 430 us over 38.9 M elements in four groups (non-temporal
+// stores as well lost 9 us of that).
 #ifndef FG_GRAD_VECS
 #define FG_GRAD_VECS 2
 #endif
@@ -46,8 +48,18 @@ struct PieceTable {
   Piece p[kMaxPieces];
 };
 
+// Binary search by the block index, which is the same in every lane: the entries
+// come by scalar loads from the kernel arguments, and a group has few members. One
+// vector load per lane and a ballot (find_entry, which the optimizer's longer
+// tables take) waits for memory once before every workgroup's copy: pack of the
+// nine 25 MiB groups 4.20 -> 4.53 TB/s without it, unpack 4.92 -> 5.11.
 __device__ __forceinline__ int find_piece(const PieceTable &t, uint32_t b) {
-  return find_entry(t.npiece, b, [&](int i) { return t.p[i].block0; });
+  int lo = 0, hi = t.npiece - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (t.p[mid].block0 <= b) lo = mid; else hi = mid - 1;
+  }
+  return lo;
 }
 
 // Bit copy of ESZ-byte elements (2: fp16 pack, 4: fp32 unpack); a piece with
