@@ -24,6 +24,7 @@
 // device: the ratio and apply kernels read the flags and return, so the host
 // never waits.
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -106,15 +107,35 @@ __device__ __forceinline__ uint16_t stored_f32_to_h(float v) {
   return f32_to_h(v);
 }
 
+// Streaming access. An update reads 14 or 16 bytes per parameter twice and writes
+// 14. Where the arrays do not fit the Infinity Cache, nothing of an array is
+// found there when the update comes back to it, and what it allocates pushes out
+// what the step still needs and has to be written back: its large accesses are
+// then non-temporal (NT). Where they fit, the apply pass finds what the norms
+// pass read. Norms and apply, plain and NT: 9 M parameters 70 and 77 us, 16 M 114
+// and 125, 20 M 166 and 152, 38.9 M 352 and 279 (fp32 gradients; 16 M of them
+// read 256 MB).
+template <bool NT, class T>
+__device__ __forceinline__ T ld_opt(const T *p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool NT>
+__device__ __forceinline__ void st_opt(float *p, const f32x4 &v) {
+  if (NT)
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+  else
+    *reinterpret_cast<f32x4 *>(p) = v;
+}
+
 // Gradient access: fp32 as stored, or fp16 times 1/S (materialised before
 // use, so that the update sees the same fp32 value in both forms).
-template <bool H>
+template <bool H, bool NT>
 struct Grad {
   uint64_t p;
   float inv;
   __device__ __forceinline__ f32x4 load4(uint32_t i) const {
     if constexpr (H) {
-      const u32x2 h = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(
+      const u32x2 h = ld_opt<NT>(reinterpret_cast<const u32x2 *>(
           reinterpret_cast<const uint16_t *>(p) + i));
       f32x4 g;
       g[0] = h_to_f32((uint16_t)h[0]) * inv;
@@ -125,7 +146,7 @@ struct Grad {
       for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(g[e]));
       return g;
     } else {
-      return __builtin_nontemporal_load(
+      return ld_opt<NT>(
           reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(p) + i));
     }
   }
@@ -140,22 +161,10 @@ struct Grad {
   }
 };
 
-// The update streams 46 bytes per parameter and finds nothing of an array in a
-// cache when it comes back to it, but what it allocates there pushes out what the
-// step still needs and has to be written back: all its large accesses are
-// non-temporal. Norms and apply over 38.9 M parameters 356 -> 290 us (loads of
-// the norms pass alone 303, of both 298).
-__device__ __forceinline__ f32x4 ld_nt(const float *p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-}
-__device__ __forceinline__ void st_nt(float *p, const f32x4 &v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
-}
-
 // One 4-element chunk of a layer's arrays, zero beyond the layer's end
 // (zeros add nothing to either sum).
-template <bool H>
-__device__ __forceinline__ void load_chunk(const OptPiece &pc, const Grad<H> &gr,
+template <bool H, bool NT>
+__device__ __forceinline__ void load_chunk(const OptPiece &pc, const Grad<H, NT> &gr,
                                            uint32_t i, uint32_t end, f32x4 &g,
                                            f32x4 &w, f32x4 &m, f32x4 &v) {
   const float *wp = reinterpret_cast<const float *>(pc.w32);
@@ -163,9 +172,9 @@ __device__ __forceinline__ void load_chunk(const OptPiece &pc, const Grad<H> &gr
   const float *vp = reinterpret_cast<const float *>(pc.v);
   if (i + 4 <= end) {
     g = gr.load4(i);
-    w = ld_nt(wp + i);
-    m = ld_nt(mp + i);
-    v = ld_nt(vp + i);
+    w = ld_opt<NT>(reinterpret_cast<const f32x4 *>(wp + i));
+    m = ld_opt<NT>(reinterpret_cast<const f32x4 *>(mp + i));
+    v = ld_opt<NT>(reinterpret_cast<const f32x4 *>(vp + i));
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -206,21 +215,21 @@ __device__ __forceinline__ void block_sum2(T &a, T &b) {
 
 // Workgroup b0 + blockIdx.x of the table: sum of u^2 and of w^2 over its
 // kOptElems elements into part[2b], part[2b+1].
-template <bool H>
+template <bool H, bool NT>
 __global__ __launch_bounds__(kOptThreads) void lars_adam_norms_kernel(
     OptTable t, OptParams p, float inv, const int32_t *step_count, uint32_t b0,
     float *part) {
   const uint32_t b = b0 + blockIdx.x;
   const OptPiece pc = t.p[opt_piece(t, b)];
   const OptStep s = opt_step(p, *step_count + 1);
-  const Grad<H> gr{pc.g, inv};
+  const Grad<H, NT> gr{pc.g, inv};
   const uint32_t beg = (b - pc.block0) * (uint32_t)kOptElems;
   const uint32_t end = min(pc.numel, beg + (uint32_t)kOptElems);
   f32x4 g[kOptIters], w[kOptIters], m[kOptIters], v[kOptIters];
 #pragma unroll
   for (int c = 0; c < kOptIters; ++c) {
     const uint32_t i = beg + (c * kOptThreads + threadIdx.x) * 4;
-    load_chunk<H>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
+    load_chunk<H, NT>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
   }
   float su = 0.f, sw = 0.f;
 #pragma unroll
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_ratio_kernel(
 }
 
 // Workgroup b0 + blockIdx.x of the table.
-template <bool H>
+template <bool H, bool NT>
 __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
     OptTable t, OptParams p, float inv, const int32_t *flags, int nflags,
     const float *ratio, const int32_t *t_cur, uint32_t b0) {
@@ -277,7 +286,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
   const OptPiece pc = t.p[pi];
   const OptStep s = opt_step(p, *t_cur);
   const float step = p.lr * ratio[pi];
-  const Grad<H> gr{pc.g, inv};
+  const Grad<H, NT> gr{pc.g, inv};
   float *wp = reinterpret_cast<float *>(pc.w32);
   float *mp = reinterpret_cast<float *>(pc.m);
   float *vp = reinterpret_cast<float *>(pc.v);
@@ -288,7 +297,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
 #pragma unroll
   for (int c = 0; c < kOptIters; ++c) {
     const uint32_t i = beg + (c * kOptThreads + threadIdx.x) * 4;
-    load_chunk<H>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
+    load_chunk<H, NT>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
   }
 #pragma unroll
   for (int c = 0; c < kOptIters; ++c) {
@@ -302,9 +311,9 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
       w[c][e] = w[c][e] - step * s.u(mm, vv);
     }
     if (i + 4 <= end) {
-      st_nt(mp + i, m[c]);
-      st_nt(vp + i, v[c]);
-      st_nt(wp + i, w[c]);
+      st_opt<NT>(mp + i, m[c]);
+      st_opt<NT>(vp + i, v[c]);
+      st_opt<NT>(wp + i, w[c]);
       u32x2 h;
       h[0] = (uint32_t)stored_f32_to_h(w[c][0]) |
              ((uint32_t)stored_f32_to_h(w[c][1]) << 16);
@@ -367,6 +376,21 @@ static void block_range(const OptTable &t, int32_t first, int32_t count, uint32_
   b1 = first + count < t.n ? t.p[first + count].block0 : t.nblocks;
 }
 
+// f(H, NT) with the gradient form and the access (see ld_opt) as constants. The
+// line is the Infinity Cache's 256 MiB against what the whole table's update
+// reads: the arrays of one launch of several are read again with all the others'.
+template <class F>
+static void opt_dispatch(const fg_opt_tensor *ts, int32_t n, bool fp16_grad, F &&f) {
+  using std::false_type, std::true_type;
+  uint64_t elems = 0;
+  for (int i = 0; i < n; ++i) elems += ts[i].numel;
+  const bool nt = elems * (fp16_grad ? 14 : 16) > (256ull << 20);
+  if (fp16_grad)
+    nt ? f(true_type{}, true_type{}) : f(true_type{}, false_type{});
+  else
+    nt ? f(false_type{}, true_type{}) : f(false_type{}, false_type{});
+}
+
 hipError_t launch_lars_adam_norms(const fg_opt_tensor *ts, int32_t n, int32_t first,
                                   int32_t count, const fg_opt_params &pp, bool fp16_grad,
                                   float inv_scale, const int32_t *step_count, void *ws,
@@ -377,12 +401,10 @@ hipError_t launch_lars_adam_norms(const fg_opt_tensor *ts, int32_t n, int32_t fi
   uint32_t b0, b1;
   block_range(t, first, count, b0, b1);
   const OptWs w = opt_ws(ws, t.nblocks);
-  if (fp16_grad)
-    hipLaunchKernelGGL(lars_adam_norms_kernel<true>, dim3(b1 - b0), dim3(kOptThreads), 0,
-                       st, t, p, inv_scale, step_count, b0, w.part);
-  else
-    hipLaunchKernelGGL(lars_adam_norms_kernel<false>, dim3(b1 - b0), dim3(kOptThreads), 0,
-                       st, t, p, inv_scale, step_count, b0, w.part);
+  opt_dispatch(ts, n, fp16_grad, [&](auto h, auto nt) {
+    hipLaunchKernelGGL((lars_adam_norms_kernel<h.value, nt.value>), dim3(b1 - b0),
+                       dim3(kOptThreads), 0, st, t, p, inv_scale, step_count, b0, w.part);
+  });
   return hipGetLastError();
 }
 
@@ -403,12 +425,11 @@ hipError_t launch_lars_adam_apply(const fg_opt_tensor *ts, int32_t n, int32_t fi
   }
   uint32_t b0, b1;
   block_range(t, first, count, b0, b1);
-  if (fp16_grad)
-    hipLaunchKernelGGL(lars_adam_apply_kernel<true>, dim3(b1 - b0), dim3(kOptThreads), 0,
-                       st, t, p, inv_scale, flags, nflags, w.ratio, w.t_cur, b0);
-  else
-    hipLaunchKernelGGL(lars_adam_apply_kernel<false>, dim3(b1 - b0), dim3(kOptThreads), 0,
-                       st, t, p, inv_scale, flags, nflags, w.ratio, w.t_cur, b0);
+  opt_dispatch(ts, n, fp16_grad, [&](auto h, auto nt) {
+    hipLaunchKernelGGL((lars_adam_apply_kernel<h.value, nt.value>), dim3(b1 - b0),
+                       dim3(kOptThreads), 0, st, t, p, inv_scale, flags, nflags, w.ratio,
+                       w.t_cur, b0);
+  });
   return hipGetLastError();
 }
 

@@ -497,8 +497,12 @@ class StepProgram:
             tab = opt_tensors(ch.w32, ch.w, ch.m, ch.v, ch.dw) if fused else ch.opt_tensors
             self._opt = dict(tab=tab, fmt=GRAD_F16_SCALED if fused else GRAD_F32,
                              inv=self._inv_scale if fused else ctypes.c_float(1.0),
-                             gb=2 if fused else 4, h="true" if fused else "false",
-                             fused=fused, n=sum(w.numel() for w in ch.w32))
+                             gb=2 if fused else 4, fused=fused,
+                             n=sum(w.numel() for w in ch.w32))
+            # the kernels' template arguments: gradient form, and non-temporal
+            # access for updates that read more than the Infinity Cache holds
+            args = (fused, self._opt["n"] * (OPT_READ_BYTES + self._opt["gb"]) > 256 << 20)
+            self._opt["args"] = ", ".join(str(a).lower() for a in args)
             self._keep.append(tab)
         last_dw = {}
 
@@ -578,7 +582,7 @@ class StepProgram:
                     ((self._apply[1],) if nl > 1 else ())
                 n_i = ch.w32[i].numel()
                 calls.append(Call(f"{ch.layers[i].name}.apply",
-                                  f"lars_adam_apply_kernel<{o['h']}>",
+                                  f"lars_adam_apply_kernel<{o['args']}>",
                                   (OPT_READ_BYTES + o["gb"] + OPT_WRITE_BYTES) * n_i,
                                   L_.lars_adam_apply,
                                   (o["tab"], nl, i, 1, ctypes.byref(self.params), o["fmt"],
@@ -618,7 +622,7 @@ class StepProgram:
         assert mem == list(range(first, first + count)), "a group is a layer range"
         o = self._opt
         n = sum(ch.w32[i].numel() for i in mem)
-        return [Call(f"G{gi}.norms", f"lars_adam_norms_kernel<{o['h']}>",
+        return [Call(f"G{gi}.norms", f"lars_adam_norms_kernel<{o['args']}>",
                      (OPT_READ_BYTES + o["gb"]) * n, L_.lars_adam_norms,
                      (o["tab"], len(ch.layers), first, count, ctypes.byref(self.params),
                       o["fmt"], o["inv"], ch.step_count.data_ptr(), ch.opt_ws.data_ptr(),

@@ -175,3 +175,54 @@ def test_apply_needs_norms_of_every_layer():
     assert d.host()[4] == 1
     with pytest.raises(fg.FgError):      # consumed by the apply
         fg.lars_adam_apply(d.tens, 1e-3, None, d.step, d.ws, **HP)
+
+
+@pytest.mark.parametrize("grad", ["fp32", "fp16"])
+def test_update_beyond_the_cache_keeps_the_bits(grad):
+    """A layer's update does not depend on the others: with a layer added that
+    takes the arrays past the Infinity Cache (256 MiB of reads, where the
+    accesses become non-temporal), the small layers keep every bit; the large
+    layer's first moments and fp16 copies follow the update rule."""
+    big = (256 << 20) // (16 if grad == "fp32" else 14) + 1
+    w, m, v, g = _state(10)
+    if grad == "fp16":
+        g = [(x * 2.0 ** 10).astype(np.float16) for x in g]
+    inv = 2.0 ** -10 if grad == "fp16" else 1.0
+    fmt = fg.GRAD_F16_SCALED if grad == "fp16" else fg.GRAD_F32
+    outs = []
+    for extra in (0, big):
+        d = Dev(w, m, v, [x.astype(np.float32) for x in g], step=6)
+        ts = [list(x) for x in (d.w32, d.w16, d.m, d.v,
+                                [torch.from_numpy(x.copy()).cuda() for x in g])]
+        if extra:
+            gen = torch.Generator(device="cuda").manual_seed(3)
+            one = lambda s: torch.randn(extra, device="cuda", generator=gen) * s
+            for t, x in zip(ts, (one(0.05), torch.empty(extra, dtype=torch.float16,
+                                                        device="cuda"),
+                                 one(1e-4), one(1e-4).square_(),
+                                 one(1e-3 / inv).to(ts[4][0].dtype))):
+                t.append(x)
+            before = [t[-1][:4096].cpu().numpy() for t in ts]
+        tens = fg.opt_tensors(*ts)
+        ws = torch.empty(fg.lars_adam_workspace_bytes(tens), dtype=torch.uint8, device="cuda")
+        n = len(ts[0])
+        fg.lars_adam_norms(tens, 0, n, d.step, ws, fmt, inv, **HP)
+        fg.lars_adam_apply(tens, 2e-3, None, d.step, ws, fmt, inv, **HP)
+        torch.cuda.synchronize()
+        outs.append(d.host())
+    assert _bits_equal(outs[0], outs[1])
+    w1, m1, v1, h1, _ = outs[1]
+    for i in range(len(SIZES)):
+        gi = g[i].astype(np.float32) * np.float32(inv)
+        check_opt_layer(w[i], m[i], v[i], gi, 7, 2e-3, w1[i], m1[i], v1[i], h1[i])
+    # the large layer's moments and fp16 copy (its tau is a sum over all of it)
+    w0, _, m0, v0, g0 = before
+    gt = g0.astype(np.float32) * np.float32(inv)
+    gt = gt.astype(np.float64) + np.float32(HP["weight_decay"]).astype(np.float64) * w0
+    b1, b2 = (float(np.float32(HP[k])) for k in ("beta1", "beta2"))
+    mb, vb = b1 * m0 + (1 - b1) * gt, b2 * v0 + (1 - b2) * gt * gt
+    got = [t[-1][:4096].cpu().numpy() for t in ts]
+    # a few fp32 roundings of each term, which may cancel
+    assert np.all(np.abs(got[2] - mb) <= 2.0 ** -21 * (np.abs(m0) + np.abs(gt)))
+    assert np.all(np.abs(got[3] - vb) <= 2.0 ** -21 * (v0 + gt * gt))
+    assert np.array_equal(got[1].view(np.uint16), got[0].astype(np.float16).view(np.uint16))
