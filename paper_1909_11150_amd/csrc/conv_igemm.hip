@@ -934,31 +934,6 @@ static DataPlan make_data_plan(const DataConvArgs &a) {
       }
     }
   }
-  if (!fixed && lds) {
-    // One corner stays on the input-reuse kernel so that the random-shape sweep
-    // still runs it there: 256 channels, 32 to 48 tiles of whole rows, a long
-    // reduction (256 x 4608 over 9984 positions 47.5 us, 40.7 on 128 x 128 tiles).
-    if (pl.tile == DataTile::k128 && a.co == 256 && halo) {
-      const DataWork w = data_work(a, 256, 256, 32);
-      if (w.tiles >= 32 && w.tiles <= 48 && w.longest >= 128) {
-        pl.tile = DataTile::k256;
-        pl.nsplit = 4;
-      }
-    }
-  }
-  // Two ranges keep the split they always had, which the tests of the split
-  // kernels' range edges hold them to, though the estimate is right that it no
-  // longer pays: strided input gradients with fewer than two 64 x 64 workgroups
-  // per CU (1024 x 2048 over 1023 positions 15.3 unsplit, 16.1 us), and 16 such
-  // tiles or fewer whose stages straddle taps, 7 and more of them (40 x 432 over
-  // 220 positions 6.2 unsplit, 9.2 us).
-  if (pl.tile == DataTile::k64 && pl.nsplit == 1) {
-    const DataWork w = data_work(a, 64, 64, 64);
-    const bool uneven = a.nphase > 1 && w.longest * w.tiles != w.stages;
-    if ((uneven && w.tiles < 2 * kCUs && w.longest >= 32) ||
-        (a.cr % 32 != 0 && w.tiles <= 16 && w.longest >= 7))
-      pl.nsplit = fixed ? so.nchunk : 2;
-  }
   pl.nchunk = fixed ? so.nchunk : pl.nsplit;
   // the kernels' own stages where the order is free
   pl.unit = fixed ? unit : pl.tile == DataTile::k256 ? 32 : 64;

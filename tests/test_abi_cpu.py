@@ -154,6 +154,20 @@ def test_small_tile_plans_keep_one_workgroup_per_cu(L):
         "data_conv_dma_kernel<true")
 
 
+def test_plans_follow_the_estimate(L):
+    """Shapes that were planned apart from the time estimate take the plan it
+    finds cheapest: one 128 x 128 launch instead of the input-reuse kernel in
+    four splits (40.7 us against 47.5), and one launch of small tiles instead
+    of two parts and a second launch (15.3 against 16.1, 6.2 against 9.2)."""
+    reuse = fg.ConvDesc.make(1, 78, 128, 256, 512, 3, 3, 1, 1)
+    assert "halo" not in fg.kernel_name(reuse, fg.OP_BWD_DATA)
+    for shape, op in (((1, 33, 31, 1024, 512, 3, 3, 2, 1), fg.OP_BWD_DATA),
+                      ((2, 20, 21, 48, 40, 3, 3, 2, 1), fg.OP_FWD),
+                      ((2, 20, 21, 40, 48, 3, 3, 1, 1), fg.OP_BWD_DATA)):
+        d = fg.ConvDesc.make(*shape)
+        assert L.fg_conv_workspace_bytes(ctypes.byref(d), op) == 0, shape
+
+
 def test_kernel_gradients_without_big_tiles_split_widely(L):
     """A kernel gradient whose R*S*C or K is below 256 has only 128x128
     tiles, and few of them: it may split its reduction beyond 16 ways to

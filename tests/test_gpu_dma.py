@@ -32,7 +32,8 @@ CASES = [
     ((8, 64, 64, 64, 128, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, false>"),
     ((1, 31, 33, 512, 768, 3, 2, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, true>"),
     ((4, 64, 64, 256, 128, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
-    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, true>"),
+    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
+    ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, true>"),
 ]
 
 

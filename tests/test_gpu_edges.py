@@ -47,6 +47,8 @@ CASES = [
     ((2, 64, 64, 16, 16, 3, 1, 1), FWD,
      "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>"),
     ((2, 20, 21, 48, 40, 3, 2, 1), FWD,
+     "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>"),
+    ((1, 8, 7, 104, 16, 3, 1, 1), FWD,
      "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, true>"),
     ((4, 128, 128, 264, 512, 3, 1, 1), FWD,
      "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, false>"),
@@ -55,12 +57,15 @@ CASES = [
     ((1, 127, 129, 512, 256, 3, 2, 1), DX, "data_conv_dma_kernel<false, false>"),
     ((1, 77, 79, 512, 512, 3, 1, 1), DX, "data_conv_dma_kernel<false, true>"),
     ((4, 64, 64, 256, 128, 3, 1, 1), DX, "data_conv_dma_kernel<128, false, false>"),
-    ((1, 33, 31, 1024, 512, 3, 2, 1), DX, "data_conv_dma_kernel<128, false, true>"),
+    ((1, 33, 31, 1024, 512, 3, 2, 1), DX, "data_conv_dma_kernel<128, false, false>"),
+    ((1, 15, 6, 8, 96, 3, 1, 1), DX, "data_conv_dma_kernel<128, false, true>"),
     ((2, 128, 128, 512, 320, 3, 1, 1), DX, "data_conv_halo_kernel<false, false>"),
     ((1, 64, 64, 1024, 1024, 3, 1, 1), DX, "data_conv_halo_kernel<false, true>"),
     ((2, 20, 21, 48, 40, 3, 2, 1), DX,
      "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>"),
     ((2, 20, 21, 40, 48, 3, 1, 1), DX,
+     "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>"),
+    ((1, 5, 5, 16, 88, 3, 1, 1), DX,
      "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, true>"),
     ((4, 128, 128, 512, 264, 3, 1, 1), DX,
      "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, false>"),

@@ -39,7 +39,7 @@ def _out(h, pad, r, stride):
     return (h + 2 * pad - r) // stride + 1
 
 
-def draw_cases(seed=20191125, n_small=90, n_large=30, n_layer=30):
+def draw_cases(seed=20191125, n_small=90, n_large=30, n_layer=42):
     """(op, (n, h, w, c, k, r, s, stride, pad)) cases, all of which the
     library accepts: c, k multiples of 8, r*s <= 16, output at least 1x1,
     input-gradient strides at most 2. Three groups: small shapes of any kind,
