@@ -49,12 +49,16 @@
  *                        being the output itself, an unknown enum value;
  *       FG_EUNSUPPORTED  a valid shape outside what the kernels implement
  *                        (listed per call);
- *       FG_EWORKSPACE    ws_bytes below fg_conv_workspace_bytes();
+ *       FG_EWORKSPACE    ws_bytes below fg_conv_workspace_bytes() (for the
+ *                        two gradients, below the shape's least size, see
+ *                        there);
  *       FG_ELAUNCH       the HIP runtime rejected a launch.
  *     No exception crosses the interface. On any error nothing is launched
  *     (FG_ELAUNCH: kernels launched before the failing one stay queued).
  *   - Results are bit-reproducible for a fixed device, shape and input:
- *     every sum is evaluated in a fixed order (no floating-point atomics).
+ *     every sum is evaluated in a fixed order (no floating-point atomics). A
+ *     gradient given less workspace than fg_conv_workspace_bytes() has an
+ *     order of its own, also fixed.
  *   - Tensor sizes must stay below 2^31 elements per tensor.
  */
 #ifndef FCNGRAD_H
@@ -341,7 +345,13 @@ fg_status fg_mfma_loop(float *out, int32_t blocks, int32_t iters, int32_t operan
  * Either may be null (disarms). The caller owns the events. */
 fg_status fg_profile_next_launch(hipEvent_t start, hipEvent_t stop);
 
-/* Workspace in bytes that the given pass needs for this shape (0 if none). */
+/* Workspace in bytes that the given pass needs for this shape (0 if none).
+ * conv2d_bwd_data and conv2d_bwd_weight[_checked] also accept less, down to a
+ * least size per shape (often the same, possibly 0): they then split the
+ * reduction into the fewer, longer parts that fit the least size, which takes
+ * longer and adds in another order. The least size is what this query returned
+ * before the kernels took more parts, so a program that kept that size works
+ * on; programs that ask need not know it. */
 size_t fg_conv_workspace_bytes(const fg_conv_desc *d, int op);
 
 /* ---- optimizer (Section 6.2: layer-wise adaptive rates with Adam) ------ */

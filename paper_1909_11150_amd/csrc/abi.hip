@@ -289,6 +289,16 @@ fg_status check_ws(const fg_conv_desc *d, int op, void *ws, size_t ws_bytes,
                        n1, p2, n2, p3, n3);
 }
 
+// Bound on the split partials that the plan of a gradient call keeps to, given what
+// the plan without a bound needs, the least the call accepts and what it brings:
+// none, or exactly that least, so that a shape has two plans and no more. (The
+// least is what the query gave before the kernels took more splits; a program that
+// kept that size need not ask again.)
+size_t plan_bound(size_t need, size_t least, const void *ws, size_t ws_bytes) {
+  const size_t has = ws ? ws_bytes : 0;
+  return has < need && has >= least ? least : SIZE_MAX;
+}
+
 // ---- the no-allocation kernel gradient's scratch ---------------------------
 // fp32 split partials of conv2d_bwd_weight_noalloc. Each GPU the library runs
 // on holds its own copy until the process ends. In host code the array's name
@@ -469,17 +479,22 @@ fg_status conv2d_bwd_data(const fg_conv_desc *d, const uint16_t *dy,
     return launch_status(launch_head_bwd_data(
         dy, w_krsc, dx, (int64_t)d->n * d->h * d->w, d->c, epi, gate, stream));
   }
-  if ((st = check_ws(d, FG_OP_BWD_DATA, ws, ws_bytes, dy, ny * 2, w_krsc, nw * 2,
-                     dx, sx, gate, sx)) != FG_OK)
-    return st;
   DataConvArgs a = bwd_data_args(d, P, Q);
+  size_t cap = SIZE_MAX, need = plan_data_conv(a).ws_bytes;
+  if (need && (!ws || ws_bytes < need)) {
+    cap = plan_bound(need, data_least_ws_bytes(a), ws, ws_bytes);
+    need = plan_data_conv(a, cap).ws_bytes;
+  }
+  if ((st = check_ws_need(need, ws, ws_bytes, dy, ny * 2, w_krsc, nw * 2, dx, sx, gate,
+                          sx)) != FG_OK)
+    return st;
   a.act = dy;
   a.wgt = w_krsc;
   a.out = dx;
   a.gate = gate;
   a.epi = epi;
   a.part = (float *)ws;
-  return launch_status(launch_data_conv(a, false, stream));
+  return launch_status(launch_data_conv(a, false, stream, cap));
 }
 
 fg_status conv_transpose2d_fwd(const fg_conv_desc *d, const uint16_t *x,
@@ -549,9 +564,13 @@ static fg_status bwd_weight(const fg_conv_desc *d, const uint16_t *x,
        overlap(found_nonfinite, 4, ws, ws_bytes)))
     return FG_EINVAL;
   if ((st = check_conv_support(d)) != FG_OK) return st;
-  const size_t plan_cap = noalloc ? (size_t)FG_NOALLOC_SCRATCH_BYTES : SIZE_MAX;
-  const size_t need = d->k == 1 ? head_wgrad_ws_bytes(*d)
-                                : plan_wgrad(*d, P, Q, plan_cap).ws_bytes;
+  size_t plan_cap = noalloc ? (size_t)FG_NOALLOC_SCRATCH_BYTES : SIZE_MAX;
+  size_t need = d->k == 1 ? head_wgrad_ws_bytes(*d)
+                          : plan_wgrad(*d, P, Q, plan_cap).ws_bytes;
+  if (!noalloc && d->k != 1 && need && (!ws || ws_bytes < need)) {
+    plan_cap = plan_bound(need, wgrad_least_ws_bytes(*d, P, Q), ws, ws_bytes);
+    need = plan_wgrad(*d, P, Q, plan_cap).ws_bytes;
+  }
   if (noalloc) {
     // the library's scratch cannot overlap the caller's buffers
     if (need > (size_t)FG_NOALLOC_SCRATCH_BYTES) return FG_EWORKSPACE;

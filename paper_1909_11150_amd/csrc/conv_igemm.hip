@@ -25,6 +25,7 @@
 // reduction dimension is strided in memory are transposed in registers on
 // their way to LDS. Each of the 4 waves owns a (BM/2) x (BN/2) block of the
 // tile and issues v_mfma_f32_32x32x16_f16 over it.
+#include <algorithm>
 #include <cstring>
 
 #include "common.h"
@@ -812,42 +813,60 @@ struct PlanMemo {
 
 }  // namespace
 
-// Summation order of a forward or transposed-forward pass, and the plan of the
-// register-staged kernels: the reduction is summed in nchunk equal parts, each
-// from zero, and the parts are added in order. An activation's last bit decides
-// ReLU gates downstream (a network's input gradient moves by 3-4% in 2-norm when
-// one layer's sums are reordered), so the order of a shape is fixed by this
-// function alone, and every kernel that takes the shape keeps it: as parts of a
-// split, or by folding its accumulators at the same places (data_tile). The
-// figures are rates of earlier kernels, whose splits these parts were; they are
-// part of the definition and need no update.
-struct SumOrder {
-  bool big;        // 256 x 256 tiles: whole-row shapes take channels before taps
-  int32_t nchunk;
+// Number of equal parts a reduction of nk stages is summed in, over 128 x 128 or
+// (big) 256 x 256 tiles, by rates of workgroups in flop/s. The rates are those of
+// earlier kernels, whose splits these parts were; they are part of what they define
+// (the order of a forward pass's sums, the least workspace of a call) and need no
+// update.
+struct PartRates {
+  double big, small, alone;              // alone: a 128 x 128 one with its CU to itself
+  double partial_bw, launch_s, round_s;  // a split's partials and launch; per round of tiles
 };
-static SumOrder sum_order(const DataConvArgs &a) {
-  const bool lds = a.cr % 32 == 0 && data_tile_ok(a);
-  const double rate_small = lds ? 0.85e12 : 1.3e12, rate_alone = lds ? 2.1e12 : 1.3e12;
-  const int64_t out = (int64_t)a.n * a.ho * a.wo * a.co, nk = data_nk_max(a);
-  SumOrder best{false, 1};
+struct PartCount {
+  bool big;
+  int32_t n;
+};
+static PartCount part_count(int64_t tiles_big, int64_t tiles_small, int64_t nk, int64_t out,
+                            bool allow_big, const PartRates &r, int max_n) {
+  PartCount best{false, 1};
   double best_t = 1e30;
   for (int big = 0; big < 2; ++big) {
-    if (big && a.co < 256) continue;
+    if (big && !allow_big) continue;
     const int t = big ? 256 : 128;
-    const int64_t tiles = data_tiles(a, t, t), slots = big ? kCUs : 2 * kCUs;
-    for (int ns = 1; ns <= 16; ++ns) {
+    const int64_t tiles = big ? tiles_big : tiles_small, slots = big ? kCUs : 2 * kCUs;
+    for (int ns = 1; ns <= max_n; ++ns) {
       if (ns > 1 && (nk + ns - 1) / ns < 4) break;
-      const double rate = big ? 3.0e12 : tiles * ns <= kCUs ? rate_alone : rate_small;
-      const int64_t waves = (tiles * ns + slots - 1) / slots;
-      double tt = waves * (2.0 * t * t * BK * (double)((nk + ns - 1) / ns) / rate);
-      if (ns > 1) tt += ns * (double)out * 8.0 / 6.0e12 + 4e-6;
+      const double rate = big ? r.big : tiles * ns <= kCUs ? r.alone : r.small;
+      const int64_t rounds = (tiles * ns + slots - 1) / slots;
+      double tt = rounds * (2.0 * t * t * BK * (double)((nk + ns - 1) / ns) / rate + r.round_s);
+      if (ns > 1) tt += ns * (double)out * 8.0 / r.partial_bw + r.launch_s;
       if (tt < best_t * 0.98) {
         best_t = tt;
-        best = SumOrder{big != 0, ns};
+        best = PartCount{big != 0, ns};
       }
     }
   }
   return best;
+}
+
+// Summation order of a forward or transposed-forward pass, and the plan of the
+// register-staged kernels: the reduction is summed in n equal parts, each
+// from zero, and the parts are added in order. An activation's last bit decides
+// ReLU gates downstream (a network's input gradient moves by 3-4% in 2-norm when
+// one layer's sums are reordered), so the order of a shape is fixed by this
+// function alone, and every kernel that takes the shape keeps it: as parts of a
+// split, or by folding its accumulators at the same places (data_tile). big: whole-
+// row shapes take channels before taps.
+static PartCount sum_order(const DataConvArgs &a) {
+  const bool lds = a.cr % 32 == 0 && data_tile_ok(a);
+  const PartRates r{3.0e12, lds ? 0.85e12 : 1.3e12, lds ? 2.1e12 : 1.3e12, 6.0e12, 4e-6, 0.0};
+  return part_count(data_tiles(a, 256, 256), data_tiles(a, 128, 128), data_nk_max(a),
+                    (int64_t)a.n * a.ho * a.wo * a.co, a.co >= 256, r, 16);
+}
+
+size_t data_least_ws_bytes(const DataConvArgs &a) {
+  const PartCount pc = sum_order(a);
+  return pc.n > 1 ? (size_t)pc.n * a.n * a.ho * a.wo * a.co * sizeof(float) : 0;
 }
 
 // Tile and split count of a data convolution, by an estimate of its time (as
@@ -884,19 +903,20 @@ constexpr double kDataReduce = 3.2;       // us: the second launch of a split
 constexpr double kDataPartialBw = 5.3e6;  // bytes/us, 8 per partial element
 constexpr int kMaxDataSplit = 16;
 
-static DataPlan make_data_plan(const DataConvArgs &a) {
+// max_ws_bytes bounds the partials of a split whose order is free.
+static DataPlan make_data_plan(const DataConvArgs &a, size_t max_ws_bytes) {
   DataPlan pl{DataTile::k64, 1, 1, 64, 0};
   const int64_t out = (int64_t)a.n * a.ho * a.wo * a.co;
   const bool lds = data_tile_ok(a), fixed = a.fixed_order;
-  const SumOrder so = fixed || !lds ? sum_order(a) : SumOrder{false, 0};
+  const PartCount so = fixed || !lds ? sum_order(a) : PartCount{false, 0};
   const bool halo = data_halo_ok(a);
   const int unit = a.cr % 32 == 0 ? 32 : 64;  // of the parts
   if (!lds) {
     pl.tile = so.big ? DataTile::kStaged256 : DataTile::kStaged128;
-    pl.nsplit = so.nchunk;
+    pl.nsplit = so.n;
   } else if (fixed && so.big && halo) {
     pl.tile = DataTile::k256;
-    pl.nsplit = so.nchunk;
+    pl.nsplit = so.n;
   } else {
     const bool mn = a.ldw == 0;
     double best = 1e30;
@@ -905,8 +925,9 @@ static DataPlan make_data_plan(const DataConvArgs &a) {
       if (c.tm == 256 && (a.co < 256 || (fixed && halo))) continue;
       const PhaseWork pw(a, c.tm, c.tn, c.bk);
       for (int ns = 1; ns <= kMaxDataSplit; ++ns) {
-        if (fixed && ns != 1 && ns != so.nchunk) continue;
-        if (fixed && ns == 1 && so.nchunk > 1 && c.tm == 256) continue;  // cannot fold
+        if (fixed && ns != 1 && ns != so.n) continue;
+        if (!fixed && ns > 1 && (size_t)ns * out * sizeof(float) > max_ws_bytes) break;
+        if (fixed && ns == 1 && so.n > 1 && c.tm == 256) continue;  // cannot fold
         const DataWork w = pw.split(ns);
         if (w.tiles == 0 || (ns > 1 && !fixed && w.longest * c.bk < 128)) break;
         if (ns > 1 && !fixed && w.tiles * (ns - 1) >= 4 * kCUs) break;  // full already
@@ -919,7 +940,7 @@ static DataPlan make_data_plan(const DataConvArgs &a) {
           shared = halo ? kHaloShared : gen ? kGen256Shared : c.shared;
         else if (gen)
           f *= kGenFactor;
-        if (fixed && ns == 1 && so.nchunk > 1) f *= kFoldFactor;
+        if (fixed && ns == 1 && so.n > 1) f *= kFoldFactor;
         const double d = c.bk / 64.0, wgs = (double)w.tiles * ns;
         const double per_cu = (double)((w.tiles * ns + kCUs - 1) / kCUs);
         double t = c.fixed +
@@ -934,24 +955,30 @@ static DataPlan make_data_plan(const DataConvArgs &a) {
       }
     }
   }
-  pl.nchunk = fixed ? so.nchunk : pl.nsplit;
+  pl.nchunk = fixed ? so.n : pl.nsplit;
   // the kernels' own stages where the order is free
   pl.unit = fixed ? unit : pl.tile == DataTile::k256 ? 32 : 64;
   pl.ws_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * out * sizeof(float) : 0;
   return pl;
 }
 
-DataPlan plan_data_conv(const DataConvArgs &a) {
-  static thread_local PlanMemo<DataConvArgs, DataPlan> memo;
-  DataConvArgs key;  // the shape alone
-  memcpy(&key, &a, sizeof(key));
-  key.act = key.wgt = key.gate = nullptr;
-  key.out = nullptr;
-  key.part = nullptr;
-  key.epi = key.nsplit = key.nchunk = key.unit = 0;
+DataPlan plan_data_conv(const DataConvArgs &a, size_t max_ws_bytes) {
+  struct Key {
+    DataConvArgs a;
+    uint64_t cap;
+  };
+  static thread_local PlanMemo<Key, DataPlan> memo;
+  Key key;  // the shape alone
+  memset(&key, 0, sizeof(key));
+  memcpy(&key.a, &a, sizeof(a));
+  key.a.act = key.a.wgt = key.a.gate = nullptr;
+  key.a.out = nullptr;
+  key.a.part = nullptr;
+  key.a.epi = key.a.nsplit = key.a.nchunk = key.a.unit = 0;
+  key.cap = max_ws_bytes;
   auto &e = memo.at(key);
   if (!e.set || memcmp(&e.key, &key, sizeof(key)) != 0) {
-    e.plan = make_data_plan(a);
+    e.plan = make_data_plan(a, max_ws_bytes);
     memcpy(&e.key, &key, sizeof(key));
     e.set = true;
   }
@@ -1001,9 +1028,10 @@ hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_km
   return hipGetLastError();
 }
 
-hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor, hipStream_t st) {
+hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor, hipStream_t st,
+                            size_t max_ws_bytes) {
   DataConvArgs a = a0;
-  const DataPlan pl = plan_data_conv(a);
+  const DataPlan pl = plan_data_conv(a, max_ws_bytes);
   a.nsplit = pl.nsplit;
   a.nchunk = pl.nchunk;
   a.unit = pl.unit;
@@ -1109,6 +1137,21 @@ static WgradPlan plan_staged(int64_t rsc, int64_t k, int64_t mtot, int max_split
   return pl;
 }
 
+// The least workspace of a kernel gradient: that of the split the earlier kernels
+// took (their rates fitted to the network's layers; up to 16 parts, or 256 where
+// the gradient has no 256 x 256 tile).
+size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q) {
+  constexpr PartRates kRates{6.35e12, 1.3e12, 1.3e12, 4.05e12, 6.3e-6, 4.2e-6};
+  const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k, mtot = (int64_t)d.n * p * q;
+  const bool big = rsc >= 256 && k >= 256;
+  auto tiles = [&](int64_t t) { return ((rsc + t - 1) / t) * ((k + t - 1) / t); };
+  const PartCount pc = part_count(tiles(256), tiles(128), (mtot + BK - 1) / BK, k * rsc, big,
+                                  kRates, big ? 16 : kMaxWgradSplit);
+  const int64_t chunk = ((mtot + pc.n - 1) / pc.n + BK - 1) / BK * BK;
+  const int64_t ns = (mtot + chunk - 1) / chunk;
+  return ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
+}
+
 static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
                                  size_t max_ws_bytes) {
   const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k;
@@ -1129,11 +1172,14 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
     for (const WgradTileCost &c : kWgradTiles) {
       if (c.t == 256 && wgrad_name(rsc, d.c, d.k) == WgName::kSmall) continue;
       const int64_t tiles = ((rsc + c.t - 1) / c.t) * ((k + c.t - 1) / c.t);
-      // no split, a few, and as many as fill the CUs 1 to 6 times
+      // no split, a few, and as many as fill the CUs 1 to 6 times (or as many as
+      // a bound on the workspace leaves: 160 x 216 outputs over 1826 positions in
+      // the 1.1 MB of 8 parts otherwise take 4)
       int64_t cand[10] = {1, 2, 3, 4};
       for (int l = 1; l <= 6; ++l) cand[3 + l] = l * kCUs / tiles;
       int64_t last = 0;
-      for (const int64_t ns : cand) {
+      for (int64_t ns : cand) {
+        if (max_ws_bytes != SIZE_MAX) ns = std::min<int64_t>(ns, max_split);
         if (ns <= last || ns > max_split || ns > nk) continue;
         last = ns;
         const int64_t st = (nk + ns - 1) / ns, wgs = tiles * ((nk + st - 1) / st);

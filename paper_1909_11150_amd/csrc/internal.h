@@ -75,7 +75,10 @@ struct DataPlan {
   int32_t nsplit, nchunk, unit;
   size_t ws_bytes;
 };
-DataPlan plan_data_conv(const DataConvArgs &a);
+// max_ws_bytes bounds the partials of an input gradient's split; the least a call
+// may bring (see plan_bound in abi.hip) is data_least_ws_bytes.
+DataPlan plan_data_conv(const DataConvArgs &a, size_t max_ws_bytes = SIZE_MAX);
+size_t data_least_ws_bytes(const DataConvArgs &a);
 
 // Bytes from the first element of act to the last one a convolution reads
 // (the span a buffer resource must cover).
@@ -120,6 +123,7 @@ struct WgradPlan {
 // ws_bytes <= max_ws_bytes (fewer splits when the best plan needs more).
 WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
                      size_t max_ws_bytes = SIZE_MAX);
+size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q);
 
 // The same span for the kernel gradient's x.
 __host__ __device__ inline size_t x_span_bytes(const WgradArgs &a) {
@@ -128,8 +132,8 @@ __host__ __device__ inline size_t x_span_bytes(const WgradArgs &a) {
 }
 size_t head_wgrad_ws_bytes(const fg_conv_desc &d);
 
-hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor,
-                            hipStream_t st);
+hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor, hipStream_t st,
+                            size_t max_ws_bytes = SIZE_MAX);
 hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
                                  hipStream_t st);
 const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor);

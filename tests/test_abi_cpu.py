@@ -154,6 +154,39 @@ def test_small_tile_plans_keep_one_workgroup_per_cu(L):
         "data_conv_dma_kernel<true")
 
 
+# (n, h, w, c, k, r, stride, pad), op, least size, size of the full plan
+LEAST_WS = [
+    ((2, 64, 64, 16, 16, 3, 1, 1), fg.OP_BWD_WEIGHT, 294912, 1179648),
+    ((1, 83, 22, 24, 160, 3, 1, 1), fg.OP_BWD_WEIGHT, 1105920, 2073600),
+    ((3, 31, 19, 64, 32, 3, 1, 1), fg.OP_BWD_WEIGHT, 516096, 2064384),
+    ((3, 55, 32, 168, 64, 3, 2, 1), fg.OP_BWD_WEIGHT, 2322432, 2709504),
+    ((1, 33, 138, 512, 224, 3, 1, 1), fg.OP_BWD_DATA, 0, 27979776),
+    ((2, 23, 15, 56, 288, 3, 1, 1), fg.OP_BWD_DATA, 1700160, 2163840),
+    ((2, 105, 9, 32, 256, 3, 2, 1), fg.OP_BWD_DATA, 967680, 1935360),
+    ((3, 9, 10, 128, 96, 3, 1, 1), fg.OP_BWD_DATA, 552960, 967680),
+]
+
+
+@pytest.mark.parametrize("shape,op,least,full", LEAST_WS, ids=str)
+def test_gradients_accept_the_least_workspace(L, shape, op, least, full):
+    """Sizes that the workspace query gave for these shapes when the kernels
+    took fewer parts are still accepted, one byte less is not. An accepted
+    workspace overlaps an operand here, so that no call gets to a launch."""
+    n, h, w, c, k, r, st, pd = shape
+    d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
+    assert L.fg_conv_workspace_bytes(ctypes.byref(d), op) == full
+    x, dy, wt = FAKE, FAKE + (1 << 28), FAKE + (1 << 30)
+    def call(ws, nbytes):
+        if op == fg.OP_BWD_WEIGHT:
+            return L.conv2d_bwd_weight(ctypes.byref(d), x, dy, wt, ws, nbytes, None)
+        return L.conv2d_bwd_data(ctypes.byref(d), dy, wt, x, 0, None, ws, nbytes, None)
+    assert call(x, full) == fg.FG_EINVAL   # large enough, but overlaps
+    if least:                              # (with none needed, the call would launch)
+        assert call(x, full - 1) == call(x, least) == fg.FG_EINVAL
+        assert call(x, least - 1) == fg.FG_EWORKSPACE
+        assert call(None, full) == fg.FG_EWORKSPACE
+
+
 def test_plans_follow_the_estimate(L):
     """Shapes that were planned apart from the time estimate take the plan it
     finds cheapest: one 128 x 128 launch instead of the input-reuse kernel in
