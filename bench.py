@@ -128,15 +128,17 @@ def short_kernel_name(name):
     name = name.replace("(anonymous namespace)::", "")
     name = name.split("(")[0].replace("void ", "")
     name = name.replace("fg::dma::", "").replace("fg::", "")
-    # the pipeline configuration: dropped, except a tile size other than 256
+    # the pipeline configuration: dropped, except a tile other than 256 x 256
+    name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, 256, 256>, ", "", name)
+    name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, (\d+), \1>, ", r"\1, ", name)
+    name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, (\d+), (\d+)>, ", r"\1x\2, ", name)
     name = re.sub(r"K<\d+, \d+, \d+, \d+(, 256)?>, ", "", name)
     return re.sub(r"K<\d+, \d+, \d+, \d+, (\d+)>, ", r"\1, ", name)
 
 
 def kernel_source(kernel):
     """Source file (under paper_1909_11150_amd/csrc) that defines `kernel`."""
-    if "_dma_kernel" in kernel or "_halo_kernel" in kernel or \
-            kernel.startswith(("wgrad_kernel", "data_conv_kernel")):
+    if any(f in kernel for f in ("_dma_kernel", "_halo_kernel", "_gen_kernel", "_fold_kernel")):
         return "conv_dma.hip"
     if kernel.startswith(("copy_pieces", "unscale", "head_grad", "relu_backward")):
         return "grad_path.hip"

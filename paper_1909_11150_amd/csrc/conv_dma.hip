@@ -46,8 +46,6 @@ using DataRun = K<FG_DMA_DATA_CFG>;
 #define FG_DMA_HALO_NS 3
 #endif
 using HaloRun = K<32, FG_DMA_HALO_NS, 2, 4>;  // weights ring; the rest is patches
-// the small tiles' family name (their own pipelines are at data_tile)
-using SmallRun = K<32, 5, 2, 2, 128>;
 
 // ---------------------------------------------------------------------------
 // Output tile store of the data convolutions. The accumulator layout gives
@@ -931,77 +929,52 @@ using Data64x128 = Pipe<64, 3, 2, 4, 64, 128>;  // 8 waves of 32 x 32
 using Data128 = Pipe<64, 2, 4, 2, 128, 128>;    // 8 waves of 32 x 64
 using Data256 = Pipe<32, 5, 2, 4, 256, 256>;    // 8 waves of 128 x 64
 
-// Overloads by tile (Gen<P>: stages that straddle taps), under the name of the
-// shape's family: data_conv_dma_kernel<K<..., 128>, ...> for reduction channels
-// that are a multiple of 32, data_conv_kernel with the largest tile the output
-// fills for the others.
-template <class P>
-struct Gen {};
-template <class T>
-struct Fold {};  // Sum::kFold where not split
-#define FG_DATA_DMA_KERNEL(P, WPE, TAG, GEN, FOLD)                                  \
-  template <class C, bool WK, bool SPLIT>                                           \
-  __global__ __launch_bounds__(P::NT, WPE) void data_conv_dma_kernel(               \
-      DataConvArgs a, TileMap tm, PosDiv pd, TAG) {                                 \
-    data_tile<P, WK, SPLIT ? Sum::kPart : FOLD, GEN>(a, tm, pd);                    \
-  }
-#define FG_DATA_GEN_KERNEL(P, WPE, TAG, FOLD)                                       \
-  template <class C, bool WK, bool FAST, bool SPLIT>                                \
-  __global__ __launch_bounds__(P::NT, WPE) void data_conv_kernel(                   \
-      DataConvArgs a, TileMap tm, PosDiv pd, TAG) {                                 \
-    data_tile<P, WK, SPLIT ? Sum::kPart : FOLD, true>(a, tm, pd);                   \
-  }
-#define FG_DATA_KERNELS(P, WPE)                                                     \
-  FG_DATA_DMA_KERNEL(P, WPE, P, false, Sum::kWhole)                                 \
-  FG_DATA_DMA_KERNEL(P, WPE, Gen<P>, true, Sum::kWhole)                             \
-  FG_DATA_DMA_KERNEL(P, WPE, Fold<P>, false, Sum::kFold)                            \
-  FG_DATA_DMA_KERNEL(P, WPE, Fold<Gen<P>>, true, Sum::kFold)                        \
-  FG_DATA_GEN_KERNEL(P, WPE, Gen<P>, Sum::kWhole)                                   \
-  FG_DATA_GEN_KERNEL(P, WPE, Fold<Gen<P>>, Sum::kFold)
-FG_DATA_KERNELS(Data64, 3)
-FG_DATA_KERNELS(Data64x128, 4)
-FG_DATA_KERNELS(Data128, 4)
-FG_DATA_GEN_KERNEL(Data256, 2, Gen<Data256>, Sum::kWhole)
-#undef FG_DATA_KERNELS
-#undef FG_DATA_DMA_KERNEL
-#undef FG_DATA_GEN_KERNEL
+// The kernels by what a stage and a sum are: whole taps per stage (overloading the
+// 256 x 256 tiles' kernel above), stages that straddle taps, and sums folded in
+// parts (either kind of stage).
+template <class P, bool WK, bool SPLIT>
+__global__ __launch_bounds__(P::NT, P::WPE) void data_conv_dma_kernel(DataConvArgs a, TileMap tm,
+                                                                      PosDiv pd) {
+  data_tile<P, WK, SPLIT ? Sum::kPart : Sum::kWhole, false>(a, tm, pd);
+}
+template <class P, bool WK, bool SPLIT>
+__global__ __launch_bounds__(P::NT, P::WPE) void data_conv_gen_kernel(DataConvArgs a, TileMap tm,
+                                                                      PosDiv pd) {
+  data_tile<P, WK, SPLIT ? Sum::kPart : Sum::kWhole, true>(a, tm, pd);
+}
+template <class P, bool WK, bool GEN>
+__global__ __launch_bounds__(P::NT, P::WPE) void data_conv_fold_kernel(DataConvArgs a, TileMap tm,
+                                                                       PosDiv pd) {
+  data_tile<P, WK, Sum::kFold, GEN>(a, tm, pd);
+}
+using DataTileKernel = void (*)(DataConvArgs, TileMap, PosDiv);
 
-template <class P, class TAG, bool LARGE>
-static auto data_kernel(const DataConvArgs &a, bool w_kmajor) {
-  using Kernel = void (*)(DataConvArgs, TileMap, PosDiv, TAG);
-  using D = std::conditional_t<LARGE, DataRun, SmallRun>;
-  using C = std::conditional_t<LARGE, Cfg<256, 256, 2, 4>, Cfg<128, 128, 2, 2>>;
-  const int i = 2 * w_kmajor + (a.nsplit > 1);
-  if constexpr (std::is_same_v<TAG, Gen<P>> || std::is_same_v<TAG, Fold<Gen<P>>>)
-    if (a.cr % 32 != 0) {
-      const Kernel k[4] = {
-          data_conv_kernel<C, false, false, false>, data_conv_kernel<C, false, false, true>,
-          data_conv_kernel<C, true, false, false>, data_conv_kernel<C, true, false, true>};
-      return k[i];
-    }
-  if constexpr (P::TM != 256) {  // the larger tiles have whole-tap kernels
-    const Kernel k[4] = {
-        data_conv_dma_kernel<D, false, false>, data_conv_dma_kernel<D, false, true>,
-        data_conv_dma_kernel<D, true, false>, data_conv_dma_kernel<D, true, true>};
-    return k[i];
-  }
-  return (Kernel) nullptr;
+template <class P, bool WK>
+static DataTileKernel data_tile_kernel(bool split, bool gen, bool fold) {
+  if constexpr (P::TM == 256)  // whole taps: the kernel above; it cannot fold
+    return split ? data_conv_gen_kernel<P, WK, true> : data_conv_gen_kernel<P, WK, false>;
+  else if (fold)
+    return gen ? data_conv_fold_kernel<P, WK, true> : data_conv_fold_kernel<P, WK, false>;
+  else if (gen)
+    return split ? data_conv_gen_kernel<P, WK, true> : data_conv_gen_kernel<P, WK, false>;
+  return split ? static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, true>)
+               : static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, false>);
 }
 
-template <class P, class TAG>
-static hipError_t launch_data_tile(const DataConvArgs &a0, DataTile tile, bool w_kmajor,
+template <class P>
+static hipError_t launch_data_tile(const DataConvArgs &a0, bool w_kmajor, bool gen, bool fold,
                                    hipStream_t st) {
-  const auto k = data_conv_large(a0, tile) ? data_kernel<P, TAG, true>(a0, w_kmajor)
-                                           : data_kernel<P, TAG, false>(a0, w_kmajor);
-  if (!k) return hipErrorInvalidValue;
   DataConvArgs a = a0;
+  const bool split = a.nsplit > 1;
+  const DataTileKernel k = w_kmajor ? data_tile_kernel<P, true>(split, gen, fold)
+                                    : data_tile_kernel<P, false>(split, gen, fold);
   const TileMap tm = data_tile_map(a, P::TM, P::TN);
   PosDiv pd;
   for (int i = 0; i < 4; ++i) {
     pd.mw[i] = make_fastdiv((uint32_t)std::max(a.ph[i].mw, 1));
     pd.mh[i] = make_fastdiv((uint32_t)std::max(a.ph[i].mh, 1));
   }
-  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, tm, pd, TAG{});
+  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, tm, pd);
   return hipGetLastError();
 }
 
@@ -1242,47 +1215,20 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs a, const WgradDiv fd,
   }
 }
 
-// The kernels, one overload per tile (the last argument's type). Two names:
-// wgrad_dma_kernel for channel counts that are multiples of 256, wgrad_kernel
-// for the others, with the largest tile their row and column counts fill.
-// WPE: waves per SIMD (workgroups per CU that the ring leaves room for).
-#define FG_WGRAD_KERNELS(P, WPE)                                                  \
-  template <bool SPLIT>                                                           \
-  __global__ __launch_bounds__(P::NT, WPE) void wgrad_dma_kernel(                 \
-      WgradArgs a, WgradDiv fd, TileMap tm, P) {                                  \
-    wgrad_tile<P, SPLIT>(a, fd, tm);                                              \
-  }                                                                               \
-  template <class C, bool SPLIT>                                                  \
-  __global__ __launch_bounds__(P::NT, WPE) void wgrad_kernel(                     \
-      WgradArgs a, WgradDiv fd, TileMap tm, P) {                                  \
-    wgrad_tile<P, SPLIT>(a, fd, tm);                                              \
-  }
-FG_WGRAD_KERNELS(Tile256, 2)
-FG_WGRAD_KERNELS(Tile128, 2)
-FG_WGRAD_KERNELS(Tile64, 3)
-#undef FG_WGRAD_KERNELS
+template <class P, bool SPLIT>
+__global__ __launch_bounds__(P::NT, P::WPE) void wgrad_dma_kernel(WgradArgs a, WgradDiv fd,
+                                                                  TileMap tm) {
+  wgrad_tile<P, SPLIT>(a, fd, tm);
+}
 
 template <class P>
-static hipError_t launch_tile(const WgradArgs &a, WgName name, hipStream_t st) {
-  using Kernel = void (*)(WgradArgs, WgradDiv, TileMap, P);
-  using Big = Cfg<256, 256, 2, 4>;
-  using Small = Cfg<128, 128, 2, 2>;
-  const bool s = a.nsplit > 1;
-  const Kernel k =
-      name == WgName::kDma
-          ? (s ? (Kernel)wgrad_dma_kernel<true> : (Kernel)wgrad_dma_kernel<false>)
-      : name == WgName::kBig
-          ? (s ? (Kernel)wgrad_kernel<Big, true> : (Kernel)wgrad_kernel<Big, false>)
-      : P::TM == 256
-          ? nullptr  // not planned for fewer than 256 rows or columns
-          : (s ? (Kernel)wgrad_kernel<std::conditional_t<P::TM == 256, Big, Small>, true>
-               : (Kernel)wgrad_kernel<std::conditional_t<P::TM == 256, Big, Small>, false>);
-  if (!k) return hipErrorInvalidValue;
+static hipError_t launch_tile(const WgradArgs &a, hipStream_t st) {
   const WgradDiv fd{make_fastdiv((uint32_t)(a.p * a.q)), make_fastdiv((uint32_t)a.q)};
   TileMap tm{(a.r * a.s * a.c + P::TM - 1) / P::TM, (a.k + P::TN - 1) / P::TN, a.nsplit, 0,
              kOutputMajor};
   tm.per = (tm.n0 * tm.n1 * tm.n2 + 7) / 8;
-  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, fd, tm, P{});
+  const auto k = a.nsplit > 1 ? wgrad_dma_kernel<P, true> : wgrad_dma_kernel<P, false>;
+  hipLaunchKernelGGL(k, dim3(8 * tm.per), dim3(P::NT), 0, st, a, fd, tm);
   return hipGetLastError();
 }
 
@@ -1358,37 +1304,29 @@ bool data_tile_ok(const DataConvArgs &a) {
   return act_span_bytes(a) < 0x7FFFFFFFull && (size_t)a.wbytes < 0x7FFFFFFFull;
 }
 
-template <class P>
-static hipError_t launch_data_tile_any(const DataConvArgs &a, DataTile tile, bool w_kmajor,
-                                       hipStream_t st) {
-  using dma::Fold;
-  using dma::Gen;
-  const bool fold = a.nsplit == 1 && a.nchunk > 1;
-  bool gen = a.cr % P::BK != 0;
+DataTileMode data_tile_mode(const DataConvArgs &a, DataTile tile) {
+  const int bk = tile == DataTile::k256 ? dma::Data256::BK : dma::Data64::BK;
+  static_assert(dma::Data64::BK == dma::Data64x128::BK && dma::Data64::BK == dma::Data128::BK);
+  bool gen = a.cr % bk != 0;
   for (int i = 0; a.nsplit > 1 && i < a.nphase; ++i)  // parts that end within a stage
-    gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, a.unit, a.nchunk) % P::BK != 0;
-  return fold ? (gen ? dma::launch_data_tile<P, Fold<Gen<P>>>(a, tile, w_kmajor, st)
-                     : dma::launch_data_tile<P, Fold<P>>(a, tile, w_kmajor, st))
-              : (gen ? dma::launch_data_tile<P, Gen<P>>(a, tile, w_kmajor, st)
-                     : dma::launch_data_tile<P, P>(a, tile, w_kmajor, st));
+    gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, a.unit, a.nchunk) % bk != 0;
+  return {gen, a.nsplit == 1 && a.nchunk > 1};
 }
 
 hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_kmajor,
                                  hipStream_t st) {
-  using dma::Gen;
-  const bool whole = a.cr % 32 == 0;  // a 32-deep stage lies in one tap
+  const auto [gen, fold] = data_tile_mode(a, tile);
   switch (tile) {
     case DataTile::k64:
-      return launch_data_tile_any<dma::Data64>(a, tile, w_kmajor, st);
+      return dma::launch_data_tile<dma::Data64>(a, w_kmajor, gen, fold, st);
     case DataTile::k64x128:
-      return launch_data_tile_any<dma::Data64x128>(a, tile, w_kmajor, st);
+      return dma::launch_data_tile<dma::Data64x128>(a, w_kmajor, gen, fold, st);
     case DataTile::k128:
-      return launch_data_tile_any<dma::Data128>(a, tile, w_kmajor, st);
+      return dma::launch_data_tile<dma::Data128>(a, w_kmajor, gen, fold, st);
     case DataTile::k256:
       return data_halo_ok(a) ? launch_data_conv_halo(a, w_kmajor, st)
-             : whole         ? launch_data_conv_dma(a, w_kmajor, st)
-                             : dma::launch_data_tile<dma::Data256, Gen<dma::Data256>>(
-                                   a, tile, w_kmajor, st);
+             : gen           ? dma::launch_data_tile<dma::Data256>(a, w_kmajor, true, false, st)
+                             : launch_data_conv_dma(a, w_kmajor, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1398,10 +1336,9 @@ bool wgrad_tile_ok(const WgradArgs &a) {
 }
 
 hipError_t launch_wgrad_tile(const WgradArgs &a, WgTile tile, hipStream_t st) {
-  const WgName name = wgrad_name(a.r * a.s * a.c, a.c, a.k);
-  return tile == WgTile::k256   ? dma::launch_tile<dma::Tile256>(a, name, st)
-         : tile == WgTile::k128 ? dma::launch_tile<dma::Tile128>(a, name, st)
-                                : dma::launch_tile<dma::Tile64>(a, name, st);
+  return tile == WgTile::k256   ? dma::launch_tile<dma::Tile256>(a, st)
+         : tile == WgTile::k128 ? dma::launch_tile<dma::Tile128>(a, st)
+                                : dma::launch_tile<dma::Tile64>(a, st);
 }
 
 }  // namespace fg

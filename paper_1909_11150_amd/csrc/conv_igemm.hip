@@ -1012,8 +1012,8 @@ static hipError_t launch_dc_tile(const DataConvArgs &a, bool w_kmajor,
               : launch_dc<C, false, false>(a, st);
 }
 
-hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
-                                 hipStream_t st) {
+static hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
+                                        hipStream_t st) {
   hipError_t e = prof_begin(st);
   if (e != hipSuccess) return e;
   e = tile == DataTile::kStaged256   ? launch_dc_tile<BigCfg>(a, w_kmajor, st)
@@ -1028,76 +1028,73 @@ hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_km
   return hipGetLastError();
 }
 
-hipError_t launch_data_conv(const DataConvArgs &a0, bool w_kmajor, hipStream_t st,
-                            size_t max_ws_bytes) {
+// The call's arguments with the plan's split filled in.
+static DataConvArgs planned(const DataConvArgs &a0, const DataPlan &pl) {
   DataConvArgs a = a0;
-  const DataPlan pl = plan_data_conv(a, max_ws_bytes);
   a.nsplit = pl.nsplit;
   a.nchunk = pl.nchunk;
   a.unit = pl.unit;
-  return launch_data_conv_plan(a, pl.tile, w_kmajor, st);
+  return a;
 }
 
-// The smaller tiles run under the name of the 256 x 256 ones where the output
-// is large (96 tiles of 256 x 256 and more, or fewer with a long reduction),
-// else under that of the 128 x 128 ones.
-bool data_conv_large(const DataConvArgs &a, DataTile tile) {
-  if (tile == DataTile::k256) return true;
-  const DataWork w = data_work(a, 256, 256, 32);
-  return a.co >= 256 && (w.tiles >= 96 || (a.nphase == 1 && w.stages >= 6000));
+hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor, hipStream_t st,
+                            size_t max_ws_bytes) {
+  const DataPlan pl = plan_data_conv(a, max_ws_bytes);
+  return launch_data_conv_plan(planned(a, pl), pl.tile, w_kmajor, st);
 }
 
-const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor) {
-  const DataPlan pl = plan_data_conv(a);
-  const bool split = pl.nsplit > 1, big = data_conv_large(a, pl.tile);
-  // as a kernel trace prints them: [w_kmajor][split], then [big] or [fast]
-  static const char *halo[2][2] = {
-      {"data_conv_halo_kernel<false, false>", "data_conv_halo_kernel<false, true>"},
-      {"data_conv_halo_kernel<true, false>", "data_conv_halo_kernel<true, true>"}};
-  static const char *dma[2][2][2] = {
-      {{"data_conv_dma_kernel<128, false, false>", "data_conv_dma_kernel<false, false>"},
-       {"data_conv_dma_kernel<128, false, true>", "data_conv_dma_kernel<false, true>"}},
-      {{"data_conv_dma_kernel<128, true, false>", "data_conv_dma_kernel<true, false>"},
-       {"data_conv_dma_kernel<128, true, true>", "data_conv_dma_kernel<true, true>"}}};
-  static const char *gen[2][2][2] = {
-      {{"data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>",
-        "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, false>"},
-       {"data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, true>",
-        "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, true>"}},
-      {{"data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>",
-        "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, false>"},
-       {"data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, true>",
-        "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, true>"}}};
-  // the register-staged ones by tile and weight layout only
-  static const char *staged[2][2] = {
-      {"data_conv_staged_kernel<Cfg<128, 128, 2, 2>, false>",
-       "data_conv_staged_kernel<Cfg<256, 256, 2, 4>, false>"},
-      {"data_conv_staged_kernel<Cfg<128, 128, 2, 2>, true>",
-       "data_conv_staged_kernel<Cfg<256, 256, 2, 4>, true>"}};
+// Kernel names as a kernel trace prints them, without namespaces, and with a
+// pipeline's configuration (Pipe<...>, K<...>) as its tile: nothing for 256 x 256,
+// T for a square, TMxTN else. F2: by two truth values, F3: by three.
+#define F2(K, T)                                  \
+  {                                               \
+    {K "<" T "false, false>", K "<" T "false, true>"}, \
+        {K "<" T "true, false>", K "<" T "true, true>"} \
+  }
+#define F3(K, T) \
+  { F2(K, T "false, "), F2(K, T "true, ") }
+
+const char *data_conv_kernel_name(const DataConvArgs &a0, bool w_kmajor) {
+  static const char *halo[2][2] = F2("data_conv_halo_kernel", "");  // weights, split
+  static const char *dma[4][2][2] = {  // by DataTile, then the same
+      F2("data_conv_dma_kernel", ""), F2("data_conv_dma_kernel", "128, "),
+      F2("data_conv_dma_kernel", "64x128, "), F2("data_conv_dma_kernel", "64, ")};
+  static const char *gen[4][2][2] = {
+      F2("data_conv_gen_kernel", ""), F2("data_conv_gen_kernel", "128, "),
+      F2("data_conv_gen_kernel", "64x128, "), F2("data_conv_gen_kernel", "64, ")};
+  static const char *fold[4][2][2] = {  // weights, stages across taps
+      {{"", ""}, {"", ""}}, F2("data_conv_fold_kernel", "128, "),
+      F2("data_conv_fold_kernel", "64x128, "), F2("data_conv_fold_kernel", "64, ")};
+  static const char *staged[2][2][2][2] = {  // weights, whole taps per slice, split
+      F3("data_conv_staged_kernel", "Cfg<128, 128, 2, 2>, "),
+      F3("data_conv_staged_kernel", "Cfg<256, 256, 2, 4>, ")};
+  const DataPlan pl = plan_data_conv(a0);
+  const DataConvArgs a = planned(a0, pl);
+  const bool split = pl.nsplit > 1;
   if (pl.tile == DataTile::kStaged128 || pl.tile == DataTile::kStaged256)
-    return staged[w_kmajor][pl.tile == DataTile::kStaged256];
+    return staged[pl.tile == DataTile::kStaged256][w_kmajor][a.cr % BK == 0][split];
   if (pl.tile == DataTile::k256 && data_halo_ok(a)) return halo[w_kmajor][split];
-  return (a.cr % 32 == 0 ? dma : gen)[w_kmajor][split][big];
+  const DataTileMode m = data_tile_mode(a, pl.tile);
+  return m.fold ? fold[(int)pl.tile][w_kmajor][m.gen]
+                : (m.gen ? gen : dma)[(int)pl.tile][w_kmajor][split];
 }
 
 const char *wgrad_kernel_name(const fg_conv_desc &d) {
   int32_t p = (d.h + 2 * d.pad_h - d.r) / d.stride_h + 1;
   int32_t q = (d.w + 2 * d.pad_w - d.s) / d.stride_w + 1;
-  const WgradPlan pl = plan_wgrad(d, p, q);
-  const int split = pl.nsplit > 1;
-  static const char *staged[2][2] = {
-      {"wgrad_staged_kernel<Cfg<128, 128, 2, 2>, false>",
-       "wgrad_staged_kernel<Cfg<128, 128, 2, 2>, true>"},
-      {"wgrad_staged_kernel<Cfg<256, 256, 2, 4>, false>",
-       "wgrad_staged_kernel<Cfg<256, 256, 2, 4>, true>"}};
-  if (pl.tile == WgTile::kStaged256 || pl.tile == WgTile::kStaged128)
-    return staged[pl.tile == WgTile::kStaged256][split];
-  static const char *names[3][2] = {  // by WgName
+  static const char *names[5][2] = {  // by WgTile, split
       {"wgrad_dma_kernel<false>", "wgrad_dma_kernel<true>"},
-      {"wgrad_kernel<Cfg<256, 256, 2, 4>, false>", "wgrad_kernel<Cfg<256, 256, 2, 4>, true>"},
-      {"wgrad_kernel<Cfg<128, 128, 2, 2>, false>", "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"}};
-  return names[(int)wgrad_name((int64_t)d.r * d.s * d.c, d.c, d.k)][split];
+      {"wgrad_dma_kernel<128, false>", "wgrad_dma_kernel<128, true>"},
+      {"wgrad_dma_kernel<64, false>", "wgrad_dma_kernel<64, true>"},
+      {"wgrad_staged_kernel<Cfg<256, 256, 2, 4>, false>",
+       "wgrad_staged_kernel<Cfg<256, 256, 2, 4>, true>"},
+      {"wgrad_staged_kernel<Cfg<128, 128, 2, 2>, false>",
+       "wgrad_staged_kernel<Cfg<128, 128, 2, 2>, true>"}};
+  const WgradPlan pl = plan_wgrad(d, p, q);
+  return names[(int)pl.tile][pl.nsplit > 1];
 }
+#undef F2
+#undef F3
 
 // Tile and split count of a kernel gradient, by an estimate of its time:
 //   kWgradFixed + stages * max(alone, L * shared) (+ a split's reduction),
@@ -1170,7 +1167,7 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
   } else {
     double best = 1e30;
     for (const WgradTileCost &c : kWgradTiles) {
-      if (c.t == 256 && wgrad_name(rsc, d.c, d.k) == WgName::kSmall) continue;
+      if (c.t == 256 && (rsc < 256 || k < 256)) continue;
       const int64_t tiles = ((rsc + c.t - 1) / c.t) * ((k + c.t - 1) / c.t);
       // no split, a few, and as many as fill the CUs 1 to 6 times (or as many as
       // a bound on the workspace leaves: 160 x 216 outputs over 1826 positions in

@@ -26,6 +26,8 @@ struct Pipe {
   static constexpr int PB = B_BYTES / 1024 / NW;
   static constexpr int CPR = BK / 8;                 // 16-byte chunks per row
   static constexpr int RBA = 2 * TM, RBB = 2 * TN;   // mn-major row bytes
+  // waves per SIMD: those of the workgroups whose rings fit the 160 KiB of LDS
+  static constexpr int WPE = 160 * 1024 / (NS * (A_BYTES + B_BYTES)) * NW / 4;
   static_assert(A_BYTES == 1024 * NW * PA && B_BYTES == 1024 * NW * PB,
                 "DMA instructions must divide among waves");
 };
@@ -37,8 +39,6 @@ struct K : Pipe<BK_, NS_, WGM_, WGN_, T_, T_> {
   static constexpr int TILE_BYTES = Base::A_BYTES;   // per operand per stage
   static constexpr int PW = Base::PA;                // DMA instrs per operand
   static constexpr int RB = 2 * T;                   // mn-major row bytes
-  // waves per SIMD the kernel must fit (small tiles run two per CU)
-  static constexpr int WPE = T == 128 ? 2 * Base::NW / 4 : (Base::NW + 3) / 4;
 };
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format
 

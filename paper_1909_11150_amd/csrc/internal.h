@@ -107,13 +107,6 @@ enum class WgTile : int32_t {
   k256, k128, k64,           // fed by LDS DMA, square rho x k tiles (conv_dma.hip)
   kStaged256, kStaged128     // register-staged: tensors beyond a buffer resource
 };
-// Which name the kernel gradient of a shape runs under.
-enum class WgName : int32_t { kDma, kBig, kSmall };
-inline WgName wgrad_name(int64_t rsc, int32_t c, int32_t k) {
-  return c % 256 == 0 && k % 256 == 0 ? WgName::kDma
-         : rsc >= 256 && k >= 256     ? WgName::kBig
-                                      : WgName::kSmall;
-}
 struct WgradPlan {
   WgTile tile;
   int32_t nsplit, mchunk;
@@ -134,15 +127,18 @@ size_t head_wgrad_ws_bytes(const fg_conv_desc &d);
 
 hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor, hipStream_t st,
                             size_t max_ws_bytes = SIZE_MAX);
-hipError_t launch_data_conv_plan(const DataConvArgs &a, DataTile tile, bool w_kmajor,
-                                 hipStream_t st);
 const char *data_conv_kernel_name(const DataConvArgs &a, bool w_kmajor);
-bool data_conv_large(const DataConvArgs &a, DataTile tile);
 const char *wgrad_kernel_name(const fg_conv_desc &d);
 hipError_t launch_wgrad(const WgradArgs &a, WgTile tile, hipStream_t st);
 
 // Kernels fed by LDS DMA, on every tile: applicability and launchers.
 bool data_tile_ok(const DataConvArgs &a);
+// Which kernel of a tile runs a planned convolution (nsplit, nchunk, unit set).
+struct DataTileMode {
+  bool gen;   // stages straddle taps, or a part ends within one
+  bool fold;  // the parts of the sum are folded in one workgroup
+};
+DataTileMode data_tile_mode(const DataConvArgs &a, DataTile tile);
 hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_kmajor,
                                  hipStream_t st);
 // Stride-1 3x3 data convolution whose tile is whole output rows: the

@@ -133,25 +133,35 @@ def test_small_tile_plans_keep_one_workgroup_per_cu(L):
     """The 16x16 layers' passes on 128x128 tiles split their reduction only
     as far as one workgroup per CU (at most 256 workgroups): such a
     workgroup, alone on its CU, runs faster than two sharing one, so filling
-    the second slot with more splits loses."""
+    the second slot with more splits loses. The input gradient whose 128x128
+    tiles would already be 256, with phases of different lengths, takes 512
+    smaller ones, two per CU, unsplit."""
     from paper_1909_11150_amd.fcn import convt_dx_desc, fwd_desc
     layers = {l.name: l for l in synth.fcn_layers()}
-    cases = {  # pass: (descriptor, op, output shape, 128x128 tiles, expected splits)
-        "E4a.fwd": (fwd_desc(layers["E4a"]), fg.OP_FWD, layers["E4a"].y_shape, 64, 4),
-        "E4b.fwd": (fwd_desc(layers["E4b"]), fg.OP_FWD, layers["E4b"].y_shape, 64, 4),
-        "E4b.dx": (fwd_desc(layers["E4b"]), fg.OP_BWD_DATA, layers["E4b"].x_shape, 64, 4),
-        "E4a.dx": (fwd_desc(layers["E4a"]), fg.OP_BWD_DATA, layers["E4a"].x_shape, 256, 1),
-        "D4T.fwd": (fwd_desc(layers["D4T"]), fg.OP_CONVT, layers["D4T"].y_shape, 256, 1),
+    cases = {  # pass: (descriptor, op, output shape, kernel, tiles, expected splits)
+        "E4a.fwd": (fwd_desc(layers["E4a"]), fg.OP_FWD, layers["E4a"].y_shape,
+                    "data_conv_dma_kernel<128, true, true>", 64, 4),
+        "E4b.fwd": (fwd_desc(layers["E4b"]), fg.OP_FWD, layers["E4b"].y_shape,
+                    "data_conv_dma_kernel<128, true, true>", 64, 4),
+        "E4b.dx": (fwd_desc(layers["E4b"]), fg.OP_BWD_DATA, layers["E4b"].x_shape,
+                   "data_conv_dma_kernel<128, false, true>", 64, 4),
+        "E4a.dx": (fwd_desc(layers["E4a"]), fg.OP_BWD_DATA, layers["E4a"].x_shape,
+                   "data_conv_dma_kernel<64x128, false, false>", 512, 1),
+        "D4T.fwd": (fwd_desc(layers["D4T"]), fg.OP_CONVT, layers["D4T"].y_shape,
+                    "data_conv_dma_kernel<128, false, false>", 256, 1),
     }
-    for name, (d, op, shape, tiles, splits) in cases.items():
-        kern = fg.kernel_name(d, op)
-        assert kern.startswith("data_conv_dma_kernel<128,"), (name, kern)
+    for name, (d, op, shape, kern, tiles, splits) in cases.items():
+        assert fg.kernel_name(d, op) == kern, name
+        tm, tn = (64, 128) if "64x128" in kern else (128, 128)
+        phases = 4 if op == fg.OP_CONVT or d.stride_h == 2 and op == fg.OP_BWD_DATA else 1
+        n, h, w, ch = shape
+        assert phases * -(-ch // tm) * -(-(n * h * w // phases) // tn) == tiles, name
         ws = L.fg_conv_workspace_bytes(ctypes.byref(d), op)
         got = ws // (4 * int(np.prod(shape))) if ws else 1
-        assert got == splits and tiles * got <= 256, (name, got)
+        assert got == splits and tiles * got <= (512 if tm == 64 else 256), (name, got)
     # the transposed convolution's input gradient keeps 256x256 tiles
-    assert fg.kernel_name(convt_dx_desc(layers["D4T"]), fg.OP_FWD).startswith(
-        "data_conv_dma_kernel<true")
+    assert fg.kernel_name(convt_dx_desc(layers["D4T"]), fg.OP_FWD) == \
+        "data_conv_dma_kernel<true, true>"
 
 
 # (n, h, w, c, k, r, stride, pad), op, least size, size of the full plan
@@ -202,15 +212,14 @@ def test_plans_follow_the_estimate(L):
 
 
 def test_kernel_gradients_without_big_tiles_split_widely(L):
-    """A kernel gradient whose R*S*C or K is below 256 has only 128x128
-    tiles, and few of them: it may split its reduction beyond 16 ways to
-    fill the GPU; shapes with 256x256 tiles (the network's layers) keep 16
-    at most."""
+    """A kernel gradient whose R*S*C or K is below 256 has few tiles, of at
+    most 128x128: it may split its reduction beyond 16 ways to fill the GPU;
+    the network's layers, with 256x256 tiles, keep 16 at most."""
     def splits(d):
         ws = L.fg_conv_workspace_bytes(ctypes.byref(d), fg.OP_BWD_WEIGHT)
         return ws // (4 * d.k * d.r * d.s * d.c) if ws else 1
-    one_by_one = fg.ConvDesc.make(8, 64, 64, 128, 64, 1, 1, 1, 0)  # one 128x128 tile
-    assert fg.kernel_name(one_by_one, fg.OP_BWD_WEIGHT) == "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"
+    one_by_one = fg.ConvDesc.make(8, 64, 64, 128, 64, 1, 1, 1, 0)  # two 64x64 tiles
+    assert fg.kernel_name(one_by_one, fg.OP_BWD_WEIGHT) == "wgrad_dma_kernel<64, true>"
     assert splits(one_by_one) > 16
     from paper_1909_11150_amd.fcn import convt_dx_desc, fwd_desc
     for l in synth.fcn_layers():
@@ -447,6 +456,24 @@ def test_noalloc_kernel_gradient_validates_before_any_device_call(L):
                                        None) == fg.FG_EINVAL
     assert L.conv2d_bwd_weight_noalloc(ref(_desc(c=12)), FAKE, FAKE + (1 << 20),
                                        FAKE + (1 << 22), None) == fg.FG_EUNSUPPORTED
+
+
+def test_cases_name_the_kernels_the_planner_picks(L):
+    """The kernels named by the GPU tests of each path are those the planner
+    picks for their shapes, and between them they are all there are."""
+    import test_gpu_dma
+    import test_gpu_edges as edges
+    import test_gpu_strided
+    import test_gpu_zero_copy
+    cases = [(s, op, k) for s, op, k in edges.CASES + test_gpu_dma.CASES]
+    cases += [(s + (4, 2, 1), fg.OP_CONVT, k) for s, k in edges.CONVT]
+    cases += [(s + (3, 1, 1), fg.OP_BWD_WEIGHT, k) for s, k in test_gpu_zero_copy.PATHS]
+    cases += [c for c in test_gpu_strided.CASES if "<" in c[2]]
+    for (n, h, w, c, k, r, st, pd), op, kern in cases:
+        d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
+        assert fg.kernel_name(d, op) == kern, (n, h, w, c, k, r, st, pd, op)
+    edges.test_every_path_is_covered()
+    test_gpu_strided.test_strided_kernel_gradient_paths_covered()
 
 
 def test_random_shape_sweep_reaches_every_kernel_family(L):

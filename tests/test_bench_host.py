@@ -133,12 +133,21 @@ def test_ceiling_summary_prints_every_section(tmp_path, capsys):
 def test_kernel_names_from_the_trace_match_the_library_names():
     """rocprofv3's demangled names map to the names fg_conv_kernel_name
     reports: namespaces and arguments dropped, the pipeline configuration
-    dropped unless its tile is not 256, anonymous namespaces too."""
+    dropped but for a tile other than 256 x 256, anonymous namespaces too."""
     f = bench.short_kernel_name
     assert f("void fg::dma::wgrad_dma_kernel<fg::dma::K<32, 4, 2, 4, 256>, true>"
              "(fg::WgradArgs, fg::dma::WgradDiv, fg::dma::TileMap)") == "wgrad_dma_kernel<true>"
     assert f("void fg::dma::data_conv_dma_kernel<fg::dma::K<32, 5, 2, 2, 128>, false, true>"
              "(fg::DataConvArgs, fg::dma::TileMap)") == "data_conv_dma_kernel<128, false, true>"
+    args = "(fg::DataConvArgs, fg::dma::TileMap, fg::dma::PosDiv)"
+    for pipe, tile in (("32, 5, 2, 4, 256, 256", ""), ("64, 2, 4, 2, 128, 128", "128, "),
+                       ("64, 3, 2, 4, 64, 128", "64x128, "), ("64, 3, 2, 2, 64, 64", "64, ")):
+        for k in ("dma", "gen", "fold"):
+            assert f(f"void fg::dma::data_conv_{k}_kernel<fg::dma::Pipe<{pipe}>, true, false>"
+                     f"{args}") == f"data_conv_{k}_kernel<{tile}true, false>"
+    assert f("void fg::data_conv_staged_kernel<fg::Cfg<128, 128, 2, 2>, true, false, true>"
+             "(fg::DataConvArgs)") == \
+        "data_conv_staged_kernel<Cfg<128, 128, 2, 2>, true, false, true>"
     assert f("fg::(anonymous namespace)::mfma_loop_kernel(float*, int, int)") == \
         "mfma_loop_kernel"
     assert f("fg::split_reduce_kernel(float const*, int, long, unsigned short*, int*)") == \

@@ -19,8 +19,9 @@ pytestmark = pytest.mark.gpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# n, h, w, c, k, r, stride, pad: a register-staged, a 128-tile and a
-# 256-tile shape with a split kernel gradient
+# n, h, w, c, k, r, stride, pad: stages across taps with a split kernel
+# gradient, a strided shape on small tiles, and a folded forward sum with a
+# split kernel gradient on 128 x 128 tiles
 SHAPES = [(2, 19, 23, 24, 40, 3, 1, 1), (2, 33, 31, 64, 128, 3, 2, 1),
           (1, 64, 64, 256, 256, 3, 1, 1)]
 

@@ -1,9 +1,9 @@
 """GPU parity of the LDS-DMA kernels on ragged shapes.
 
-The tile planner sends large shapes to the LDS-DMA kernels (256 x 256
-tiles fed by buffer loads straight into LDS) and shapes with few output
-positions to their 128 x 128 version. These cases are chosen so that
-each of those kernels is reached with ragged edges: output positions and
+The tile planner sends large shapes to 256 x 256 tiles fed by buffer loads
+straight into LDS, and shapes with fewer output positions to tiles of 128 x
+128 down to 64 x 64. These cases are chosen so that
+each of those tiles is reached with ragged edges: output positions and
 channels that do not fill the last tile, odd image sizes with padding at the
 borders, stride-2 phases, reduction splits and partial last stages. Outputs
 are checked on sampled elements (plus all corners) against the oracle.
@@ -21,19 +21,24 @@ pytestmark = pytest.mark.gpu
 
 # (n, h, w, c, k, r, stride, pad), op, expected kernel
 CASES = [
-    ((2, 93, 95, 256, 512, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<true, false>"),
+    # 256 x 256 tiles
+    ((4, 79, 125, 32, 520, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<true, false>"),
     ((1, 77, 79, 512, 512, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<true, true>"),
-    ((4, 77, 79, 288, 256, 1, 1, 0), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, false>"),
-    ((1, 77, 79, 512, 512, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, true>"),
-    ((1, 127, 129, 512, 256, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, false>"),
+    ((3, 123, 119, 456, 32, 1, 1, 0), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, false>"),
+    ((2, 29, 135, 264, 288, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, true>"),
     ((1, 93, 95, 512, 512, 3, 1, 1), fg.OP_BWD_WEIGHT, "wgrad_dma_kernel<true>"),
     # 128 x 128 tiles
+    ((2, 93, 95, 256, 512, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<128, true, false>"),
     ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, true>"),
     ((8, 64, 64, 64, 128, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, false>"),
-    ((1, 31, 33, 512, 768, 3, 2, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, true>"),
     ((4, 64, 64, 256, 128, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
-    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
-    ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, true>"),
+    ((1, 77, 79, 512, 512, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, true>"),
+    ((1, 127, 129, 512, 256, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
+    # smaller ones
+    ((4, 77, 79, 288, 256, 1, 1, 0), fg.OP_BWD_DATA, "data_conv_dma_kernel<64x128, false, false>"),
+    ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<64x128, false, true>"),
+    ((1, 31, 33, 512, 768, 3, 2, 1), fg.OP_FWD, "data_conv_dma_kernel<64, true, true>"),
+    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<64, false, false>"),
 ]
 
 
@@ -78,10 +83,13 @@ def test_dma_conv(shape, op, kern):
         conv_parity(host(dw).ravel()[idx], ref, f"dW {shape}")
 
 
-def test_dma_convt_ragged():
-    n, h, w, ci, co = 1, 65, 66, 256, 512
+@pytest.mark.parametrize("shape,kern", [
+    ((3, 85, 49, 32, 392), "data_conv_dma_kernel<false, false>"),
+    ((1, 65, 66, 256, 512), "data_conv_dma_kernel<128, false, false>")], ids=str)
+def test_dma_convt_ragged(shape, kern):
+    n, h, w, ci, co = shape
     d = fg.ConvDesc.make(n, h, w, ci, co, 4, 4, 2, 1)
-    assert fg.kernel_name(d, fg.OP_CONVT) == "data_conv_dma_kernel<false, false>"
+    assert fg.kernel_name(d, fg.OP_CONVT) == kern
     rng = np.random.default_rng(23)
     x = synth.uniform(rng, (n, h, w, ci))
     Wt = synth.normal(rng, (ci, 4, 4, co), np.sqrt(2.0 / (4 * ci)))

@@ -37,54 +37,91 @@ FWD, DX, DW = fg.OP_FWD, fg.OP_BWD_DATA, fg.OP_BWD_WEIGHT
 
 # (n, h, w, c, k, r, stride, pad), op, the kernel the planner picks
 CASES = [
-    ((2, 93, 95, 256, 512, 1, 1, 0), FWD, "data_conv_dma_kernel<true, false>"),
+    ((2, 93, 95, 256, 512, 1, 1, 0), FWD, "data_conv_dma_kernel<128, true, false>"),
     ((1, 77, 79, 512, 512, 3, 1, 1), FWD, "data_conv_dma_kernel<true, true>"),
     ((8, 64, 64, 64, 128, 3, 1, 1), FWD, "data_conv_dma_kernel<128, true, false>"),
     ((2, 15, 17, 1024, 1024, 3, 1, 1), FWD, "data_conv_dma_kernel<128, true, true>"),
     ((1, 127, 129, 512, 256, 3, 2, 1), FWD, "data_conv_dma_kernel<128, true, true>"),
     ((2, 128, 128, 256, 320, 3, 1, 1), FWD, "data_conv_halo_kernel<true, false>"),
     ((1, 64, 64, 1024, 1024, 3, 1, 1), FWD, "data_conv_halo_kernel<true, true>"),
-    ((2, 64, 64, 16, 16, 3, 1, 1), FWD,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>"),
-    ((2, 20, 21, 48, 40, 3, 2, 1), FWD,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, false>"),
-    ((1, 8, 7, 104, 16, 3, 1, 1), FWD,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, true, false, true>"),
-    ((4, 128, 128, 264, 512, 3, 1, 1), FWD,
-     "data_conv_kernel<Cfg<256, 256, 2, 4>, true, false, false>"),
+    ((2, 64, 64, 16, 16, 3, 1, 1), FWD, "data_conv_gen_kernel<64, true, false>"),
+    ((2, 20, 21, 48, 40, 3, 2, 1), FWD, "data_conv_fold_kernel<64, true, true>"),
+    ((1, 8, 7, 104, 16, 3, 1, 1), FWD, "data_conv_gen_kernel<64, true, true>"),
+    ((4, 128, 128, 264, 512, 3, 1, 1), FWD, "data_conv_gen_kernel<true, false>"),
     ((2, 30, 30, 64, 1, 1, 1, 0), FWD, "head_fwd_kernel"),
-    ((4, 77, 79, 288, 256, 1, 1, 0), DX, "data_conv_dma_kernel<false, false>"),
-    ((1, 127, 129, 512, 256, 3, 2, 1), DX, "data_conv_dma_kernel<false, false>"),
-    ((1, 77, 79, 512, 512, 3, 1, 1), DX, "data_conv_dma_kernel<false, true>"),
+    ((4, 77, 79, 288, 256, 1, 1, 0), DX, "data_conv_dma_kernel<64x128, false, false>"),
+    ((1, 127, 129, 512, 256, 3, 2, 1), DX, "data_conv_dma_kernel<128, false, false>"),
+    ((1, 77, 79, 512, 512, 3, 1, 1), DX, "data_conv_dma_kernel<128, false, true>"),
     ((4, 64, 64, 256, 128, 3, 1, 1), DX, "data_conv_dma_kernel<128, false, false>"),
-    ((1, 33, 31, 1024, 512, 3, 2, 1), DX, "data_conv_dma_kernel<128, false, false>"),
-    ((1, 15, 6, 8, 96, 3, 1, 1), DX, "data_conv_dma_kernel<128, false, true>"),
+    ((1, 33, 31, 1024, 512, 3, 2, 1), DX, "data_conv_dma_kernel<64, false, false>"),
+    ((1, 15, 6, 8, 96, 3, 1, 1), DX, "data_conv_gen_kernel<64, false, true>"),
     ((2, 128, 128, 512, 320, 3, 1, 1), DX, "data_conv_halo_kernel<false, false>"),
     ((1, 64, 64, 1024, 1024, 3, 1, 1), DX, "data_conv_halo_kernel<false, true>"),
-    ((2, 20, 21, 48, 40, 3, 2, 1), DX,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>"),
-    ((2, 20, 21, 40, 48, 3, 1, 1), DX,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>"),
-    ((1, 5, 5, 16, 88, 3, 1, 1), DX,
-     "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, true>"),
-    ((4, 128, 128, 512, 264, 3, 1, 1), DX,
-     "data_conv_kernel<Cfg<256, 256, 2, 4>, false, false, false>"),
+    ((2, 20, 21, 48, 40, 3, 2, 1), DX, "data_conv_gen_kernel<64, false, false>"),
+    ((2, 20, 21, 40, 48, 3, 1, 1), DX, "data_conv_gen_kernel<64, false, false>"),
+    ((1, 5, 5, 16, 88, 3, 1, 1), DX, "data_conv_gen_kernel<64, false, true>"),
+    ((4, 128, 128, 512, 264, 3, 1, 1), DX, "data_conv_gen_kernel<false, false>"),
     ((2, 30, 30, 64, 1, 1, 1, 0), DX, "head_bwd_data_kernel"),
     ((1, 77, 79, 512, 512, 3, 1, 1), DW, "wgrad_dma_kernel<true>"),
     ((2, 15, 17, 1024, 1024, 3, 1, 1), DW, "wgrad_dma_kernel<false>"),
-    ((2, 20, 21, 48, 40, 3, 2, 1), DW, "wgrad_kernel<Cfg<128, 128, 2, 2>, false>"),
-    ((2, 64, 64, 16, 16, 3, 1, 1), DW, "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"),
-    ((1, 64, 64, 264, 512, 3, 2, 1), DW, "wgrad_kernel<Cfg<256, 256, 2, 4>, false>"),
-    ((4, 77, 79, 288, 256, 1, 1, 0), DW, "wgrad_kernel<Cfg<256, 256, 2, 4>, true>"),
+    ((2, 20, 21, 48, 40, 3, 2, 1), DW, "wgrad_dma_kernel<64, false>"),
+    ((2, 64, 64, 16, 16, 3, 1, 1), DW, "wgrad_dma_kernel<128, true>"),
+    ((1, 64, 64, 264, 512, 3, 2, 1), DW, "wgrad_dma_kernel<64, false>"),
+    ((4, 77, 79, 288, 256, 1, 1, 0), DW, "wgrad_dma_kernel<64, true>"),
     ((2, 30, 30, 64, 1, 1, 1, 0), DW, "head_wgrad_kernel"),
+    # the kernels that the shapes above leave out
+    ((1, 4, 50, 64, 16, 1, 1, 0), FWD, "data_conv_dma_kernel<64, true, false>"),
+    ((5, 4, 10, 128, 16, 3, 1, 1), FWD, "data_conv_dma_kernel<64, true, true>"),
+    ((5, 26, 64, 64, 72, 3, 1, 1), FWD, "data_conv_dma_kernel<64x128, true, false>"),
+    ((6, 10, 27, 128, 72, 3, 1, 1), FWD, "data_conv_dma_kernel<64x128, true, true>"),
+    ((7, 49, 64, 96, 264, 3, 1, 1), FWD, "data_conv_dma_kernel<true, false>"),
+    ((6, 49, 32, 128, 392, 3, 1, 1), FWD, "data_conv_fold_kernel<128, true, false>"),
+    ((1, 118, 141, 72, 72, 3, 1, 1), FWD, "data_conv_fold_kernel<128, true, true>"),
+    ((1, 7, 32, 640, 16, 1, 1, 0), FWD, "data_conv_fold_kernel<64, true, false>"),
+    ((7, 11, 71, 128, 136, 3, 1, 1), FWD, "data_conv_fold_kernel<64x128, true, false>"),
+    ((7, 37, 64, 56, 16, 3, 1, 1), FWD, "data_conv_fold_kernel<64x128, true, true>"),
+    ((3, 66, 128, 16, 72, 3, 1, 1), FWD, "data_conv_gen_kernel<128, true, false>"),
+    ((1, 50, 44, 288, 72, 3, 1, 1), FWD, "data_conv_gen_kernel<128, true, true>"),
+    ((5, 26, 128, 16, 16, 3, 1, 1), FWD, "data_conv_gen_kernel<64x128, true, false>"),
+    ((3, 11, 51, 120, 72, 3, 1, 1), FWD, "data_conv_gen_kernel<64x128, true, true>"),
+    ((3, 29, 64, 336, 416, 3, 1, 1), FWD, "data_conv_gen_kernel<true, true>"),
+    ((2, 34, 3, 16, 128, 3, 1, 1), DX, "data_conv_dma_kernel<64, false, true>"),
+    ((1, 52, 26, 16, 320, 3, 1, 1), DX, "data_conv_dma_kernel<64x128, false, true>"),
+    ((7, 99, 32, 272, 96, 3, 1, 1), DX, "data_conv_dma_kernel<false, false>"),
+    ((2, 50, 72, 264, 288, 3, 1, 1), DX, "data_conv_dma_kernel<false, true>"),
+    ((3, 130, 64, 72, 16, 3, 1, 1), DX, "data_conv_gen_kernel<128, false, false>"),
+    ((5, 26, 32, 72, 248, 3, 1, 1), DX, "data_conv_gen_kernel<128, false, true>"),
+    ((5, 26, 128, 16, 16, 3, 1, 1), DX, "data_conv_gen_kernel<64x128, false, false>"),
+    ((4, 13, 64, 16, 88, 3, 1, 1), DX, "data_conv_gen_kernel<64x128, false, true>"),
+    ((2, 74, 64, 392, 264, 3, 1, 1), DX, "data_conv_gen_kernel<false, true>"),
+    ((3, 6, 13, 928, 200, 3, 1, 1), DW, "wgrad_dma_kernel<128, false>"),
 ]
 
 # transposed convolutions, 4x4 stride 2 pad 1: (n, h, w, c_in, c_out)
 CONVT = [
-    ((1, 65, 66, 256, 512), "data_conv_dma_kernel<false, false>"),
+    ((1, 65, 66, 256, 512), "data_conv_dma_kernel<128, false, false>"),
     ((1, 15, 16, 1024, 1024), "data_conv_dma_kernel<128, false, true>"),
     ((8, 32, 32, 256, 128), "data_conv_dma_kernel<128, false, false>"),
-    ((2, 40, 40, 72, 256), "data_conv_kernel<Cfg<128, 128, 2, 2>, false, false, false>"),
+    ((2, 40, 40, 72, 256), "data_conv_gen_kernel<128, false, false>"),
+    ((5, 5, 32, 64, 16), "data_conv_dma_kernel<64, false, false>"),
+    ((5, 5, 32, 256, 16), "data_conv_dma_kernel<64, false, true>"),
+    ((5, 41, 20, 64, 16), "data_conv_dma_kernel<64x128, false, false>"),
+    ((5, 5, 32, 320, 16), "data_conv_dma_kernel<64x128, false, true>"),
+    ((4, 25, 64, 96, 392), "data_conv_dma_kernel<false, false>"),
+    ((3, 33, 12, 672, 392), "data_conv_dma_kernel<false, true>"),
+    ((4, 13, 64, 256, 264), "data_conv_fold_kernel<128, false, false>"),
+    ((7, 37, 16, 152, 72), "data_conv_fold_kernel<128, false, true>"),
+    ((2, 20, 20, 192, 16), "data_conv_fold_kernel<64, false, false>"),
+    ((2, 25, 16, 104, 16), "data_conv_fold_kernel<64, false, true>"),
+    ((3, 43, 16, 192, 72), "data_conv_fold_kernel<64x128, false, false>"),
+    ((7, 4, 75, 120, 72), "data_conv_fold_kernel<64x128, false, true>"),
+    ((2, 27, 16, 392, 72), "data_conv_gen_kernel<128, false, true>"),
+    ((5, 5, 32, 16, 16), "data_conv_gen_kernel<64, false, false>"),
+    ((7, 29, 4, 200, 16), "data_conv_gen_kernel<64, false, true>"),
+    ((6, 43, 16, 40, 16), "data_conv_gen_kernel<64x128, false, false>"),
+    ((1, 12, 67, 272, 16), "data_conv_gen_kernel<64x128, false, true>"),
+    ((3, 65, 32, 56, 400), "data_conv_gen_kernel<false, false>"),
+    ((1, 21, 64, 744, 392), "data_conv_gen_kernel<false, true>"),
 ]
 
 F16_MAX_FINITE = 65504.0
@@ -261,15 +298,27 @@ def test_fp16_range_edges_convt(shape, kern, recipe):
     _check("convT", (n, h, w, ci, co, 4, 2, 1), kern, recipe)
 
 
+def all_kernels():
+    """(pass, kernel) for every kernel that runs a pass below 2 GiB: by tile,
+    whole-tap or straddling stages, split, unsplit or folded sums. Forward
+    weights are read as they lie ("true"), the others transposed."""
+    tiles, out = ("128, ", "64x128, ", "64, "), set()
+    for op, wk in ((FWD, "true"), (DX, "false"), ("convT", "false")):
+        for split in ("true", "false"):
+            out |= {(op, f"data_conv_{kind}_kernel<{t}{wk}, {split}>")
+                    for kind in ("dma", "gen") for t in ("",) + tiles}
+            if op != "convT":   # whole-row tiles of stride-1 3x3 kernels
+                out.add((op, f"data_conv_halo_kernel<{wk}, {split}>"))
+        if op != DX:            # passes whose order of sums is fixed
+            out |= {(op, f"data_conv_fold_kernel<{t}{wk}, {gen}>")
+                    for t in tiles for gen in ("true", "false")}
+    out |= {(DW, f"wgrad_dma_kernel<{t}{split}>") for t in ("", "128, ", "64, ")
+            for split in ("true", "false")}
+    return out | {(FWD, "head_fwd_kernel"), (DX, "head_bwd_data_kernel"),
+                  (DW, "head_wgrad_kernel")}
+
+
 def test_every_path_is_covered():
-    """The cases above reach every kernel name the planner reports for the
-    shapes they hold, forward, input gradient, kernel gradient and
-    transposed forward alike."""
-    names = {k for _, _, k in CASES} | {k for _, k in CONVT}
-    for prefix in ("data_conv_dma_kernel<", "data_conv_halo_kernel<",
-                   "data_conv_kernel<", "wgrad_dma_kernel<", "wgrad_kernel<", "head_"):
-        assert any(nm.startswith(prefix) for nm in names), prefix
-    dma = {nm for nm in names if nm.startswith("data_conv_dma_kernel<")}
-    assert len(dma) == 8
-    halo = {nm for nm in names if nm.startswith("data_conv_halo_kernel<")}
-    assert len(halo) == 4
+    """The cases above name every kernel of every pass (test_abi_cpu.py checks
+    that the planner picks the named ones)."""
+    assert {(op, k) for _, op, k in CASES} | {("convT", k) for _, k in CONVT} == all_kernels()

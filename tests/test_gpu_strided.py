@@ -1,10 +1,10 @@
 """GPU parity of strided outputs and the accumulate epilogue (the layout a
 dense block's concatenation and its gradient sums need, Section 6.2).
 
-For each output path of the data convolutions (staged 256 x 256 store with
-and without a split, the input-reuse kernel, 128 x 128 tiles, the
-register-staged kernel, a strided input gradient's four phases, the
-transposed convolution), the pass writes into a channel slice of a wider
+For each output path of the data convolutions (256 x 256 tiles with and
+without a split, the input-reuse kernel, the smaller tiles with and without a
+split, with stages across taps and with folded sums, a strided input
+gradient's four phases, the transposed convolution), the pass writes into a channel slice of a wider
 buffer (pixel stride = channels + 24, slice at channel 8):
   * plain: the slice equals the dense call's output bit for bit, and every
     other channel of the buffer keeps its bits;
@@ -31,14 +31,17 @@ PAD, OFF = 24, 8
 
 # (n, h, w, c, k, r, stride, pad), op, kernel-name fragment
 CASES = [
-    ((2, 93, 95, 256, 512, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<true, false>"),
+    ((4, 79, 125, 32, 520, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<true, false>"),
+    ((2, 93, 95, 256, 512, 1, 1, 0), fg.OP_FWD, "data_conv_dma_kernel<128, true, false>"),
     ((1, 77, 79, 512, 512, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<true, true>"),
     ((2, 128, 128, 512, 320, 3, 1, 1), fg.OP_BWD_DATA, "halo"),
     ((1, 64, 64, 1024, 1024, 3, 1, 1), fg.OP_FWD, "halo"),
-    ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128"),
-    ((2, 16, 16, 24, 40, 3, 1, 1), fg.OP_FWD, "data_conv_kernel<"),
-    ((1, 127, 129, 512, 256, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<false"),
-    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128"),
+    ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128, true, true>"),
+    ((2, 16, 16, 24, 40, 3, 1, 1), fg.OP_FWD, "data_conv_gen_kernel<64, true, false>"),
+    ((2, 20, 21, 48, 40, 3, 2, 1), fg.OP_FWD, "data_conv_fold_kernel<64, true, true>"),
+    ((3, 123, 119, 456, 32, 1, 1, 0), fg.OP_BWD_DATA, "data_conv_dma_kernel<false, false>"),
+    ((1, 127, 129, 512, 256, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
+    ((1, 33, 31, 1024, 512, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<64, false, false>"),
 ]
 
 
@@ -137,7 +140,8 @@ def test_strided_convt_and_gate():
 # channel slice of a wider buffer, on each kernel path
 IN_CASES = [(s, f) for s, op, f in CASES if op == fg.OP_FWD] + \
     [((1, 127, 129, 512, 256, 3, 2, 1), "")]
-WG_FRAGS = ("wgrad_dma_kernel<false>", "wgrad_dma_kernel<true>", "wgrad_kernel<")
+WG_FRAGS = ("wgrad_dma_kernel<true>", "wgrad_dma_kernel<false>", "wgrad_dma_kernel<128, true>",
+            "wgrad_dma_kernel<64, false>", "wgrad_dma_kernel<64, true>")
 
 
 @pytest.mark.parametrize("shape,frag", IN_CASES, ids=[f"{f}-{s}" for s, f in IN_CASES])
@@ -174,10 +178,10 @@ def test_strided_input(shape, frag):
 
 
 def test_strided_kernel_gradient_paths_covered():
-    names = {fg.kernel_name(fg.ConvDesc.make(*s, x_ld=s[3] + PAD), fg.OP_BWD_WEIGHT)
-             for s, _ in IN_CASES}
-    for f in WG_FRAGS:
-        assert any(f in nm for nm in names), (f, names)
+    names = {fg.kernel_name(fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd, x_ld=c + PAD),
+                            fg.OP_BWD_WEIGHT)
+             for (n, h, w, c, k, r, st, pd), _ in IN_CASES}
+    assert names == set(WG_FRAGS), names
 
 
 def test_interleaved_input_and_output():

@@ -10,7 +10,7 @@ below the kernel size, channels any multiple of 8, images from 1x1 up, so
 that the planner's choices meet shapes nobody picked: empty output phases of
 strided input gradients, images smaller than the kernel, single-tile and
 ragged tiles, split and unsplit reductions. Small cases are compared in
-full; large ones (on the LDS-DMA, halo and split kernels) on sampled outputs
+full; large ones (on the larger tiles, halo and split kernels) on sampled outputs
 plus all corners; each call is made twice and must give the same bits. The parity rule is the one every convolution test uses
 (rel_L2 <= 5e-3 and max_abs <= 2e-2 * RMS against the fp64 oracle on the
 same fp16 inputs).
@@ -116,23 +116,30 @@ def _name(case):
 
 
 def check_coverage():
-    """The draw reaches the register-staged, LDS-DMA, halo and split kernels
-    and the strided, non-square and empty-phase corners (run by the CPU
-    tests: it needs the planner only)."""
+    """The draw reaches the tiles of the LDS-DMA kernels, whole-tap and
+    straddling stages, split and folded sums, the input-reuse kernel, and the
+    strided, non-square and empty-phase corners (run by the CPU tests: it needs
+    the planner only)."""
     names = set()
     for op, (n, h, w, c, k, r, s, st, pd) in CASES:
         names.add(fg.kernel_name(fg.ConvDesc.make(n, h, w, c, k, r, s, st, pd), op))
     ct = {fg.kernel_name(fg.ConvDesc.make(n, h, w, c, k, 4, 4, 2, 1), CT)
           for n, h, w, c, k in CONVT}
-    assert any(nm.startswith("data_conv_dma_kernel<false") for nm in ct), ct
-    assert any(nm.startswith("data_conv_kernel<") for nm in ct), ct
+    for fam in ("data_conv_dma_kernel<false", "data_conv_gen_kernel<64, ",
+                "data_conv_fold_kernel<"):
+        assert any(nm.startswith(fam) for nm in ct), (fam, ct)
+    names |= ct   # weights read transposed, as for input gradients
     epis = {epilogue_of(_name(c)) for c in CASES}
     assert epis == {"none", "relu", "gate"}, epis
-    joined = " ".join(sorted(names))
-    for fam in ("data_conv_kernel<", "data_conv_dma_kernel<true", "data_conv_dma_kernel<false",
-                "data_conv_dma_kernel<128", "data_conv_halo_kernel<", "wgrad_kernel<",
-                "wgrad_dma_kernel<true>"):
-        assert fam in joined, (fam, sorted(names))
+    fams = [f"data_conv_{k}_kernel<{t}" for k in ("dma", "gen") for t in
+            ("128, ", "64x128, ", "64, true", "64, false")]
+    fams += ["data_conv_dma_kernel<true", "data_conv_dma_kernel<false", "data_conv_halo_kernel<",
+             "data_conv_fold_kernel<64x128, ", "data_conv_fold_kernel<64, "]
+    fams += [f"wgrad_dma_kernel<{t}" for t in ("true>", "128, true>", "64, true>", "64, false>")]
+    for fam in fams:
+        assert any(nm.startswith(fam) for nm in names), (fam, sorted(names))
+    for kind in ("dma", "gen"):   # split sums
+        assert any(nm.startswith(f"data_conv_{kind}") and nm.endswith("true>") for nm in names)
     assert any(r != s for _, (_, _, _, _, _, r, s, _, _) in CASES)
     assert any(st == 2 and op == DX for op, (*_, st, _) in CASES)
     # an input gradient with an output phase that no tap reaches

@@ -5,8 +5,8 @@ its group buffer (the fusion buffer of Section 4.2 without the copy-in), and
 flags a non-finite result in the same store (the check of Section 6.2's loss
 scaling). Checks:
 - the checked call writes bit for bit what conv2d_bwd_weight writes, on each
-  kernel path (LDS-DMA with and without a split reduction, the register-
-  staged kernel, the K = 1 head);
+  kernel path (each tile size with and without a split reduction, the K = 1
+  head);
 - a closed form pins both the values and the flag: with x = dy = a constant
   a, a 3x3 stride-1 pad-1 kernel gradient is a^2 * n * cnt(r) * cnt(s) with
   cnt = (h-1, h, h-1) by (w-1, w, w-1); a is a power of two chosen so that
@@ -29,10 +29,13 @@ pytestmark = pytest.mark.gpu
 
 # (n, h, w, c, k), kernel path
 PATHS = [
-    ((1, 16, 16, 256, 256), "wgrad_dma_kernel<false>"),
-    ((4, 64, 64, 256, 256), "wgrad_dma_kernel<true>"),
-    ((1, 8, 8, 64, 64), "wgrad_kernel<Cfg<128, 128, 2, 2>, false>"),
-    ((2, 16, 32, 64, 64), "wgrad_kernel<Cfg<128, 128, 2, 2>, true>"),
+    ((1, 16, 16, 1024, 1024), "wgrad_dma_kernel<false>"),
+    ((4, 64, 64, 512, 256), "wgrad_dma_kernel<true>"),
+    ((4, 16, 16, 512, 512), "wgrad_dma_kernel<128, false>"),
+    ((4, 64, 64, 256, 256), "wgrad_dma_kernel<128, true>"),
+    ((1, 16, 16, 256, 256), "wgrad_dma_kernel<64, false>"),
+    ((1, 8, 8, 64, 64), "wgrad_dma_kernel<64, false>"),
+    ((2, 16, 32, 64, 64), "wgrad_dma_kernel<64, true>"),
 ]
 
 
@@ -52,7 +55,7 @@ def _run(d, x, dy, shape_w):
     return host(plain), host(checked), int(host(flag)[0])
 
 
-@pytest.mark.parametrize("shape,kern", PATHS, ids=[k for _, k in PATHS])
+@pytest.mark.parametrize("shape,kern", PATHS, ids=[f"{k}-{s[3]}" for s, k in PATHS])
 def test_checked_kernel_gradient_closed_form(shape, kern):
     n, h, w, c, k = shape
     d = fg.ConvDesc.make(n, h, w, c, k, 3, 3, 1, 1)
