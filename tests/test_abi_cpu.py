@@ -472,7 +472,11 @@ def test_cases_name_the_kernels_the_planner_picks(L):
     for (n, h, w, c, k, r, st, pd), op, kern in cases:
         d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
         assert fg.kernel_name(d, op) == kern, (n, h, w, c, k, r, st, pd, op)
+    import test_gpu_staged
+    for d, op, kern in test_gpu_staged.descs():
+        assert fg.kernel_name(d, op) == kern
     edges.test_every_path_is_covered()
+    test_gpu_staged.test_every_staged_kernel_is_named()
     test_gpu_strided.test_strided_kernel_gradient_paths_covered()
 
 
