@@ -473,6 +473,11 @@ def test_cases_name_the_kernels_the_planner_picks(L):
         d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
         assert fg.kernel_name(d, op) == kern, (n, h, w, c, k, r, st, pd, op)
     import test_gpu_staged
+    import test_gpu_sum_order as order
+    for op, shape, nf, ns, parts, fold, split in order.CASES:
+        assert [fg.kernel_name(order.desc(op, n, shape), op) for n in (nf, ns)] == \
+            ["data_conv_" + fold, "data_conv_" + split], shape
+        assert order.parts_of_split(op, ns, shape) == parts
     for d, op, kern in test_gpu_staged.descs():
         assert fg.kernel_name(d, op) == kern
     edges.test_every_path_is_covered()
