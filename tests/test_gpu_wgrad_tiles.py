@@ -1,9 +1,11 @@
 """Kernel gradients at the edges of their tiles: channel counts that no tile
 divides (so that a tile straddles taps and runs past the last row or column),
 reductions shorter than a stage, not a multiple of one, and split, on each
-tile size; checked against the oracle, twice for identical bits."""
+tile size; checked against the oracle, twice for identical bits, and once more
+on operands that are not 16-byte aligned."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1909_11150_amd as fg
@@ -31,6 +33,14 @@ CASES = [
 ]
 
 
+def _at(t, off):
+    """The tensor's values at element offset off of a larger buffer."""
+    buf = torch.zeros(t.numel() + 16, dtype=torch.float16, device="cuda")
+    v = buf[off:off + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
 @pytest.mark.parametrize("shape", CASES, ids=[str(s) for s in CASES])
 def test_kernel_gradient_tiles(shape):
     n, h, w, c, k, r, st, pd = shape
@@ -41,11 +51,12 @@ def test_kernel_gradient_tiles(shape):
     dy = synth.uniform(rng, (n, p, q, k))
     xd, dyd = dev(x), dev(dy)
     outs = []
-    for _ in range(2):
-        dw = empty16((k, r, r, c))
-        fg.conv2d_bwd_weight(d, xd, dyd, dw, workspace(d, fg.OP_BWD_WEIGHT))
+    for off in (0, 0, 1):  # the last: every pointer 2 bytes past 16-byte alignment
+        dw = _at(empty16((k, r, r, c)), off)
+        fg.conv2d_bwd_weight(d, _at(xd, off), _at(dyd, off), dw, workspace(d, fg.OP_BWD_WEIGHT))
         outs.append(host(dw))
-    np.testing.assert_array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    for o in outs[1:]:
+        np.testing.assert_array_equal(outs[0].view(np.uint16), o.view(np.uint16))
     idx = sample_indices((k, r, r, c), 2500, rng)
     ref = oracle.conv2d_bwd_weight_points(x, dy, r, r, idx, st, pd)
     conv_parity(outs[0].ravel()[idx], ref, f"dW {shape}")
