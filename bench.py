@@ -146,12 +146,15 @@ def kernel_source(kernel):
 
 
 def source_hash(kernel):
-    """Hash of the source file that defines `kernel` and of the one that
-    holds the tile and split planner (which decides the layers and splits a
-    kernel runs, and so its bytes per launch)."""
+    """Hash of the source file that defines `kernel`, of the pipeline it is
+    built from where it has one, and of the file that holds the tile and split
+    planner (which decides the layers and splits a kernel runs, and so its bytes
+    per launch)."""
     import hashlib
     h = hashlib.sha256()
-    for f in dict.fromkeys((kernel_source(kernel), "conv_igemm.hip")):
+    src = kernel_source(kernel)
+    pipe = ("dma_pipe.h",) if src == "conv_dma.hip" else ()
+    for f in dict.fromkeys((src,) + pipe + ("conv_igemm.hip",)):
         h.update(open(os.path.join(ROOT, "paper_1909_11150_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -79,7 +79,8 @@ def test_trace_summary_separates_detail_and_timed_launches(tmp_path, capsys):
 
 def test_traffic_record_is_keyed_by_kernel_and_planner_sources(tmp_path, monkeypatch):
     """recorded_traffic reads the committed profile's line for the kernel only
-    while the hash of the kernel's source and the planner's matches."""
+    while the hash of the kernel's sources (its file and the pipeline's) and the
+    planner's matches."""
     prof = tmp_path / "profiles"
     prof.mkdir()
     k = "wgrad_dma_kernel<true>"
@@ -93,14 +94,20 @@ def test_traffic_record_is_keyed_by_kernel_and_planner_sources(tmp_path, monkeyp
     # real source files
     csrc = tmp_path / "paper_1909_11150_amd" / "csrc"
     csrc.mkdir(parents=True)
-    for f in ("conv_dma.hip", "conv_igemm.hip"):
+    files = ("conv_dma.hip", "dma_pipe.h", "conv_igemm.hip")
+    for f in files:
         (csrc / f).write_bytes(open(os.path.join(ROOT, "paper_1909_11150_amd", "csrc", f),
                                     "rb").read())
     assert bench.recorded_traffic(k) == 123
     assert bench.recorded_traffic("data_conv_dma_kernel<true, false>") is None
-    # an edit to the planner's file invalidates the record
-    (csrc / "conv_igemm.hip").write_bytes(b"// edited\n" + (csrc / "conv_igemm.hip").read_bytes())
-    assert bench.recorded_traffic(k) is None
+    # an edit to the kernel's, the pipeline's or the planner's file invalidates
+    # the record
+    for f in files:
+        text = (csrc / f).read_bytes()
+        (csrc / f).write_bytes(b"// edited\n" + text)
+        assert bench.recorded_traffic(k) is None, f
+        (csrc / f).write_bytes(text)
+    assert bench.recorded_traffic(k) == 123
 
 
 def test_ceiling_summary_prints_every_section(tmp_path, capsys):
