@@ -34,11 +34,14 @@
  *     device memory. Its only device memory of its own is the static
  *     scratch array of conv2d_bwd_weight_noalloc (one per GPU, loaded with
  *     the library), and no call reads what an earlier call left there, so it
- *     keeps no device state between calls. Its host state is two small
- *     records: the optimizer's per-workspace record of which layers have
- *     norms and which are applied in the current step (lars_adam_norms /
- *     lars_adam_apply, under a mutex), and the one-shot profiling events of
- *     fg_profile_next_launch (per host thread).
+ *     keeps no device state between calls. Its host state: the optimizer's
+ *     per-workspace record of which layers have norms and which are applied
+ *     in the current step (lars_adam_norms / lars_adam_apply, under a mutex);
+ *     the address of the scratch array on each GPU (under a mutex); and per
+ *     host thread the one-shot profiling events of fg_profile_next_launch and
+ *     the plans of up to 64 data-convolution and 64 kernel-gradient shapes (a
+ *     function of the descriptor and the pass alone; some 30 KiB, freed with
+ *     the thread).
  *   - GPU work is enqueued on `stream` (0 = the null stream) and the call
  *     returns without synchronising; results are valid once the caller has
  *     synchronised the stream. Device faults surface at that synchronisation.
@@ -508,9 +511,12 @@ fg_status grad_group_plan(const uint64_t *numel, int32_t ntensors,
                           uint64_t *offset_of, int32_t *ngroups,
                           uint64_t *group_numel);
 
-/* Name of the main GPU kernel the given pass launches for this shape (a
- * static string; "" for an invalid or unsupported shape). Lets a profiler
- * or benchmark group launches the way a kernel trace does. */
+/* Name of the main GPU kernel the given pass launches for this shape, with
+ * the workspace that fg_conv_workspace_bytes asks for (a static string; "" for
+ * an invalid or unsupported shape): the template's name and arguments as a
+ * kernel trace prints them, without namespaces, and with a pipeline's
+ * configuration as its tile (nothing for 256 x 256, 128 for 128 x 128, 64x128).
+ * Lets a profiler or benchmark group launches the way a kernel trace does. */
 const char *fg_conv_kernel_name(const fg_conv_desc *d, int op);
 
 /* Human-readable name of a status code (static string). */

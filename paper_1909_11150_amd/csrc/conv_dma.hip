@@ -757,7 +757,9 @@ __device__ __forceinline__ void data_tile(const DataConvArgs &a, const TileMap &
     }
   }
   const int dt = BK / a.cr, dc = BK - dt * a.cr;  // GEN: a stage's advance
-  const int nsm = (255 + F.ns) / max(F.ns, 1);     // t / ns = t * nsm >> 8, t < 64
+  // t / ns = t * nsm >> 8 for the taps there are, t < nr * ns <= 16 (not for every
+  // t < 64); later ones, past the end of the sum, are masked off by kend
+  const int nsm = (255 + F.ns) / max(F.ns, 1);
 
   // uniform stage decode (whole stages of one tap), as in the kernels above
   int cr0 = 0, ti = 0, tj = 0, kk0 = kbeg;

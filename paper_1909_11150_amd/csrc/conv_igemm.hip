@@ -792,7 +792,8 @@ DataWork data_work(const DataConvArgs &a, int tm, int tn, int bk) {
 
 // Plans of the last shapes a host thread asked for: a call asks at least twice
 // (workspace, launch), a program for the same shapes every step, and working
-// one out takes 1 to 2 us of the 5 that a launch costs the host.
+// one out takes 1 to 2 us of the 5 that a launch costs the host. One place per
+// hash: of two shapes that share one, each is worked out anew when its turn comes.
 template <class Key, class Plan>
 struct PlanMemo {
   static constexpr unsigned N = 64;
