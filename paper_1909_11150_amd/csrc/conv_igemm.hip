@@ -1170,14 +1170,17 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
     for (const WgradTileCost &c : kWgradTiles) {
       if (c.t == 256 && (rsc < 256 || k < 256)) continue;
       const int64_t tiles = ((rsc + c.t - 1) / c.t) * ((k + c.t - 1) / c.t);
-      // no split, a few, and as many as fill the CUs 1 to 6 times (or as many as
-      // a bound on the workspace leaves: 160 x 216 outputs over 1826 positions in
-      // the 1.1 MB of 8 parts otherwise take 4)
+      // no split, a few, and as many as fill the CUs 1 to 6 times; where even once,
+      // on the smallest tiles, is more than there are stages, or than a bound on
+      // the workspace leaves, as many as those (64 x 64 outputs over 14432
+      // positions, 226 stages on one tile: 24.4 us in 4 parts, 8.4 in 226). From 36
+      // stages on, where both take 8.2 us: with 20 7.0 and 8.3, with 64 10.7 and 8.0.
       int64_t cand[10] = {1, 2, 3, 4};
       for (int l = 1; l <= 6; ++l) cand[3 + l] = l * kCUs / tiles;
+      const int64_t most = nk >= 36 ? std::min<int64_t>(nk, max_split) : max_split;
       int64_t last = 0;
       for (int64_t ns : cand) {
-        if (max_ws_bytes != SIZE_MAX) ns = std::min<int64_t>(ns, max_split);
+        if (c.tile == WgTile::k64 && last <= 4) ns = std::min(ns, most);
         if (ns <= last || ns > max_split || ns > nk) continue;
         last = ns;
         const int64_t st = (nk + ns - 1) / ns, wgs = tiles * ((nk + st - 1) / st);
