@@ -128,8 +128,10 @@ def short_kernel_name(name):
     name = name.replace("(anonymous namespace)::", "")
     name = name.split("(")[0].replace("void ", "")
     name = name.replace("fg::dma::", "").replace("fg::", "")
-    # the pipeline configuration: dropped, except a tile other than 256 x 256
+    # the pipeline configuration: dropped, except a tile other than 256 x 256, and
+    # that the smaller data-convolution tile has 32-deep stages
     name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, 256, 256>, ", "", name)
+    name = re.sub(r"Pipe<32, \d+, \d+, \d+, (\d+), \1>, ", r"\1/32, ", name)
     name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, (\d+), \1>, ", r"\1, ", name)
     name = re.sub(r"Pipe<\d+, \d+, \d+, \d+, (\d+), (\d+)>, ", r"\1x\2, ", name)
     name = re.sub(r"K<\d+, \d+, \d+, \d+(, 256)?>, ", "", name)

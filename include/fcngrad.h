@@ -515,7 +515,8 @@ fg_status grad_group_plan(const uint64_t *numel, int32_t ntensors,
  * the workspace that fg_conv_workspace_bytes asks for (a static string; "" for
  * an invalid or unsupported shape): the template's name and arguments as a
  * kernel trace prints them, without namespaces, and with a pipeline's
- * configuration as its tile (nothing for 256 x 256, 128 for 128 x 128, 64x128).
+ * configuration as its tile (nothing for 256 x 256, 128 for 128 x 128, 64x128,
+ * 128/32 for 128 x 128 in 32-deep stages).
  * Lets a profiler or benchmark group launches the way a kernel trace does. */
 const char *fg_conv_kernel_name(const fg_conv_desc *d, int op);
 

@@ -929,6 +929,7 @@ __device__ __forceinline__ void data_tile(const DataConvArgs &a, const TileMap &
 using Data64 = Pipe<64, 3, 2, 2, 64, 64>;       // 4 waves of 32 x 32
 using Data64x128 = Pipe<64, 3, 2, 4, 64, 128>;  // 8 waves of 32 x 32
 using Data128 = Pipe<64, 2, 4, 2, 128, 128>;    // 8 waves of 32 x 64
+using Data128d32 = Pipe<32, 5, 2, 2, 128, 128>;  // 4 waves of 64 x 64
 using Data256 = Pipe<32, 5, 2, 4, 256, 256>;    // 8 waves of 128 x 64
 
 // The kernels by what a stage and a sum are: whole taps per stage (overloading the
@@ -953,14 +954,22 @@ using DataTileKernel = void (*)(DataConvArgs, TileMap, PosDiv);
 
 template <class P, bool WK>
 static DataTileKernel data_tile_kernel(bool split, bool gen, bool fold) {
-  if constexpr (P::TM == 256)  // whole taps: the kernel above; it cannot fold
+  if constexpr (P::TM == 256) {  // whole taps: the kernel above; it cannot fold
     return split ? data_conv_gen_kernel<P, WK, true> : data_conv_gen_kernel<P, WK, false>;
-  else if (fold)
-    return gen ? data_conv_fold_kernel<P, WK, true> : data_conv_fold_kernel<P, WK, false>;
-  else if (gen)
-    return split ? data_conv_gen_kernel<P, WK, true> : data_conv_gen_kernel<P, WK, false>;
-  return split ? static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, true>)
-               : static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, false>);
+  } else if constexpr (P::BK == 32) {  // whole taps and parts
+    if constexpr (!WK) {  // weights read as they lie: only split sums
+      if (fold) return data_conv_fold_kernel<P, WK, false>;
+      if (!split) return data_conv_dma_kernel<P, WK, false>;
+    }
+    return data_conv_dma_kernel<P, WK, true>;
+  } else {
+    if (fold)
+      return gen ? data_conv_fold_kernel<P, WK, true> : data_conv_fold_kernel<P, WK, false>;
+    if (gen)
+      return split ? data_conv_gen_kernel<P, WK, true> : data_conv_gen_kernel<P, WK, false>;
+    return split ? static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, true>)
+                 : static_cast<DataTileKernel>(data_conv_dma_kernel<P, WK, false>);
+  }
 }
 
 template <class P>
@@ -1307,7 +1316,7 @@ bool data_tile_ok(const DataConvArgs &a) {
 }
 
 DataTileMode data_tile_mode(const DataConvArgs &a, DataTile tile) {
-  const int bk = tile == DataTile::k256 ? dma::Data256::BK : dma::Data64::BK;
+  const int bk = tile == DataTile::k256 || tile == DataTile::k128d32 ? 32 : dma::Data64::BK;
   static_assert(dma::Data64::BK == dma::Data64x128::BK && dma::Data64::BK == dma::Data128::BK);
   bool gen = a.cr % bk != 0;
   for (int i = 0; a.nsplit > 1 && i < a.nphase; ++i)  // parts that end within a stage
@@ -1325,6 +1334,8 @@ hipError_t launch_data_conv_tile(const DataConvArgs &a, DataTile tile, bool w_km
       return dma::launch_data_tile<dma::Data64x128>(a, w_kmajor, gen, fold, st);
     case DataTile::k128:
       return dma::launch_data_tile<dma::Data128>(a, w_kmajor, gen, fold, st);
+    case DataTile::k128d32:
+      return dma::launch_data_tile<dma::Data128d32>(a, w_kmajor, gen, fold, st);
     case DataTile::k256:
       return data_halo_ok(a) ? launch_data_conv_halo(a, w_kmajor, st)
              : gen           ? dma::launch_data_tile<dma::Data256>(a, w_kmajor, true, false, st)

@@ -893,7 +893,8 @@ constexpr DataTileCost kDataTiles[] = {
     {DataTile::k256, 256, 256, 32, 6.9, 1.10, 1.45},
     {DataTile::k128, 128, 128, 64, 4.4, 0.63, 0.46},
     {DataTile::k64x128, 64, 128, 64, 4.2, 0.38, 0.33},
-    {DataTile::k64, 64, 64, 64, 3.9, 0.29, 0.217}};
+    {DataTile::k64, 64, 64, 64, 3.9, 0.29, 0.217},
+    {DataTile::k128d32, 128, 128, 32, 4.4, 0.70, 0.52}};
 constexpr double kHaloShared = 1.33;      // of 256 x 256 tiles whose input is reused
 constexpr double kGen256Shared = 1.95;    // of 256 x 256 tiles across taps
 constexpr double kGenFactor = 1.2;        // stages across taps, the other tiles
@@ -903,6 +904,27 @@ constexpr double kDataStoreBw = 2.66e6;   // bytes/us of the fp16 output
 constexpr double kDataReduce = 3.2;       // us: the second launch of a split
 constexpr double kDataPartialBw = 5.3e6;  // bytes/us, 8 per partial element
 constexpr int kMaxDataSplit = 16;
+
+// Whether 128 x 128 tiles in ns parts take 32-deep stages (4 waves, a ring of five)
+// instead of 64-deep ones (8 waves, two): where a 64-deep stage would straddle taps
+// or parts and a 32-deep one does not. With weights read transposed always: 96
+// channels, K 3096 over 14756 positions 18.7 us, 22.7 in 64-deep stages; 224, K 2016
+// over 143260 163 and 183 (436 such passes 0.93 of the time in the geometric mean,
+// 6 of them more than 1.03). With weights read as they lie only for a split into
+// parts of 20 and more 64-deep stages, one workgroup to a CU at most: 576 channels,
+// K 6656 over 1298 positions 40.8 and 47.0 (55 passes 0.90); with more to a CU they
+// take 0.95 to 1.07 of the time, shorter, whole and folded sums 0.97 to 1.13, as 128
+// channels, K 864 over 22960 14.6 and 13.4.
+static bool deep32(const DataConvArgs &a, const PartCount &so, int ns) {
+  if (a.cr % 32 != 0) return false;
+  bool straddles = a.cr % 64 != 0;
+  for (int i = 0; a.fixed_order && ns > 1 && i < a.nphase; ++i)
+    straddles |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, 32, ns) % 64 != 0;
+  const bool mn = a.ldw == 0;
+  return straddles &&
+         (mn || (ns > 1 && part_len(a.ph[0].nr * a.ph[0].ns * a.cr, 32, so.n) >= 20 * 64 &&
+                 data_work(a, 128, 128, 64).tiles * ns <= kCUs));
+}
 
 // max_ws_bytes bounds the partials of a split whose order is free.
 static DataPlan make_data_plan(const DataConvArgs &a, size_t max_ws_bytes) {
@@ -936,6 +958,10 @@ static DataPlan make_data_plan(const DataConvArgs &a, size_t max_ws_bytes) {
         if (fixed && ns > 1)  // a part may end within a stage
           for (int i = 0; i < a.nphase; ++i)
             gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, unit, ns) % c.bk != 0;
+        // 32-deep stages: here against the smallest tiles, else see below
+        if (c.tile == DataTile::k128d32 &&
+            !(pl.tile == DataTile::k64 && mn && deep32(a, so, ns)))
+          continue;
         double shared = c.shared, f = mn ? kMnFactor : 1.0;
         if (c.tm == 256)
           shared = halo ? kHaloShared : gen ? kGen256Shared : c.shared;
@@ -956,9 +982,10 @@ static DataPlan make_data_plan(const DataConvArgs &a, size_t max_ws_bytes) {
       }
     }
   }
+  if (pl.tile == DataTile::k128 && deep32(a, so, pl.nsplit)) pl.tile = DataTile::k128d32;
   pl.nchunk = fixed ? so.n : pl.nsplit;
   // the kernels' own stages where the order is free
-  pl.unit = fixed ? unit : pl.tile == DataTile::k256 ? 32 : 64;
+  pl.unit = fixed ? unit : pl.tile == DataTile::k256 || pl.tile == DataTile::k128d32 ? 32 : 64;
   pl.ws_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * out * sizeof(float) : 0;
   return pl;
 }
@@ -1046,7 +1073,7 @@ hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor, hipStream_t st
 
 // Kernel names as a kernel trace prints them, without namespaces, and with a
 // pipeline's configuration (Pipe<...>, K<...>) as its tile: nothing for 256 x 256,
-// T for a square, TMxTN else. F2: by two truth values, F3: by three.
+// T for a square, TMxTN else, "/32" after a smaller one in 32-deep stages. F2: by two truth values, F3: by three.
 #define F2(K, T)                                  \
   {                                               \
     {K "<" T "false, false>", K "<" T "false, true>"}, \
@@ -1057,15 +1084,18 @@ hipError_t launch_data_conv(const DataConvArgs &a, bool w_kmajor, hipStream_t st
 
 const char *data_conv_kernel_name(const DataConvArgs &a0, bool w_kmajor) {
   static const char *halo[2][2] = F2("data_conv_halo_kernel", "");  // weights, split
-  static const char *dma[4][2][2] = {  // by DataTile, then the same
+  static const char *dma[5][2][2] = {  // by DataTile, then the same
       F2("data_conv_dma_kernel", ""), F2("data_conv_dma_kernel", "128, "),
-      F2("data_conv_dma_kernel", "64x128, "), F2("data_conv_dma_kernel", "64, ")};
-  static const char *gen[4][2][2] = {
+      F2("data_conv_dma_kernel", "64x128, "), F2("data_conv_dma_kernel", "64, "),
+      F2("data_conv_dma_kernel", "128/32, ")};
+  static const char *gen[5][2][2] = {
       F2("data_conv_gen_kernel", ""), F2("data_conv_gen_kernel", "128, "),
-      F2("data_conv_gen_kernel", "64x128, "), F2("data_conv_gen_kernel", "64, ")};
-  static const char *fold[4][2][2] = {  // weights, stages across taps
+      F2("data_conv_gen_kernel", "64x128, "), F2("data_conv_gen_kernel", "64, "),
+      F2("data_conv_gen_kernel", "128/32, ")};
+  static const char *fold[5][2][2] = {  // weights, stages across taps
       {{"", ""}, {"", ""}}, F2("data_conv_fold_kernel", "128, "),
-      F2("data_conv_fold_kernel", "64x128, "), F2("data_conv_fold_kernel", "64, ")};
+      F2("data_conv_fold_kernel", "64x128, "), F2("data_conv_fold_kernel", "64, "),
+      F2("data_conv_fold_kernel", "128/32, ")};
   static const char *staged[2][2][2][2] = {  // weights, whole taps per slice, split
       F3("data_conv_staged_kernel", "Cfg<128, 128, 2, 2>, "),
       F3("data_conv_staged_kernel", "Cfg<256, 256, 2, 4>, ")};

@@ -64,6 +64,7 @@ struct DataConvArgs {
 // Tile and split choice for a data convolution (pure host logic).
 enum class DataTile : int32_t {
   k256, k128, k64x128, k64,  // fed by LDS DMA, channels x positions (conv_dma.hip)
+  k128d32,                   // 128 x 128 in 32-deep stages (cr a multiple of 32)
   kStaged256, kStaged128     // register-staged: tensors beyond a buffer resource
 };
 // Length of each of n parts of a reduction of ktot, a multiple of `unit`.

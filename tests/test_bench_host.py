@@ -148,6 +148,7 @@ def test_kernel_names_from_the_trace_match_the_library_names():
              "(fg::DataConvArgs, fg::dma::TileMap)") == "data_conv_dma_kernel<128, false, true>"
     args = "(fg::DataConvArgs, fg::dma::TileMap, fg::dma::PosDiv)"
     for pipe, tile in (("32, 5, 2, 4, 256, 256", ""), ("64, 2, 4, 2, 128, 128", "128, "),
+                       ("32, 5, 2, 2, 128, 128", "128/32, "),
                        ("64, 3, 2, 4, 64, 128", "64x128, "), ("64, 3, 2, 2, 64, 64", "64, ")):
         for k in ("dma", "gen", "fold"):
             assert f(f"void fg::dma::data_conv_{k}_kernel<fg::dma::Pipe<{pipe}>, true, false>"

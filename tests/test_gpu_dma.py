@@ -34,6 +34,10 @@ CASES = [
     ((4, 64, 64, 256, 128, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
     ((1, 77, 79, 512, 512, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, true>"),
     ((1, 127, 129, 512, 256, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128, false, false>"),
+    # 128 x 128 tiles in 32-deep stages
+    ((1, 97, 61, 344, 96, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128/32, false, false>"),
+    ((5, 121, 81, 72, 288, 3, 2, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<128/32, false, false>"),
+    ((4, 9, 89, 576, 144, 3, 1, 1), fg.OP_FWD, "data_conv_dma_kernel<128/32, true, true>"),
     # smaller ones
     ((4, 77, 79, 288, 256, 1, 1, 0), fg.OP_BWD_DATA, "data_conv_dma_kernel<64x128, false, false>"),
     ((2, 15, 17, 1024, 1024, 3, 1, 1), fg.OP_BWD_DATA, "data_conv_dma_kernel<64x128, false, true>"),

@@ -95,6 +95,9 @@ CASES = [
     ((4, 13, 64, 16, 88, 3, 1, 1), DX, "data_conv_gen_kernel<64x128, false, true>"),
     ((2, 74, 64, 392, 264, 3, 1, 1), DX, "data_conv_gen_kernel<false, true>"),
     ((3, 6, 13, 928, 200, 3, 1, 1), DW, "wgrad_dma_kernel<128, false>"),
+    ((4, 9, 89, 576, 144, 3, 1, 1), FWD, "data_conv_dma_kernel<128/32, true, true>"),
+    ((2, 129, 64, 72, 32, 3, 1, 1), DX, "data_conv_dma_kernel<128/32, false, false>"),
+    ((3, 45, 32, 72, 288, 3, 1, 1), DX, "data_conv_dma_kernel<128/32, false, true>"),
 ]
 
 # transposed convolutions, 4x4 stride 2 pad 1: (n, h, w, c_in, c_out)
@@ -122,6 +125,9 @@ CONVT = [
     ((1, 12, 67, 272, 16), "data_conv_gen_kernel<64x128, false, true>"),
     ((3, 65, 32, 56, 400), "data_conv_gen_kernel<false, false>"),
     ((1, 21, 64, 744, 392), "data_conv_gen_kernel<false, true>"),
+    ((7, 49, 18, 32, 72), "data_conv_dma_kernel<128/32, false, false>"),
+    ((7, 30, 4, 416, 72), "data_conv_dma_kernel<128/32, false, true>"),
+    ((5, 21, 32, 224, 264), "data_conv_fold_kernel<128/32, false, false>"),
 ]
 
 F16_MAX_FINITE = 65504.0
@@ -312,6 +318,11 @@ def all_kernels():
         if op != DX:            # passes whose order of sums is fixed
             out |= {(op, f"data_conv_fold_kernel<{t}{wk}, {gen}>")
                     for t in tiles for gen in ("true", "false")}
+    # 128 x 128 tiles in 32-deep stages: whole taps and parts; forward, split sums
+    out |= {(op, f"data_conv_dma_kernel<128/32, false, {split}>")
+            for op in (DX, "convT") for split in ("true", "false")}
+    out |= {(FWD, "data_conv_dma_kernel<128/32, true, true>"),
+            ("convT", "data_conv_fold_kernel<128/32, false, false>")}
     out |= {(DW, f"wgrad_dma_kernel<{t}{split}>") for t in ("", "128, ", "64, ")
             for split in ("true", "false")}
     return out | {(FWD, "head_fwd_kernel"), (DX, "head_bwd_data_kernel"),

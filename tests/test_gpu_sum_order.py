@@ -51,6 +51,8 @@ CASES = [
      "gen_kernel<64x128, false, true>"),
     (CT, (51, 41, 512, 80, 4, 2, 1), 4, 1, 3, "fold_kernel<128, false, false>",
      "dma_kernel<128, false, true>"),
+    (CT, (17, 69, 416, 72, 4, 2, 1), 7, 2, 3, "fold_kernel<128/32, false, false>",
+     "dma_kernel<128/32, false, true>"),
     (CT, (18, 53, 456, 144, 4, 2, 1), 4, 3, 2, "fold_kernel<128, false, true>",
      "gen_kernel<128, false, true>"),
 ]
