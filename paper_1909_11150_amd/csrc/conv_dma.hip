@@ -581,8 +581,9 @@ static TileMap data_tile_map(DataConvArgs &a, int tm_, int tn_) {
 // workgroup's stages and what two launches of a split cost. These tiles (64 x
 // 64, 64 channels x 128 positions, 128 x 128) have 64-deep stages (whole
 // 128-byte lines, half the barriers), two waves per SIMD and workgroup for the
-// two larger ones, and a store through LDS in whole rows. Against the 128 x 128
-// tiles of 4 waves in 32-deep stages that ran these shapes: 128 channels, K 1152
+// two larger ones, and a store through LDS in whole rows. Where 64-deep stages
+// would straddle taps, 128 x 128 tiles have 4 waves and 32-deep stages (deep32 in
+// conv_igemm.hip). Against such tiles on all of these shapes: 128 channels, K 1152
 // over 32768 positions 19.9 -> 15.5 us; the strided input gradient of 64
 // channels, K 128 to 512 over 131072 28.4 -> 16.5; 64 channels, K 576 over 6240
 // 11.7 -> 6.6; the register-staged kernel on 512 channels, K 2376 over 65536
