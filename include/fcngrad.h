@@ -61,7 +61,7 @@
  *   - Results are bit-reproducible for a fixed device, shape and input:
  *     every sum is evaluated in a fixed order (no floating-point atomics). A
  *     gradient given less workspace than fg_conv_workspace_bytes() has an
- *     order of its own, also fixed.
+ *     order of its own, also fixed (see there).
  *   - Tensor sizes must stay below 2^31 elements per tensor.
  */
 #ifndef FCNGRAD_H
@@ -351,10 +351,11 @@ fg_status fg_profile_next_launch(hipEvent_t start, hipEvent_t stop);
 /* Workspace in bytes that the given pass needs for this shape (0 if none).
  * conv2d_bwd_data and conv2d_bwd_weight[_checked] also accept less, down to a
  * least size per shape (often the same, possibly 0): they then split the
- * reduction into the fewer, longer parts that fit the least size, which takes
- * longer and adds in another order. The least size is what this query returned
- * before the kernels took more parts, so a program that kept that size works
- * on; programs that ask need not know it. */
+ * reduction into the fewer, longer parts that fit what this query returned
+ * before the kernels took more parts, which takes longer and adds in another
+ * order. A program that kept such a size works on; programs that ask need not
+ * know it. (Kernel gradients of a few small tiles have two such sizes, each with
+ * a fixed plan: the larger one that the workspace holds is used.) */
 size_t fg_conv_workspace_bytes(const fg_conv_desc *d, int op);
 
 /* ---- optimizer (Section 6.2: layer-wise adaptive rates with Adam) ------ */

@@ -291,9 +291,9 @@ fg_status check_ws(const fg_conv_desc *d, int op, void *ws, size_t ws_bytes,
 
 // Bound on the split partials that the plan of a gradient call keeps to, given what
 // the plan without a bound needs, the least the call accepts and what it brings:
-// none, or exactly that least, so that a shape has two plans and no more. (The
-// least is what the query gave before the kernels took more splits; a program that
-// kept that size need not ask again.)
+// none, or exactly that least, so that a shape has two or three plans and no more.
+// (The least is what the query gave before the kernels took more splits; a program
+// that kept that size need not ask again.)
 size_t plan_bound(size_t need, size_t least, const void *ws, size_t ws_bytes) {
   const size_t has = ws ? ws_bytes : 0;
   return has < need && has >= least ? least : SIZE_MAX;
@@ -568,7 +568,8 @@ static fg_status bwd_weight(const fg_conv_desc *d, const uint16_t *x,
   size_t need = d->k == 1 ? head_wgrad_ws_bytes(*d)
                           : plan_wgrad(*d, P, Q, plan_cap).ws_bytes;
   if (!noalloc && d->k != 1 && need && (!ws || ws_bytes < need)) {
-    plan_cap = plan_bound(need, wgrad_least_ws_bytes(*d, P, Q), ws, ws_bytes);
+    plan_cap = plan_bound(need, wgrad_least_ws_bytes(*d, P, Q, ws ? ws_bytes : 0), ws,
+                          ws_bytes);
     need = plan_wgrad(*d, P, Q, plan_cap).ws_bytes;
   }
   if (noalloc) {

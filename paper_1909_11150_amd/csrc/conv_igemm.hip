@@ -1165,23 +1165,9 @@ static WgradPlan plan_staged(int64_t rsc, int64_t k, int64_t mtot, int max_split
   return pl;
 }
 
-// The least workspace of a kernel gradient: that of the split the earlier kernels
-// took (their rates fitted to the network's layers; up to 16 parts, or 256 where
-// the gradient has no 256 x 256 tile).
-size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q) {
-  constexpr PartRates kRates{6.35e12, 1.3e12, 1.3e12, 4.05e12, 6.3e-6, 4.2e-6};
-  const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k, mtot = (int64_t)d.n * p * q;
-  const bool big = rsc >= 256 && k >= 256;
-  auto tiles = [&](int64_t t) { return ((rsc + t - 1) / t) * ((k + t - 1) / t); };
-  const PartCount pc = part_count(tiles(256), tiles(128), (mtot + BK - 1) / BK, k * rsc, big,
-                                  kRates, big ? 16 : kMaxWgradSplit);
-  const int64_t chunk = ((mtot + pc.n - 1) / pc.n + BK - 1) / BK * BK;
-  const int64_t ns = (mtot + chunk - 1) / chunk;
-  return ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
-}
-
+// all_stages: a few tiles may split into as many parts as there are stages.
 static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
-                                 size_t max_ws_bytes) {
+                                 size_t max_ws_bytes, bool all_stages = true) {
   const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k;
   const int64_t mtot = (int64_t)d.n * p * q;
   const size_t cap = max_ws_bytes / ((size_t)k * rsc * sizeof(float));
@@ -1207,7 +1193,8 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
       // stages on, where both take 8.2 us: with 20 7.0 and 8.3, with 64 10.7 and 8.0.
       int64_t cand[10] = {1, 2, 3, 4};
       for (int l = 1; l <= 6; ++l) cand[3 + l] = l * kCUs / tiles;
-      const int64_t most = nk >= 36 ? std::min<int64_t>(nk, max_split) : max_split;
+      const int64_t most =
+          all_stages && nk >= 36 ? std::min<int64_t>(nk, max_split) : max_split;
       int64_t last = 0;
       for (int64_t ns : cand) {
         if (c.tile == WgTile::k64 && last <= 4) ns = std::min(ns, most);
@@ -1232,6 +1219,26 @@ static WgradPlan make_wgrad_plan(const fg_conv_desc &d, int32_t p, int32_t q,
   pl.mchunk = (int32_t)chunk;
   pl.ws_bytes = ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
   return pl;
+}
+
+// The size below the plan's own that a kernel gradient given `has` bytes keeps to:
+// that of the split the earlier kernels took (their rates fitted to the network's
+// layers; up to 16 parts, or 256 where the gradient has no 256 x 256 tile), or, if
+// the call brings less, that of the plan without splits into all stages where
+// that is smaller. The query gave both, so programs may keep either.
+size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q, size_t has) {
+  constexpr PartRates kRates{6.35e12, 1.3e12, 1.3e12, 4.05e12, 6.3e-6, 4.2e-6};
+  const int64_t rsc = (int64_t)d.r * d.s * d.c, k = d.k, mtot = (int64_t)d.n * p * q;
+  const bool big = rsc >= 256 && k >= 256;
+  auto tiles = [&](int64_t t) { return ((rsc + t - 1) / t) * ((k + t - 1) / t); };
+  const PartCount pc = part_count(tiles(256), tiles(128), (mtot + BK - 1) / BK, k * rsc, big,
+                                  kRates, big ? 16 : kMaxWgradSplit);
+  const int64_t chunk = ((mtot + pc.n - 1) / pc.n + BK - 1) / BK * BK;
+  const int64_t ns = (mtot + chunk - 1) / chunk;
+  const size_t earlier = ns > 1 ? (size_t)ns * k * rsc * sizeof(float) : 0;
+  return has >= earlier
+             ? earlier
+             : std::min(earlier, make_wgrad_plan(d, p, q, SIZE_MAX, false).ws_bytes);
 }
 
 // max_ws_bytes bounds the fp32 partials of a split (and so the split count);

@@ -117,7 +117,7 @@ struct WgradPlan {
 // ws_bytes <= max_ws_bytes (fewer splits when the best plan needs more).
 WgradPlan plan_wgrad(const fg_conv_desc &d, int32_t p, int32_t q,
                      size_t max_ws_bytes = SIZE_MAX);
-size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q);
+size_t wgrad_least_ws_bytes(const fg_conv_desc &d, int32_t p, int32_t q, size_t has);
 
 // The same span for the kernel gradient's x.
 __host__ __device__ inline size_t x_span_bytes(const WgradArgs &a) {

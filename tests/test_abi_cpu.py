@@ -197,6 +197,27 @@ def test_gradients_accept_the_least_workspace(L, shape, op, least, full):
         assert call(None, full) == fg.FG_EWORKSPACE
 
 
+# Kernel gradients of one to a few small tiles: the query gave `least` (a few parts)
+# and before that `mid`; `full` splits into as many parts as there are stages.
+LEAST_OF_TWO_WS = [
+    ((3, 143, 17, 16, 8, 1, 1, 0), 2048, 14848, 58368),
+    ((2, 15, 159, 8, 32, 3, 1, 0), 36864, 147456, 589824),
+    ((3, 44, 29, 24, 16, 3, 1, 0), 55296, 193536, 746496),
+]
+
+
+@pytest.mark.parametrize("shape,least,mid,full", LEAST_OF_TWO_WS, ids=str)
+def test_kernel_gradients_accept_both_smaller_workspaces(L, shape, least, mid, full):
+    n, h, w, c, k, r, st, pd = shape
+    d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
+    assert L.fg_conv_workspace_bytes(ctypes.byref(d), fg.OP_BWD_WEIGHT) == full
+    x, dy, wt = FAKE, FAKE + (1 << 28), FAKE + (1 << 30)
+    call = lambda nbytes: L.conv2d_bwd_weight(ctypes.byref(d), x, dy, wt, x, nbytes, None)
+    for nbytes in (full, full - 1, mid, mid - 1, least):   # enough, but overlaps x
+        assert call(nbytes) == fg.FG_EINVAL, nbytes
+    assert call(least - 1) == fg.FG_EWORKSPACE
+
+
 def test_plans_follow_the_estimate(L):
     """Shapes that were planned apart from the time estimate take the plan it
     finds cheapest: one 128 x 128 launch instead of the input-reuse kernel in

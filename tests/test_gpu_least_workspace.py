@@ -9,7 +9,7 @@ import oracle
 import paper_1909_11150_amd as fg
 import synth
 from gpu_util import conv_parity, dev, empty16, host, sample_indices, workspace
-from test_abi_cpu import LEAST_WS
+from test_abi_cpu import LEAST_OF_TWO_WS, LEAST_WS
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,31 @@ def test_least_workspace(shape, op, least, full):
     np.testing.assert_array_equal(small, run(full - 1))   # one plan below the full size
     for got in (whole, small):
         conv_parity(got.view(np.float16).ravel()[idx], ref, f"{shape} {op}")
+
+
+@pytest.mark.parametrize("shape,least,mid,full", LEAST_OF_TWO_WS, ids=str)
+def test_both_smaller_workspaces(shape, least, mid, full):
+    """Three plans, by what the call brings: each against the oracle, nothing
+    written past the size, and one plan between two of the sizes."""
+    n, h, w, c, k, r, st, pd = shape
+    d = fg.ConvDesc.make(n, h, w, c, k, r, r, st, pd)
+    p, q = fg.out_dims(d)
+    rng = np.random.default_rng(sum(shape))
+    x, dy = synth.uniform(rng, (n, h, w, c)), synth.uniform(rng, (n, p, q, k))
+    oshape = (k, r, r, c)
+    idx = sample_indices(oshape, 2500, rng)
+    ref = oracle.conv2d_bwd_weight_points(x, dy, r, r, idx, st, pd)
+    xd, dyd = dev(x), dev(dy)
+    buf = torch.empty(full + 4096, dtype=torch.uint8, device="cuda")
+
+    def run(nbytes):
+        buf.fill_(0x5A)
+        out = empty16(oshape)
+        fg.conv2d_bwd_weight(d, xd, dyd, out, buf[:nbytes])
+        assert bool((buf[nbytes:] == 0x5A).all())
+        return host(out).view(np.uint16)
+
+    for lo, hi in ((least, mid - 1), (mid, full - 1), (full, full + 4096)):
+        got = run(lo)
+        np.testing.assert_array_equal(got, run(hi))
+        conv_parity(got.view(np.float16).ravel()[idx], ref, f"{shape} {lo}")
