@@ -958,9 +958,10 @@ static DataPlan make_data_plan(const DataConvArgs &a, size_t max_ws_bytes) {
         if (fixed && ns > 1)  // a part may end within a stage
           for (int i = 0; i < a.nphase; ++i)
             gen |= part_len(a.ph[i].nr * a.ph[i].ns * a.cr, unit, ns) % c.bk != 0;
-        // 32-deep stages: here against the smallest tiles, else see below
-        if (c.tile == DataTile::k128d32 &&
-            !(pl.tile == DataTile::k64 && mn && deep32(a, so, ns)))
+        // 32-deep stages: here against the smallest tiles, in no more parts (and so no
+        // more workspace) than those take, else see below
+        if (c.tile == DataTile::k128d32 && !(pl.tile == DataTile::k64 &&
+                                             ns <= pl.nsplit && mn && deep32(a, so, ns)))
           continue;
         double shared = c.shared, f = mn ? kMnFactor : 1.0;
         if (c.tm == 256)

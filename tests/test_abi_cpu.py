@@ -218,6 +218,14 @@ def test_kernel_gradients_accept_both_smaller_workspaces(L, shape, least, mid, f
     assert call(least - 1) == fg.FG_EWORKSPACE
 
 
+def test_input_gradient_keeps_needing_no_workspace(L):
+    """128 x 128 tiles in 32-deep stages replace 64 x 64 ones in no more parts:
+    this input gradient, unsplit on the small tiles, is still called with none."""
+    d = fg.ConvDesc.make(8, 3, 252, 72, 224, 3, 3, 1, 1)
+    assert L.fg_conv_workspace_bytes(ctypes.byref(d), fg.OP_BWD_DATA) == 0
+    assert "kernel<64, " in fg.kernel_name(d, fg.OP_BWD_DATA)
+
+
 def test_plans_follow_the_estimate(L):
     """Shapes that were planned apart from the time estimate take the plan it
     finds cheapest: one 128 x 128 launch instead of the input-reuse kernel in
