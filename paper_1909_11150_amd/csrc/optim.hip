@@ -109,23 +109,22 @@ __device__ __forceinline__ uint16_t stored_f32_to_h(float v) {
 }
 
 // Streaming access. An update reads 14 or 16 bytes per parameter twice and writes
-// 14. Where the arrays do not fit the Infinity Cache, nothing of an array is
-// found there when the update comes back to it, and what it allocates pushes out
-// what the step still needs and has to be written back: its large accesses are
-// then non-temporal (NT). Where they fit, the apply pass finds what the norms
-// pass read. Norms and apply, plain and NT: 9 M parameters 70 and 77 us, 16 M 114
-// and 125, 20 M 166 and 152, 38.9 M 352 and 279 (fp32 gradients; 16 M of them
-// read 256 MB).
+// 14. The apply pass is the last to read an array, and what it writes is not read
+// before the next update: its large accesses are non-temporal (NT), which leaves
+// the caches to the rest of the step and to what the norms pass put there. The norms
+// pass reads plainly where the arrays fit the Infinity Cache, so that the apply
+// pass finds them, and non-temporally where they do not. Whole updates with fp32
+// gradients, us, all plain / all NT / this (16 M parameters read 256 MB; "cold": two
+// to four updates' arrays in turn):
+//   bare, repeated  9 M 70 / 74 / 71,  12 M 89 / 98 / 96,   20 M 167 / 153 / 153
+//   bare, cold      8 M 78 / 70 / 64,  12 M 106 / 95 / 93,  20 M 190 / 152 / 152
+//   after the gradient path, cold  8 M 107 / 103 / 96,  12 M 148 / 141 / 137
 template <bool NT, class T>
 __device__ __forceinline__ T ld_opt(const T *p) {
   return NT ? __builtin_nontemporal_load(p) : *p;
 }
-template <bool NT>
 __device__ __forceinline__ void st_opt(float *p, const f32x4 &v) {
-  if (NT)
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
-  else
-    *reinterpret_cast<f32x4 *>(p) = v;
+  __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
 }
 
 // Gradient access: fp32 as stored, or fp16 times 1/S (materialised before
@@ -277,7 +276,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_ratio_kernel(
 }
 
 // Workgroup b0 + blockIdx.x of the table.
-template <bool H, bool NT>
+template <bool H>
 __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
     OptTable t, OptParams p, float inv, const int32_t *flags, int nflags,
     const float *ratio, const int32_t *t_cur, uint32_t b0) {
@@ -287,7 +286,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
   const OptPiece pc = t.p[pi];
   const OptStep s = opt_step(p, *t_cur);
   const float step = p.lr * ratio[pi];
-  const Grad<H, NT> gr{pc.g, inv};
+  const Grad<H, true> gr{pc.g, inv};
   float *wp = reinterpret_cast<float *>(pc.w32);
   float *mp = reinterpret_cast<float *>(pc.m);
   float *vp = reinterpret_cast<float *>(pc.v);
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
 #pragma unroll
   for (int c = 0; c < kOptIters; ++c) {
     const uint32_t i = beg + (c * kOptThreads + threadIdx.x) * 4;
-    load_chunk<H, NT>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
+    load_chunk<H, true>(pc, gr, i, end, g[c], w[c], m[c], v[c]);
   }
 #pragma unroll
   for (int c = 0; c < kOptIters; ++c) {
@@ -312,9 +311,9 @@ __global__ __launch_bounds__(kOptThreads) void lars_adam_apply_kernel(
       w[c][e] = w[c][e] - step * s.u(mm, vv);
     }
     if (i + 4 <= end) {
-      st_opt<NT>(mp + i, m[c]);
-      st_opt<NT>(vp + i, v[c]);
-      st_opt<NT>(wp + i, w[c]);
+      st_opt(mp + i, m[c]);
+      st_opt(vp + i, v[c]);
+      st_opt(wp + i, w[c]);
       u32x2 h;
       h[0] = (uint32_t)stored_f32_to_h(w[c][0]) |
              ((uint32_t)stored_f32_to_h(w[c][1]) << 16);
@@ -377,19 +376,13 @@ static void block_range(const OptTable &t, int32_t first, int32_t count, uint32_
   b1 = first + count < t.n ? t.p[first + count].block0 : t.nblocks;
 }
 
-// f(H, NT) with the gradient form and the access (see ld_opt) as constants. The
-// line is the Infinity Cache's 256 MiB against what the whole table's update
-// reads: the arrays of one launch of several are read again with all the others'.
-template <class F>
-static void opt_dispatch(const fg_opt_tensor *ts, int32_t n, bool fp16_grad, F &&f) {
-  using std::false_type, std::true_type;
+// Whether the norms pass reads non-temporally (see ld_opt): the line is the Infinity
+// Cache's 256 MiB against what the whole table's update reads, since the arrays of
+// one launch of several are read again with all the others'.
+static bool norms_nt(const fg_opt_tensor *ts, int32_t n, bool fp16_grad) {
   uint64_t elems = 0;
   for (int i = 0; i < n; ++i) elems += ts[i].numel;
-  const bool nt = elems * (fp16_grad ? 14 : 16) > (256ull << 20);
-  if (fp16_grad)
-    nt ? f(true_type{}, true_type{}) : f(true_type{}, false_type{});
-  else
-    nt ? f(false_type{}, true_type{}) : f(false_type{}, false_type{});
+  return elems * (fp16_grad ? 14 : 16) > (256ull << 20);
 }
 
 hipError_t launch_lars_adam_norms(const fg_opt_tensor *ts, int32_t n, int32_t first,
@@ -402,10 +395,13 @@ hipError_t launch_lars_adam_norms(const fg_opt_tensor *ts, int32_t n, int32_t fi
   uint32_t b0, b1;
   block_range(t, first, count, b0, b1);
   const OptWs w = opt_ws(ws, t.nblocks);
-  opt_dispatch(ts, n, fp16_grad, [&](auto h, auto nt) {
-    hipLaunchKernelGGL((lars_adam_norms_kernel<h.value, nt.value>), dim3(b1 - b0),
-                       dim3(kOptThreads), 0, st, t, p, inv_scale, step_count, b0, w.part);
-  });
+  const bool nt = norms_nt(ts, n, fp16_grad);
+  const auto k = fp16_grad ? nt ? lars_adam_norms_kernel<true, true>
+                                : lars_adam_norms_kernel<true, false>
+                 : nt      ? lars_adam_norms_kernel<false, true>
+                           : lars_adam_norms_kernel<false, false>;
+  hipLaunchKernelGGL(k, dim3(b1 - b0), dim3(kOptThreads), 0, st, t, p, inv_scale, step_count,
+                     b0, w.part);
   return hipGetLastError();
 }
 
@@ -426,11 +422,9 @@ hipError_t launch_lars_adam_apply(const fg_opt_tensor *ts, int32_t n, int32_t fi
   }
   uint32_t b0, b1;
   block_range(t, first, count, b0, b1);
-  opt_dispatch(ts, n, fp16_grad, [&](auto h, auto nt) {
-    hipLaunchKernelGGL((lars_adam_apply_kernel<h.value, nt.value>), dim3(b1 - b0),
-                       dim3(kOptThreads), 0, st, t, p, inv_scale, flags, nflags, w.ratio,
-                       w.t_cur, b0);
-  });
+  const auto k = fp16_grad ? lars_adam_apply_kernel<true> : lars_adam_apply_kernel<false>;
+  hipLaunchKernelGGL(k, dim3(b1 - b0), dim3(kOptThreads), 0, st, t, p, inv_scale, flags,
+                     nflags, w.ratio, w.t_cur, b0);
   return hipGetLastError();
 }
 

@@ -499,10 +499,10 @@ class StepProgram:
                              inv=self._inv_scale if fused else ctypes.c_float(1.0),
                              gb=2 if fused else 4, fused=fused,
                              n=sum(w.numel() for w in ch.w32))
-            # the kernels' template arguments: gradient form, and non-temporal
-            # access for updates that read more than the Infinity Cache holds
-            args = (fused, self._opt["n"] * (OPT_READ_BYTES + self._opt["gb"]) > 256 << 20)
-            self._opt["args"] = ", ".join(str(a).lower() for a in args)
+            # the kernels' template arguments: gradient form, and (norms) non-temporal
+            # reads for updates that read more than the Infinity Cache holds
+            nt = self._opt["n"] * (OPT_READ_BYTES + self._opt["gb"]) > 256 << 20
+            self._opt["h"], self._opt["nt"] = str(fused).lower(), str(nt).lower()
             self._keep.append(tab)
         last_dw = {}
 
@@ -582,7 +582,7 @@ class StepProgram:
                     ((self._apply[1],) if nl > 1 else ())
                 n_i = ch.w32[i].numel()
                 calls.append(Call(f"{ch.layers[i].name}.apply",
-                                  f"lars_adam_apply_kernel<{o['args']}>",
+                                  f"lars_adam_apply_kernel<{o['h']}>",
                                   (OPT_READ_BYTES + o["gb"] + OPT_WRITE_BYTES) * n_i,
                                   L_.lars_adam_apply,
                                   (o["tab"], nl, i, 1, ctypes.byref(self.params), o["fmt"],
@@ -622,7 +622,7 @@ class StepProgram:
         assert mem == list(range(first, first + count)), "a group is a layer range"
         o = self._opt
         n = sum(ch.w32[i].numel() for i in mem)
-        return [Call(f"G{gi}.norms", f"lars_adam_norms_kernel<{o['args']}>",
+        return [Call(f"G{gi}.norms", f"lars_adam_norms_kernel<{o['h']}, {o['nt']}>",
                      (OPT_READ_BYTES + o["gb"]) * n, L_.lars_adam_norms,
                      (o["tab"], len(ch.layers), first, count, ctypes.byref(self.params),
                       o["fmt"], o["inv"], ch.step_count.data_ptr(), ch.opt_ws.data_ptr(),

@@ -180,8 +180,8 @@ def test_apply_needs_norms_of_every_layer():
 @pytest.mark.parametrize("grad", ["fp32", "fp16"])
 def test_update_beyond_the_cache_keeps_the_bits(grad):
     """A layer's update does not depend on the others: with a layer added that
-    takes the arrays past the Infinity Cache (256 MiB of reads, where the
-    accesses become non-temporal), the small layers keep every bit; the large
+    takes the arrays past the Infinity Cache (256 MiB of reads, where the norms
+    pass reads non-temporally), the small layers keep every bit; the large
     layer's first moments and fp16 copies follow the update rule."""
     big = (256 << 20) // (16 if grad == "fp32" else 14) + 1
     w, m, v, g = _state(10)
