@@ -75,8 +75,8 @@ __device__ __forceinline__ void flag_nonfinite(int32_t *flag, bool bad) {
 // Index of the last of n table entries whose first workgroup, start(i), is at
 // most b (starts rise from 0). Every lane looks at its own entries, so the wave
 // waits for one load where a binary search waits for six or seven in turn: worth
-// it for the optimizer's long tables (60 tensors, 90 M elements 654 -> 642 us), not
-// for the few members of a gradient group.
+// it for the optimizer's long tables (60 tensors, 90 M elements 654 -> 642 us) and
+// for gradient groups of many members.
 template <class Start>
 __device__ __forceinline__ int find_entry(int n, uint32_t b, Start &&start) {
   int below = 0;

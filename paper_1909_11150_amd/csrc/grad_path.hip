@@ -48,12 +48,17 @@ struct PieceTable {
   Piece p[kMaxPieces];
 };
 
-// Binary search by the block index, which is the same in every lane: the entries
-// come by scalar loads from the kernel arguments, and a group has few members. One
-// vector load per lane and a ballot (find_entry, which the optimizer's longer
-// tables take) waits for memory once before every workgroup's copy: pack of the
-// nine 25 MiB groups 4.20 -> 4.53 TB/s without it, unpack 4.92 -> 5.11.
+// The piece of a workgroup: by binary search where there are few (the index is the
+// same in every lane, so the entries come by scalar loads from the kernel
+// arguments), else by one vector load per lane and a ballot (find_entry), which
+// waits once where the search waits for each step. Nine groups of 25 MiB, evicted,
+// search and ballot, us: pack of 1 member 103 / 110, of 16 (16 pieces) 109 / 111,
+// of 60 118 / 111; unpack of 4 196 / 191, of 16 203 / 196, of 60 207 / 199; the nine
+// groups of the full network, most of one member, 4.52 / 4.19 and 5.08 / 4.92 TB/s.
+template <int ESZ>
 __device__ __forceinline__ int find_piece(const PieceTable &t, uint32_t b) {
+  if (t.npiece > (ESZ == 2 ? 16 : 2))
+    return find_entry(t.npiece, b, [&](int i) { return t.p[i].block0; });
   int lo = 0, hi = t.npiece - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -69,7 +74,7 @@ __device__ __forceinline__ int find_piece(const PieceTable &t, uint32_t b) {
 template <int ESZ>
 __global__ __launch_bounds__(kGradThreads) void copy_pieces_kernel(
     PieceTable t) {
-  const int pi = find_piece(t, blockIdx.x);
+  const int pi = find_piece<ESZ>(t, blockIdx.x);
   const Piece pc = t.p[pi];
   constexpr int EPV = 16 / ESZ;                           // elements per vector
   constexpr int NV = kPieceElems / (kGradThreads * EPV);  // vectors per thread
